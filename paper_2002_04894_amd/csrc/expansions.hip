@@ -298,36 +298,30 @@ std::vector<float> lane_tables(const HostTables& h, int p) {
   std::vector<float> out((size_t)table_floats(p), 0.0f);
   size_t base = 0;
   for (int trans = 0; trans < 2; ++trans) {
-    int u = 0;
-    for (int n = 0; n <= p; ++n) {
-      const int sd = 2 * n + 1;
-      for (int cls = 0; cls < 2; ++cls) {
-        const int s = cls_size(n, cls);
-        for (int k = 0; k < s; ++k)
-          for (int c = 0; c < chunks(s); ++c, ++u)
-            for (int i = 0; i < 4; ++i) {
-              const int r = 4 * c + i;
-              if (r >= s) continue;
-              const int a = cls_member(n, cls, r), b = cls_member(n, cls, k);
-              const double v = trans ? h.J[h.joff[n] + b * sd + a] : h.J[h.joff[n] + a * sd + b];
-              out[base + (size_t)(u / 16) * 64 + 4 * (u % 16) + i] = (float)v;
-            }
+    for (int st = 0; st < ju_steps(p); ++st)
+      for (int b = 0; b < 4; ++b) {
+        const int n = ju_degree(p, st, b), cls = st & 1, a = b & 1, rows = ju_rows(p, st, b);
+        for (int k = 0; k < ju_cols(p, st, b); ++k)
+          for (int r = 0; r < rows; ++r) {
+            const int step = j_step(cls_size(n, cls)), sd = 2 * n + 1;
+            const int row = cls_member(n, cls, j_first_row(n, cls, a) + step * r), col = cls_member(n, cls, a + step * k);
+            const double v = trans ? h.J[h.joff[n] + col * sd + row] : h.J[h.joff[n] + row * sd + col];
+            const int u = ju(p, st, k, b) + r / 4;
+            out[base + (size_t)(u / 16) * 64 + 4 * (u % 16) + r % 4] = (float)v;
+          }
       }
-    }
     base += (size_t)64 * groups(n_j(p));
   }
   const int P1 = p + 1;
-  int u = 0;
-  for (int m = 0; m <= p; ++m) {
-    const int s = p + 1 - m;
-    for (int k = 0; k < s; ++k)
-      for (int c = 0; c < chunks(s); ++c, ++u)
-        for (int i = 0; i < 4; ++i) {
-          const int r = 4 * c + i;
-          if (r >= s) continue;
-          out[base + (size_t)(u / 16) * 64 + 4 * (u % 16) + i] = (float)h.A[((size_t)m * P1 + m + r) * P1 + m + k];
+  for (int st = 0; 2 * st <= p; ++st)
+    for (int b = 0; b < 2; ++b) {
+      const int m = b == 0 ? st : p - st, s = zu_size(p, st, b);
+      for (int k = 0; k < s; ++k)
+        for (int r = 0; r < s; ++r) {
+          const int u = zu(p, st, k, b) + r / 4;
+          out[base + (size_t)(u / 16) * 64 + 4 * (u % 16) + r % 4] = (float)h.A[((size_t)m * P1 + m + r) * P1 + m + k];
         }
-  }
+    }
   return out;
 }
 

@@ -9,13 +9,20 @@
 // broadcast to all 16 blocks, so 16 consecutive instructions take theirs from
 // one register: the table holds, per group of 16 instructions, 64 values,
 // value 4 * (u mod 16) + i = row i of instruction u (zero past the block).
+// The instructions are numbered in the order in which the kernel issues them
+// (ju, zu below), so that one register holds the operands of all blocks in
+// flight.
 //
 // Blocks, in order:
 //   J or J^T: per degree n, per parity class cls (0: n+1 members, 1: n), the
 //             class members in standard order (the quarter turn about x
-//             keeps the classes apart);
+//             keeps the classes apart).  The turn also carries reflections in
+//             y into reflections in z, so half the entries of a class block
+//             vanish: a class of more than four members runs as two
+//             sub-blocks (j_rows below);
 //   z core:   per order m, rows d and columns n = m .. P (one table for the
-//             cosine and the sine parts, which share it).
+//             cosine and the sine parts, which share it).  Orders m and p - m
+//             run in lock-step.
 #pragma once
 
 namespace fmm {
@@ -47,10 +54,74 @@ __host__ __device__ constexpr int z_offset(int p, int m) {
   for (int a = 0; a < m; ++a) u += (p + 1 - a) * chunks(p + 1 - a);
   return u;
 }
+// Entry (r, k) of the class block (n, cls) of J or J^T is zero unless
+// r + k + n + cls is even: member r is even under y -> -y iff r is even, and
+// under z -> -z iff r + n + cls is, and the quarter turn exchanges the two.  A
+// class of more than four members is split by the parity a of its columns:
+// sub-block a takes the columns a, a + 2, ... and gives the rows first_row,
+// first_row + 2, ...; up to four members share one chunk of rows, where a
+// split saves nothing.
+__host__ __device__ constexpr bool j_split(int s) { return s > 4; }
+__host__ __device__ constexpr int j_step(int s) { return j_split(s) ? 2 : 1; }
+__host__ __device__ constexpr int j_cols(int s, int a) { return j_split(s) ? (s + 1 - a) / 2 : (a == 0 ? s : 0); }
+__host__ __device__ constexpr int j_first_row(int n, int cls, int a) {
+  return j_split(cls_size(n, cls)) ? (a + n + cls) & 1 : 0;
+}
+__host__ __device__ constexpr int j_rows(int n, int cls, int a) {
+  return j_split(cls_size(n, cls)) ? (cls_size(n, cls) + 1 - j_first_row(n, cls, a)) / 2
+                                   : j_cols(cls_size(n, cls), a);
+}
 // instructions of one J application and of the z translation (per part)
 __host__ __device__ constexpr int n_j(int p) { return j_offset(p + 1, 0); }
 __host__ __device__ constexpr int n_z(int p) { return z_offset(p, p + 1); }
 __host__ __device__ constexpr int groups(int u) { return (u + 15) / 16; }
+// The table reserves n_j instructions for a J application, one per (column,
+// output chunk) of whole class blocks; its sub-blocks need about half of them.
+//
+// Step t of a J application at order p (t = 0 .. 2 (p / 2) + 1) runs class t & 1
+// of degrees t / 2 (sub-blocks b = 0, 1 for column parity b) and p - t / 2
+// (b = 2, 3 for column parity b - 2, absent unless p - t / 2 > t / 2), column
+// by column: four or five accumulator chains in flight in most steps, which
+// covers the latency of the instruction and leaves registers for the
+// expansion.
+__host__ __device__ constexpr int ju_steps(int p) { return 2 * (p / 2 + 1); }
+__host__ __device__ constexpr int ju_degree(int p, int t, int b) {
+  return b < 2 ? t / 2 : (p - t / 2 > t / 2 ? p - t / 2 : -1);
+}
+__host__ __device__ constexpr int ju_cols(int p, int t, int b) {
+  const int d = ju_degree(p, t, b);
+  return d < 0 ? 0 : j_cols(cls_size(d, t & 1), b & 1);
+}
+__host__ __device__ constexpr int ju_rows(int p, int t, int b) {
+  return ju_cols(p, t, b) == 0 ? 0 : j_rows(ju_degree(p, t, b), t & 1, b & 1);
+}
+// number of the first instruction of column k of sub-block b in step t
+__host__ __device__ constexpr int ju(int p, int t, int k, int b) {
+  int u = 0;
+  for (int s = 0; s < t; ++s)
+    for (int c = 0; c < 4; ++c) u += ju_cols(p, s, c) * chunks(ju_rows(p, s, c));
+  for (int c = 0; c < 4; ++c) {
+    const int cols = ju_cols(p, t, c), done = c < b ? k + 1 : k;
+    u += (cols < done ? cols : done) * chunks(ju_rows(p, t, c));
+  }
+  return u;
+}
+// Step m of the z translation runs the blocks of orders m (b = 0) and p - m
+// (b = 1, absent unless p - m > m), p + 1 - order rows each, once for the
+// cosine and once for the sine parts.
+__host__ __device__ constexpr int zu_size(int p, int m, int b) {
+  return b == 0 ? p + 1 - m : (p - m > m ? m + 1 : 0);
+}
+__host__ __device__ constexpr int zu(int p, int m, int k, int b) {
+  int u = 0;
+  for (int s = 0; s < m; ++s)
+    for (int c = 0; c < 2; ++c) u += zu_size(p, s, c) * chunks(zu_size(p, s, c));
+  for (int c = 0; c < 2; ++c) {
+    const int cols = zu_size(p, m, c), done = c < b ? k + 1 : k;
+    u += (cols < done ? cols : done) * chunks(cols);
+  }
+  return u;
+}
 // floats per box of the binary32 multipoles the per-lane kernel reads: the
 // (p+1)^2 coefficients in the standard order, padded to whole 16-byte loads
 __host__ __device__ constexpr int dense_stride(int p) { return ((p + 1) * (p + 1) + 3) & ~3; }

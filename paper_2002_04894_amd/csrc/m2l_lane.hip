@@ -16,15 +16,18 @@
 // four results land in that lane's registers -- lane = pair, register = row,
 // no data moves between lanes.  The operator values of 16 instructions share
 // one register (one block's values broadcast to all blocks, lane_ops.h),
-// read from a table in LDS.  Only rows of a block are padded to a multiple
-// of 4 (1.17x the algorithmic products at p = 12, against 2.42x for 16x16
-// tiles of two degree blocks each).  The z-turns and the radius powers run on
+// read from a table in LDS.  Half the entries of a class block of J vanish (the
+// turn carries reflections in y into reflections in z), so a class runs as two
+// sub-blocks by the parity of the order: 1,460 instructions per batch at p =
+// 12, where whole blocks take 2,140.  Only rows of a block are padded to a
+// multiple of 4.  The z-turns and the radius powers run on
 // the vector units.  The 64 pair results are summed across the lanes by
 // halving exchanges (a fixed order: deterministic) and the batch sums are
 // added in binary64.  The expansions are scaled as for the binary32 tile
 // kernel: M~_n = M_n / r_s^n on the way in, so the factors (r_s/rho)^n and
 // (r_t/rho)^j / rho stay below one, and the result is unscaled by r_t^-n
 // into binary64.
+#include <tuple>
 #include <type_traits>
 
 #include "fmm_internal.h"
@@ -68,106 +71,177 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Blocks on the matrix cores.  A block of S rows computes
-// D_c += Op[4c .. 4c+3][k] x_k over its S inputs x_k = X[in(k)], then sets
-// X[in(r)] = row r; its instruction U0 + k * chunks(S) + c takes its operand
-// values from group (U0 + ...) / 16 of tab.  Up to four blocks with disjoint
-// inputs run in lock-step over k, so that their accumulator chains are
-// independent instructions in flight; S = 0 is an absent block.
-template <int S, int U0>
-struct Blk {
-  static constexpr int kS = S;
-  static constexpr int kNC = S > 0 ? lops::chunks(S) : 1;
+// Blocks on the matrix cores.  A block B of kCols inputs x_k = X[in(k)] and
+// kRows results computes D_c += Op[4c .. 4c+3][k] x_k, then sets X[out(r)] =
+// row r.  The blocks of one call run in lock-step over k, so that their
+// accumulator chains are independent instructions in flight; all inputs are
+// read before any result is stored, and a block without columns is absent.
+// The instructions are numbered in the order of issue (u(k) the first one of
+// column k), sixteen to an operand register; Ops, carried from block to block,
+// holds the current register and the next one, loaded sixteen instructions
+// ahead so that its LDS latency is covered.
+struct Ops {
+  float cur, next;
+  const float* tab;
+  int lane;
+  __device__ __forceinline__ Ops(const float* t, int l) : cur(0.f), next(t[l]), tab(t), lane(l) {}
+  // before instruction U is issued, with PREV the one issued before it (-1:
+  // none) and E the last of the sequence
+  template <int U, int PREV, int E>
+  __device__ __forceinline__ void at() {
+    constexpr int G = U / 16, GP = PREV < 0 ? -1 : PREV / 16;
+    if constexpr (G != GP) {
+      cur = G == GP + 1 ? next : tab[G * 64 + lane];
+      if constexpr (G < E / 16) next = tab[(G + 1) * 64 + lane];
+    }
+  }
+};
+
+template <class B>
+struct Acc {
+  static constexpr int kNC = B::kRows > 0 ? lops::chunks(B::kRows) : 1;
   f4 D[kNC];
-  float av = 0.f;
-  __device__ __forceinline__ Blk() {
+  __device__ __forceinline__ Acc() {
     static_for<0, kNC>([&](auto c) __attribute__((always_inline)) { D[c] = f4{0.f, 0.f, 0.f, 0.f}; });
   }
-  template <int K, class In>
-  __device__ __forceinline__ void step(const float* X, const float* tab, int lane, In in) {
-    if constexpr (K < S) {
-      const float xk = X[in(std::integral_constant<int, K>{})];
+  template <int K>
+  __device__ __forceinline__ void step(const float* X, Ops& ops) {
+    if constexpr (K < B::kCols) {
+      const float xk = X[B::in(K)];
       static_for<0, kNC>([&](auto c) __attribute__((always_inline)) {
-        constexpr int u = U0 + K * kNC + decltype(c)::value;
-        if constexpr (u % 16 == 0 || (K == 0 && decltype(c)::value == 0)) av = tab[(u / 16) * 64 + lane];
-        D[c] = mfma_bc<u % 16>(av, xk, D[c]);
+        constexpr int u = B::u(K) + decltype(c)::value;
+        ops.template at<u, decltype(c)::value == 0 ? B::prev(K) : u - 1, B::kLast>();
+        D[c] = mfma_bc<u % 16>(ops.cur, xk, D[c]);
       });
     }
   }
-  template <class In>
-  __device__ __forceinline__ void store(float* X, In in) {
-    static_for<0, S>([&](auto r) __attribute__((always_inline)) {
-      X[in(r)] = D[decltype(r)::value / 4][decltype(r)::value % 4];
-    });
+  __device__ __forceinline__ void store(float* X) {
+    if constexpr (B::kCols > 0)
+      static_for<0, B::kRows>([&](auto r) __attribute__((always_inline)) {
+        X[B::out(decltype(r)::value)] = D[decltype(r)::value / 4][decltype(r)::value % 4];
+      });
   }
 };
 
-template <int S0, int U0, int S1, int U1, int S2, int U2, int S3, int U3, class I0, class I1, class I2, class I3>
-__device__ __forceinline__ void blocks_mf(float* X, const float* t0, const float* t1, const float* t2,
-                                          const float* t3, int lane, I0 in0, I1 in1, I2 in2, I3 in3) {
-  constexpr int SM01 = S0 > S1 ? S0 : S1, SM23 = S2 > S3 ? S2 : S3;
-  constexpr int SM = SM01 > SM23 ? SM01 : SM23;
-  Blk<S0, U0> b0;
-  Blk<S1, U1> b1;
-  Blk<S2, U2> b2;
-  Blk<S3, U3> b3;
-  static_for<0, SM>([&](auto k) __attribute__((always_inline)) {
-    constexpr int K = decltype(k)::value;
-    b0.template step<K>(X, t0, lane, in0);
-    b1.template step<K>(X, t1, lane, in1);
-    b2.template step<K>(X, t2, lane, in2);
-    b3.template step<K>(X, t3, lane, in3);
-  });
-  b0.store(X, in0);
-  b1.store(X, in1);
-  b2.store(X, in2);
-  b3.store(X, in3);
+__host__ __device__ constexpr int max_of(int a) { return a; }
+template <class... T>
+__host__ __device__ constexpr int max_of(int a, int b, T... r) {
+  return max_of(a > b ? a : b, r...);
 }
 
-// the class members of degree N (standard indices), and the order-M part T
-template <int N, int CLS>
-struct JIn {
-  template <class R>
-  __device__ constexpr int operator()(R) const { return N * N + lops::cls_member(N, CLS, R::value); }
+template <class... B>
+__device__ __forceinline__ void blocks_mf(float* X, Ops& ops) {
+  std::tuple<Acc<B>...> acc;
+  std::apply(
+      [&](auto&... b) __attribute__((always_inline)) {
+        static_for<0, max_of(B::kCols...)>([&](auto k) __attribute__((always_inline)) {
+          (b.template step<decltype(k)::value>(X, ops), ...);
+        });
+        (b.store(X), ...);
+      },
+      acc);
+}
+
+// sub-block B of step S of a J application at order P (lane_ops.h)
+template <int P, int S, int B>
+struct JSub {
+  static constexpr int kD = lops::ju_degree(P, S, B);
+  static constexpr int kCls = S & 1, kA = B & 1;
+  static constexpr int kCols = lops::ju_cols(P, S, B), kRows = lops::ju_rows(P, S, B);
+  static constexpr int kLast = lops::ju(P, lops::ju_steps(P), 0, 0) - 1;
+  __host__ __device__ static constexpr int u(int k) { return lops::ju(P, S, k, B); }
+  __host__ __device__ static constexpr int prev(int k) { return u(k) - 1; }
+  __host__ __device__ static constexpr int in(int k) {
+    return kD * kD + lops::cls_member(kD, kCls, kA + lops::j_step(lops::cls_size(kD, kCls)) * k);
+  }
+  __host__ __device__ static constexpr int out(int r) {
+    return kD * kD + lops::cls_member(kD, kCls, lops::j_first_row(kD, kCls, kA) +
+                                                    lops::j_step(lops::cls_size(kD, kCls)) * r);
+  }
 };
-template <int M, int T>
-struct ZIn {
-  template <class R>
-  __device__ constexpr int operator()(R) const { return cidx(M + R::value, M, T); }
+// part T (cosine or sine) of block B of step M of the z translation
+template <int P, int M, int B, int T>
+struct ZBlk {
+  static constexpr int kM = B == 0 ? M : P - M;
+  static constexpr int kCols = kM >= T ? lops::zu_size(P, M, B) : 0;
+  static constexpr int kRows = kCols;
+  static constexpr int kLast = lops::zu(P, P / 2 + 1, 0, 0) - 1;
+  __host__ __device__ static constexpr int u(int k) { return lops::zu(P, M, k, B); }
+  // the instruction issued before column k: the sine parts skip the block of
+  // order 0, beside which the one instruction of order P runs
+  __host__ __device__ static constexpr int prev(int k) {
+    if (T == 1 && M == 0) return -1;
+    if (T == 1 && M == 1 && B == 0 && k == 0) return lops::zu(P, 0, 0, 1);
+    return u(k) - 1;
+  }
+  __host__ __device__ static constexpr int in(int k) { return cidx(kM + k, kM, T); }
+  __host__ __device__ static constexpr int out(int r) { return cidx(kM + r, kM, T); }
 };
 
-// X <- J X or J^T X on the matrix cores: per degree and parity class, the
-// class block times the lane's class members (lane_ops.h), degree n beside
-// degree P - n; tab: the operator's groups in LDS
+// X <- J X or J^T X on the matrix cores: per degree and parity class the two
+// sub-blocks that hold the class block's nonzero entries times the lane's
+// class members (lane_ops.h), degree n beside degree P - n, one class at a
+// time.  The sub-blocks take 258 instructions per
+// application at order 12, the whole class blocks 428 (half of their products
+// with zeros).
 template <int P>
-__device__ __forceinline__ void japply_mf(float* X, const float* tab, int lane) {
-  static_for<0, P / 2 + 1>([&](auto nI) __attribute__((always_inline)) {
-    constexpr int n = decltype(nI)::value, n2 = P - n;
-    constexpr bool two = n2 > n;
-    constexpr int s2 = two ? lops::cls_size(n2, 0) : 0, s3 = two ? lops::cls_size(n2, 1) : 0;
-    blocks_mf<lops::cls_size(n, 0), lops::j_offset(n, 0), lops::cls_size(n, 1), lops::j_offset(n, 1), s2,
-              lops::j_offset(n2, 0), s3, lops::j_offset(n2, 1)>(X, tab, tab, tab, tab, lane, JIn<n, 0>{},
-                                                                  JIn<n, 1>{}, JIn<n2, 0>{}, JIn<n2, 1>{});
+__device__ __forceinline__ void japply_mf(float* X, Ops ops) {
+  static_for<0, lops::ju_steps(P)>([&](auto sI) __attribute__((always_inline)) {
+    constexpr int st = decltype(sI)::value;
+    blocks_mf<JSub<P, st, 0>, JSub<P, st, 1>, JSub<P, st, 2>, JSub<P, st, 3>>(X, ops);
     // a few blocks at a time: bounded registers
     __builtin_amdgcn_sched_barrier(0);
   });
 }
 
-// X <- Rz(sign * g) X, with (c1, s1) = (cos g, sin g); the multiples by the
-// angle-addition recurrence in binary64
-// FRESH: the recurrence is not shared with the other turn by the same angle
-// (shared, its 2P binary64 values stay live through the whole translation;
-// where registers are short that costs more than running it again)
-template <int P, bool FRESH>
-__device__ __forceinline__ void rotz(float* X, double c1, double s1, double sign) {
-  if constexpr (FRESH) asm volatile("" : "+v"(c1), "+v"(s1));
-  double c = 1.0, s = 0.0;
+// (cos m g, sin m g), m = 1 .. P, of one lane's turn angle, from (c1, s1) =
+// (cos g, sin g) by f_{m+1} = 2 cos g f_m - f_{m-1} in binary64, rounded to
+// binary32 and kept in LDS for the turn back by the same angle: two orders to
+// a 16-byte word, the words of a wave's lanes side by side.  (Held in
+// registers they would spill; worked out again they are a tenth of the
+// kernel's vector instructions.)
+template <int P>
+struct Turn {
+  static constexpr int kWords = (P + 1) / 2;
+  float c[P + 2], s[P + 2];
+  __device__ __forceinline__ void make(double c1, double s1) {
+    const double t = 2.0 * c1;
+    double cp = 1.0, sp = 0.0, cc = c1, ss = s1;
+#pragma unroll
+    for (int m = 1; m <= P; ++m) {
+      c[m] = (float)cc;
+      s[m] = (float)ss;
+      const double cn = t * cc - cp, sn = t * ss - sp;
+      cp = cc;
+      sp = ss;
+      cc = cn;
+      ss = sn;
+    }
+    c[P + 1] = s[P + 1] = 0.f;
+  }
+  __device__ __forceinline__ void put(float4* w) const {
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) w[64 * i] = make_float4(c[2 * i + 1], s[2 * i + 1], c[2 * i + 2], s[2 * i + 2]);
+  }
+  __device__ __forceinline__ void get(const float4* w) {
+    asm volatile("" ::: "memory");  // read from LDS, not from registers kept since put()
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+      const float4 v = w[64 * i];
+      c[2 * i + 1] = v.x;
+      s[2 * i + 1] = v.y;
+      c[2 * i + 2] = v.z;
+      s[2 * i + 2] = v.w;
+    }
+  }
+};
+
+// X <- Rz(SIGN * g) X
+template <int P, int SIGN>
+__device__ __forceinline__ void rotz(float* X, const Turn<P>& g) {
 #pragma unroll
   for (int m = 1; m <= P; ++m) {
-    const double nc = c * c1 - s * s1, ns = s * c1 + c * s1;
-    c = nc;
-    s = ns;
-    const float cm = (float)c, sm = (float)(sign * s);
+    const float cm = g.c[m], sm = SIGN < 0 ? -g.s[m] : g.s[m];
 #pragma unroll
     for (int n = m; n <= P; ++n) {
       const float a = X[cidx(n, m, 0)], b = X[cidx(n, m, 1)];
@@ -175,6 +249,20 @@ __device__ __forceinline__ void rotz(float* X, double c1, double s1, double sign
       X[cidx(n, m, 1)] = sm * a + cm * b;
     }
   }
+}
+// the turn by -g, whose cosines and sines go to w, and the turn back
+template <int P>
+__device__ __forceinline__ void turn_in(float* X, double c1, double s1, float4* w) {
+  Turn<P> g;
+  g.make(c1, s1);
+  g.put(w);
+  rotz<P, -1>(X, g);
+}
+template <int P>
+__device__ __forceinline__ void turn_back(float* X, const float4* w) {
+  Turn<P> g;
+  g.get(w);
+  rotz<P, 1>(X, g);
 }
 
 // the z-axis translation with the core products on the matrix cores: per
@@ -192,16 +280,15 @@ __device__ __forceinline__ void ztrans_mf(float* X, const float* tab, int lane, 
       w *= in_base;
     }
   }
-  // order m beside order P - m, cosine and sine parts each
-  static_for<0, P / 2 + 1>([&](auto mI) __attribute__((always_inline)) {
-    constexpr int m = decltype(mI)::value, m2 = P - m;
-    constexpr bool two = m2 > m;
-    constexpr int s1 = m > 0 ? P + 1 - m : 0, s2 = two ? P + 1 - m2 : 0;
-    constexpr int s3 = (two && m2 > 0) ? P + 1 - m2 : 0;
-    blocks_mf<P + 1 - m, lops::z_offset(P, m), s1, lops::z_offset(P, m), s2, lops::z_offset(P, m2), s3,
-              lops::z_offset(P, m2)>(
-        X, tab, tab, tab, tab, lane, ZIn<m, 0>{}, ZIn<m, 1>{}, ZIn<m2, 0>{}, ZIn<m2, 1>{});
-    __builtin_amdgcn_sched_barrier(0);
+  // order m beside order P - m, the cosine parts, then the sine parts
+  static_for<0, 2>([&](auto tI) __attribute__((always_inline)) {
+    constexpr int T = decltype(tI)::value;
+    Ops ops(tab, lane);
+    static_for<0, P / 2 + 1>([&](auto mI) __attribute__((always_inline)) {
+      constexpr int m = decltype(mI)::value;
+      blocks_mf<ZBlk<P, m, 0, T>, ZBlk<P, m, 1, T>>(X, ops);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   });
   float w = out_mult;
 #pragma unroll
@@ -248,21 +335,32 @@ __device__ __forceinline__ void halve(const float* src, float* dst, int lane) {
   }
 }
 
+// 1/sqrt(x), 0 for x = 0: the hardware estimate and two Newton steps
+__device__ __forceinline__ double lane_rsqrt(double x) {
+  double y = x > 0.0 ? __builtin_amdgcn_rsq(x) : 0.0;
+  const double h = 0.5 * x;
+  y = y * (1.5 - h * y * y);
+  return y * (1.5 - h * y * y);
+}
+
 __device__ __forceinline__ int level_of3(const LevelView& lv, int64_t gid) {
   int l = 0;
   while (l < lv.L && gid >= lv.gofs[l + 1]) ++l;
   return l;
 }
 
-// Waves per SIMD: 2 up to order 12 (256 registers; at orders 11 and 12 a
-// few values spill, which costs less than halving the waves), 1 above.
-// kFresh (the z-turns recompute their recurrence) from order 11: measured on
-// 2^24 Plummer points, sharing it is 2 % faster at order 10 and 2 % and 22 %
-// slower at 11 and 12.
+// Waves per SIMD, as the registers allow (118 at order 6, 163 at 8, 249 at 11;
+// at order 12 32 values spill, which costs less than halving the waves; at 13
+// 172 would spill: 75.2 ms against 47.9 with one wave on the cloud below).
+// What bounds the kernel: instruction issue, matrix and vector instructions
+// never running together.  Measured on 2^22 Plummer points (5 levels, theta
+// 0.6, 194 million pairs), M2L in ms: order 4 4.0, 6 7.5, 8 11.4, 10 18.0, 11
+// 22.0, 12 28.9 (98 TFLOP/s by the dense count of 14,638 flops a
+// pair), 13 47.9, 14 54.6; with whole class blocks for J and the turns' angles
+// worked out twice 4.6, 8.7, 14.7, 23.5, 29.2, 37.8, 58.2 and 69.3.
 template <int P>
 struct LaneCfg {
-  static constexpr int kWaves = P <= 12 ? 2 : 1;
-  static constexpr bool kFresh = kWaves == 2 && P >= 11;
+  static constexpr int kWaves = P <= 6 ? 4 : P <= 8 ? 3 : P <= 12 ? 2 : 1;
 };
 
 // Persistent waves: each takes the next target of the longest-first order.
@@ -274,12 +372,17 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
   constexpr int S = tl::stride(P);
   constexpr int SD = lops::dense_stride(P);
   constexpr int NF = lvl(NT, 6);  // values a lane holds after the exchanges
-  constexpr bool FR = LaneCfg<P>::kFresh;
   constexpr int GJ = 64 * lops::groups(lops::n_j(P));  // table: J, J^T, z core
   __shared__ float tabs[lops::table_floats(P)];
+  // the turn angles' cosines and sines: two angles per lane (12 KB per wave at
+  // order 12; with the tables 66 KB per block, two blocks per CU)
+  constexpr int TW = 64 * Turn<P>::kWords;
+  __shared__ float4 turns[P > 0 ? 4 * 2 * TW : 1];
   for (int i = threadIdx.x; i < lops::table_floats(P); i += blockDim.x) tabs[i] = ltab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63;
+  float4* wb = turns + (threadIdx.x >> 6) * 2 * TW + (P > 0 ? lane : 0);  // beta, then alpha
+  float4* wa = wb + TW;
   for (;;) {
     int kq = 0;
     if (lane == 0) kq = atomicAdd(queue, 1);
@@ -298,17 +401,19 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
 #pragma unroll
     for (int i = 0; i < NF; ++i) acc[i] = 0.0;
 
+    // the next batch's source indexes are loaded while this batch runs
+    int32_t jn = e0 < e1 ? widx[e0 + lane < e1 ? e0 + lane : e0] : 0;
     for (int64_t eb = e0; eb < e1; eb += 64) {
       const int64_t e = eb + lane;
       const bool valid = e < e1;
-      const int64_t j = widx[valid ? e : e0];
+      const int64_t j = jn;
+      jn = widx[e + 64 < e1 ? e + 64 : e0];
       const double dx = geo[j * 10 + 6] - cix, dy = geo[j * 10 + 7] - ciy, dz = geo[j * 10 + 8] - ciz;
       const double rs = geo[j * 10 + 9] > 0.0 ? geo[j * 10 + 9] : 1.0;
       const double rxy2 = dx * dx + dy * dy;
-      const double rho = sqrt(rxy2 + dz * dz), rxy = sqrt(rxy2);
-      const double irho = 1.0 / rho;
-      const double ca = dz * irho, sa = rxy * irho;
-      const double cb = rxy > 0.0 ? dx / rxy : 1.0, sb = rxy > 0.0 ? dy / rxy : 0.0;
+      const double irho = lane_rsqrt(rxy2 + dz * dz), irxy = lane_rsqrt(rxy2);
+      const double ca = dz * irho, sa = rxy2 * irxy * irho;
+      const double cb = rxy2 > 0.0 ? dx * irxy : 1.0, sb = dy * irxy;
       // a lane past the end of the list translates the first source with zero factors
       const float in_base = valid ? (float)(rs * irho) : 0.f;
       const float out_base = valid ? (float)(rt * irho) : 0.f;
@@ -330,15 +435,21 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
 #define FMM_STEP(x)                      \
   x;                                     \
   __builtin_amdgcn_sched_barrier(0)
-      FMM_STEP((rotz<P, FR>(X, cb, sb, -1.0)));
-      FMM_STEP(japply_mf<P>(X, tabs + GJ, lane));
-      FMM_STEP((rotz<P, FR>(X, ca, sa, -1.0)));
-      FMM_STEP(japply_mf<P>(X, tabs, lane));
+      // the first operands of a quarter turn are loaded before the z-turn
+      // ahead of it
+      const float *tJ = tabs, *tJT = tabs + GJ;
+      FMM_STEP(Ops o1(tJT, lane));
+      FMM_STEP(turn_in<P>(X, cb, sb, wb));
+      FMM_STEP(japply_mf<P>(X, o1));
+      FMM_STEP(Ops o2(tJ, lane));
+      FMM_STEP(turn_in<P>(X, ca, sa, wa));
+      FMM_STEP(japply_mf<P>(X, o2));
       FMM_STEP(ztrans_mf<P>(X, tabs + 2 * GJ, lane, in_base, out_base, out_mult));
-      FMM_STEP(japply_mf<P>(X, tabs + GJ, lane));
-      FMM_STEP((rotz<P, FR>(X, ca, sa, 1.0)));
-      FMM_STEP(japply_mf<P>(X, tabs, lane));
-      FMM_STEP((rotz<P, FR>(X, cb, sb, 1.0)));
+      FMM_STEP(japply_mf<P>(X, Ops(tJT, lane)));
+      FMM_STEP(Ops o4(tJ, lane));
+      FMM_STEP(turn_back<P>(X, wa));
+      FMM_STEP(japply_mf<P>(X, o4));
+      FMM_STEP(turn_back<P>(X, wb));
 #undef FMM_STEP
 
       // sum over the 64 lanes: six halving exchanges; at the exchange with
