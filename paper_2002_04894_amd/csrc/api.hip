@@ -229,6 +229,8 @@ void* dalloc(size_t bytes, hipStream_t s) {
     const size_t off = (g_arena->used + 255) & ~(size_t)255;
     if (off > g_arena->size || bytes > g_arena->size - off)
       fail(FMM_EINVAL, "evaluation scratch exceeds the fixed buffer of " + std::to_string(g_arena->size) + " bytes");
+    if (g_arena->n >= Arena::kSlices) fail(FMM_EINVAL, "evaluation scratch has too many parts");
+    g_arena->ofs[g_arena->n++] = off;
     g_arena->used = off + bytes;
     return g_arena->base + off;
   }
@@ -247,7 +249,12 @@ void* dalloc(size_t bytes, hipStream_t s) {
 }
 
 void dfree(void* p, hipStream_t s) {
-  if (!p || g_arena) return;
+  if (!p) return;
+  if (g_arena) {
+    if (g_arena->n > 0 && g_arena->base + g_arena->ofs[g_arena->n - 1] == (char*)p)
+      g_arena->used = g_arena->ofs[--g_arena->n];
+    return;
+  }
   const Allocator a = g_ledger ? g_ledger->a : Allocator{};
   if (g_ledger) {
     auto& v = g_ledger->live;

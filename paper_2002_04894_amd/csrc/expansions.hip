@@ -333,26 +333,27 @@ std::vector<float> lane_tables(const HostTables& h, int p) {
 enum QuadKind { kQuadM2L = 0, kQuadM2M = 1, kQuadL2L = 2 };
 std::vector<double> quad_tables(const HostTables& h, int p, int kind) {
   using namespace lops;
-  std::vector<double> out((size_t)qtable_doubles(p), 0.0);
-  const int ntab = qtable_has_jt(p) ? 2 : 1;
+  std::vector<double> out((size_t)qp_doubles(p), 0.0);
+  const int ntab = qp_has_jt(p) ? 2 : 1;
   for (int trans = 0; trans < ntab; ++trans) {
-    double* T = out.data() + (size_t)trans * 16 * qj_count(p);
+    double* T = out.data() + (size_t)trans * 16 * qp_count(p);
     for (int d = 0; d <= p; ++d) {
       const int sd = 2 * d + 1, nr = qreg(d);
       for (int x = 0; x < 2; ++x)
         for (int g = 0; g < nr; ++g)
           for (int c = 0; c < nr; ++c) {
-            const int u = qj_offset(d, x) + g * nr + c;
+            if (!qpart(d, x, g, c)) continue;
+            const int u = qp_offset(d, x) + qpart_rank(d, x, g, c);
             for (int k = 0; k < 4; ++k)
               for (int i = 0; i < 4; ++i) {
-                const int a = qmember(d, x, 4 * c + i), b = qmember(d, x, 4 * g + k);
-                if (a < 0 || b < 0) continue;
+                const int r = qorder(d, c, i), m = qorder(d, g, k), a = qmember(d, x, r), b = qmember(d, x, m);
+                if (a < 0 || b < 0 || ((r + m + d + x) & 1)) continue;
                 T[16 * u + 4 * k + i] = trans ? h.J[h.joff[d] + b * sd + a] : h.J[h.joff[d] + a * sd + b];
               }
           }
     }
   }
-  double* Z = out.data() + (size_t)ntab * 16 * qj_count(p);
+  double* Z = out.data() + (size_t)ntab * 16 * qp_count(p);
   const size_t P1 = (size_t)p + 1;
   for (int m = 0; m <= p; ++m)
     for (int d = m; d <= p; ++d)
@@ -423,7 +424,6 @@ const Tables& tables_for(int p, hipStream_t s) {
     t.quad_l2l = upload(quad_tables(h, p, kQuadL2L), s);
   }
   if (h.tiled) {
-    t.mtab = upload(h.mtab, s);
     t.mtab32 = upload(h.mtab32, s);
     t.sdeg = upload(h.sdeg, s);
     t.lane = upload(lane_tables(h, p), s);
@@ -868,18 +868,15 @@ void launch_m2m(const Tree& t, int l, const Tables& tb, double* Mx, hipStream_t 
   k_m2m<<<(unsigned)t.lev[l - 1].nbox, 64, lds, s>>>(t.view(), l, make_xt(tb), Mx);
   HIPCHECK(hipGetLastError());
 }
-bool launch_m2l_mfma(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s);
 bool launch_m2l_mfma_mixed(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s);
 bool launch_m2l_quad64(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s);
 
 // M2L on the matrix cores: binary32 on scaled expansions for orders up to 15
 // unless binary64 is asked for (one pair per lane up to 14, 16-pair tiles at
-// 15), else binary64 (four lanes per pair at orders up to 13 and 16..20,
-// 16-pair tiles at 14 and 15)
+// 15), else binary64 (four lanes per pair)
 void launch_m2l(const Tree& t, const Tables& tb, const double* Mx, double* Lx, int prec, hipStream_t s) {
   if (prec != FMM_PREC_F64 && launch_m2l_mfma_mixed(t, tb, Mx, Lx, s)) return;
   if (launch_m2l_quad64(t, tb, Mx, Lx, s)) return;
-  if (launch_m2l_mfma(t, tb, Mx, Lx, s)) return;
   fail(FMM_EUNSUPPORTED, "no M2L kernel for order " + std::to_string(tb.p));
 }
 void launch_l2l(const Tree& t, int l, const Tables& tb, double* Lx, hipStream_t s) {

@@ -46,12 +46,15 @@ void dfree(void* p, hipStream_t s);
 
 // Evaluation scratch carved from one fixed device buffer (the entry point
 // that allocates nothing): while an arena is set on this thread, dalloc hands
-// out 256-byte aligned slices of it (FMM_EINVAL when it runs out) and dfree
-// does nothing.
+// out 256-byte aligned slices of it (FMM_EINVAL when it runs out), and dfree
+// takes back the last slice handed out (others stay until the call ends).
 struct Arena {
+  static constexpr int kSlices = 32;
   char* base = nullptr;
   size_t size = 0;
   size_t used = 0;
+  int n = 0;              // slices handed out and not taken back
+  size_t ofs[kSlices];    // where each of them starts
 };
 void set_arena(Arena* a);  // nullptr: back to the allocator
 
@@ -146,11 +149,10 @@ struct Tables {
   int stride = 0;
   int* pos = nullptr;
   int* ipos = nullptr;
-  // MFMA translation tables (p <= 15), as operand fragments [step][lane]:
-  // the y-quarter-turn tile matrices [ntiles * 4][64], then the z-translation
-  // matrices per order [sum_m hsteps][64]
-  double* mtab = nullptr;
-  float* mtab32 = nullptr;  // the same in binary32, rows ordered for the binary32 MFMA
+  // 16x16 tile tables (p <= 15), as operand fragments [step][lane] of the
+  // binary32 MFMA: the y-quarter-turn tile matrices [ntiles * 4][64], then the
+  // z-translation matrices per order [sum_m hsteps][64]
+  float* mtab32 = nullptr;
   int8_t* sdeg = nullptr;  // degree of each storage position, -1 for a zero slot
   // J, J^T and the z-translation core as operands of the per-lane M2L
   // kernel's 4x4x1 matrix instructions (lane_ops.h), binary32

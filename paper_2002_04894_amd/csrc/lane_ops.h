@@ -134,13 +134,18 @@ __host__ __device__ constexpr int table_floats(int p) { return 64 * (2 * groups(
 // degree d the coefficients form two blocks indexed by the order m = 0..d:
 // block 0 holds c_m for even m and s_m for odd m, block 1 the others (its
 // member 0, s_0, is a zero slot) -- the two classes that the quarter turn
-// about x keeps apart, ordered by m.  Member m of a block sits in phase
-// m mod 4, register m / 4 of the block, so that the cosine and sine parts of
-// (d, m) share a lane and register index, and all degrees of order m share a
-// lane.  A block product takes ceil((d+1)/4)^2 instructions, one per (k-step
-// g, output chunk c): D_c += Op[4c .. 4c+3][4g .. 4g+3] X_g; the operand of
-// instruction u is 16 values, row i and column k of its 4x4 part at 16 u +
-// 4 k + i (the lane layout of the instruction: lane 16 k + 4 b + i holds
+// about x keeps apart, ordered by m.  Entry (m', m) of a block is zero unless
+// m' + m + d + x is even (the reflections in y and z, as above), so the
+// members are dealt to the registers by parity (qorder): of each eight orders
+// the even ones fill one register and the odd ones the next, or, where at most
+// four of the eight exist, all share one.  A part (output register c, input
+// register g) whose entries all vanish is left out.  The cosine and sine parts
+// of (d, m) share a lane and register index.  An exchange of the two halves of
+// the wave between an even and an odd register sorts them by order again: the
+// lower four orders of the eight in the first, as in a shared register, the
+// upper four in the second, so that all degrees of an order share a lane.  The
+// operand of instruction u is 16 values, row i and column k of its 4x4 part at
+// 16 u + 4 k + i (the lane layout of the instruction: lane 16 k + 4 b + i holds
 // A[i][k] of block b, for every b).
 __host__ __device__ constexpr int qreg(int d) { return d / 4 + 1; }
 // first register of block (d, x)
@@ -156,7 +161,32 @@ __host__ __device__ constexpr int qmember(int d, int x, int m) {
   if ((m & 1) == x) return m == 0 ? 0 : 2 * m - 1;  // c_m
   return m == 0 ? -1 : 2 * m;                       // s_m
 }
-// first instruction of block (d, x) in one J application
+// order of the member in phase k of register g of a block of degree d (none
+// if above d), and the position of order e = 0..3 of a shared register
+__host__ __device__ constexpr int qshared(int k) { return 2 * (k & 1) + (k >> 1); }
+__host__ __device__ constexpr bool qpaired(int d, int g) { return d + 1 - 8 * (g / 2) > 4; }
+__host__ __device__ constexpr int qorder(int d, int g, int k) {
+  return 8 * (g / 2) + (qpaired(d, g) ? 2 * k + (g & 1) : qshared(k));
+}
+// whether part (input register g, output register c) of block (d, x) holds
+// nonzero entries, and its rank among those that do
+__host__ __device__ constexpr bool qpart(int d, int x, int g, int c) {
+  for (int k = 0; k < 4; ++k)
+    for (int i = 0; i < 4; ++i) {
+      const int m = qorder(d, g, k), r = qorder(d, c, i);
+      if (m >= x && r >= x && m <= d && r <= d && ((m + r + d + x) & 1) == 0) return true;
+    }
+  return false;
+}
+__host__ __device__ constexpr int qpart_rank(int d, int x, int g, int c) {
+  int n = 0;
+  for (int a = 0; a < g; ++a)
+    for (int b = 0; b < qreg(d); ++b) n += qpart(d, x, a, b) ? 1 : 0;
+  for (int b = 0; b < c; ++b) n += qpart(d, x, g, b) ? 1 : 0;
+  return n;
+}
+// first instruction of block (d, x) in one J application, were all parts of
+// whole blocks kept
 __host__ __device__ constexpr int qj_offset(int d, int x) {
   int u = 0;
   for (int a = 0; a < d; ++a) u += 2 * qreg(a) * qreg(a);
@@ -175,6 +205,32 @@ __host__ __device__ constexpr bool qtable_has_jt(int p) {
 // the z-translation core
 __host__ __device__ constexpr int qtable_doubles(int p) {
   return (qtable_has_jt(p) ? 2 : 1) * 16 * qj_count(p) + qcore_doubles(p);
+}
+
+// The parts that are kept: first instruction of block (d, x), their number
+__host__ __device__ constexpr int qp_offset(int d, int x) {
+  int u = 0;
+  for (int a = 0; a <= d; ++a)
+    for (int b = 0; b < (a < d ? 2 : x); ++b) u += qpart_rank(a, b, qreg(a), 0);
+  return u;
+}
+__host__ __device__ constexpr int qp_count(int p) { return qp_offset(p + 1, 0); }
+// Threads of a block (one block per CU): two waves per SIMD up to order 15,
+// where the registers allow it, one above.
+__host__ __device__ constexpr int qthreads(int p) { return p <= 15 ? 512 : 256; }
+// values a lane holds of the sum over a batch's 16 pairs
+__host__ __device__ constexpr int qsums(int p) { return (nq(p) + 15) / 16; }
+// bytes of LDS beside the tables: six values and the sums parked by each
+// lane, a word for each (register, phase)
+__host__ __device__ constexpr int qpark_bytes(int p) { return (6 + qsums(p)) * qthreads(p) * 8 + nq(p) * 16; }
+// the tables: J (16 values per instruction), J^T in the same form where it
+// fits beside the rest (orders up to 18; above, J^T is read from J
+// transposed), the z-translation core
+__host__ __device__ constexpr bool qp_has_jt(int p) {
+  return (2 * 16 * qp_count(p) + qcore_doubles(p)) * 8 + qpark_bytes(p) <= 160 * 1024;
+}
+__host__ __device__ constexpr int qp_doubles(int p) {
+  return (qp_has_jt(p) ? 2 : 1) * 16 * qp_count(p) + qcore_doubles(p);
 }
 
 }  // namespace lops

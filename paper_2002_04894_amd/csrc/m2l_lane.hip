@@ -32,6 +32,7 @@
 
 #include "fmm_internal.h"
 #include "lane_ops.h"
+#include "m2l_queue.h"
 #include "tile_layout.h"
 
 namespace fmm {
@@ -268,10 +269,10 @@ __device__ __forceinline__ void turn_back(float* X, const float4* w) {
 // the z-axis translation with the core products on the matrix cores: per
 // order m the block A[m][d][n] (d, n = m .. P) times the lane's cosine and
 // sine parts of order m (one operand table for both)
-template <int P>
-__device__ __forceinline__ void ztrans_mf(float* X, const float* tab, int lane, float in_base, float out_base,
-                                          float out_mult) {
+template <int P, class F>
+__device__ __forceinline__ void ztrans_mf(float* X, const float* tab, int lane, const F& fac) {
   {
+    const float in_base = fac.get(0);
     float w = in_base;
 #pragma unroll
     for (int n = 1; n <= P; ++n) {
@@ -290,7 +291,8 @@ __device__ __forceinline__ void ztrans_mf(float* X, const float* tab, int lane, 
       __builtin_amdgcn_sched_barrier(0);
     });
   });
-  float w = out_mult;
+  const float out_base = fac.get(1);
+  float w = fac.get(2);
 #pragma unroll
   for (int d = 0; d <= P; ++d) {
 #pragma unroll
@@ -335,39 +337,35 @@ __device__ __forceinline__ void halve(const float* src, float* dst, int lane) {
   }
 }
 
-// 1/sqrt(x), 0 for x = 0: the hardware estimate and two Newton steps
-__device__ __forceinline__ double lane_rsqrt(double x) {
-  double y = x > 0.0 ? __builtin_amdgcn_rsq(x) : 0.0;
-  const double h = 0.5 * x;
-  y = y * (1.5 - h * y * y);
-  return y * (1.5 - h * y * y);
-}
-
 __device__ __forceinline__ int level_of3(const LevelView& lv, int64_t gid) {
   int l = 0;
   while (l < lv.L && gid >= lv.gofs[l + 1]) ++l;
   return l;
 }
 
-// Waves per SIMD, as the registers allow (118 at order 6, 163 at 8, 249 at 11;
-// at order 12 32 values spill, which costs less than halving the waves; at 13
-// 172 would spill: 75.2 ms against 47.9 with one wave on the cloud below).
+// Waves per SIMD, as the registers allow (two at 12 with a few values parked
+// in LDS; at 13 172 would spill: 75.2 ms against 47.9 with one wave on the
+// cloud below).
 // What bounds the kernel: instruction issue, matrix and vector instructions
 // never running together.  Measured on 2^22 Plummer points (5 levels, theta
-// 0.6, 194 million pairs), M2L in ms: order 4 4.0, 6 7.5, 8 11.4, 10 18.0, 11
-// 22.0, 12 28.9 (98 TFLOP/s by the dense count of 14,638 flops a
-// pair), 13 47.9, 14 54.6; with whole class blocks for J and the turns' angles
+// 0.6, 194 million pairs), M2L in ms: order 4 4.2, 6 7.5, 8 11.7, 10 18.1, 11
+// 22.0, 12 27.5 (103 TFLOP/s by the dense count of 14,638 flops a
+// pair), 13 46.2, 14 54.6; with whole class blocks for J and the turns' angles
 // worked out twice 4.6, 8.7, 14.7, 23.5, 29.2, 37.8, 58.2 and 69.3.
 template <int P>
 struct LaneCfg {
   static constexpr int kWaves = P <= 6 ? 4 : P <= 8 ? 3 : P <= 12 ? 2 : 1;
+  // at order 12 15 values would spill without (28.4 ms instead of 27.5 on the
+  // cloud above); elsewhere the LDS traffic only costs (1 to 5 %)
+  static constexpr bool kPark = P == 12;
 };
 
-// Persistent waves: each takes the next target of the longest-first order.
+// Persistent waves: each takes the next target of its XCD's part of the order.
 template <int P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LaneCfg<P>::kWaves, LaneCfg<P>::kWaves))) void
 k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__ pos, const float* __restrict__ Mf,
-           double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order, int* __restrict__ queue) {
+           double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order, int* __restrict__ queue,
+           int run) {
   constexpr int NT = (P + 1) * (P + 1);
   constexpr int S = tl::stride(P);
   constexpr int SD = lops::dense_stride(P);
@@ -378,46 +376,55 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
   // order 12; with the tables 66 KB per block, two blocks per CU)
   constexpr int TW = 64 * Turn<P>::kWords;
   __shared__ float4 turns[P > 0 ? 4 * 2 * TW : 1];
+  // values that a lane parks while the translation runs, where they would
+  // spill: the sums over the batches and the polar angle; the distance factors
+  constexpr bool PK = LaneCfg<P>::kPark;
+  __shared__ double parkd[PK ? (NF + 2) * 256 : 1];
+  __shared__ float parkf[PK ? 3 * 256 : 1];
   for (int i = threadIdx.x; i < lops::table_floats(P); i += blockDim.x) tabs[i] = ltab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63;
   float4* wb = turns + (threadIdx.x >> 6) * 2 * TW + (P > 0 ? lane : 0);  // beta, then alpha
   float4* wa = wb + TW;
+  m2lq::Cursor cur;
   for (;;) {
-    int kq = 0;
-    if (lane == 0) kq = atomicAdd(queue, 1);
-    kq = __builtin_amdgcn_readfirstlane(kq);  // uniform: the target's values in scalar registers
-    if (kq >= ntarget) break;
-    const int64_t gid = lv.gofs[1] + order[kq];
+    const int64_t kq = m2lq::next(cur, queue, ntarget, run, lane);
+    if (kq < 0) break;
+    // the target's data are the same in all lanes: kept in scalar registers
+    const int64_t gid = lv.gofs[1] + m2lq::uniform(order[kq]);
     const int l = level_of3(lv, gid);
     const int64_t bi = gid - lv.gofs[l];
     const double* geo = lv.geom[l];
-    const double cix = geo[bi * 10 + 6], ciy = geo[bi * 10 + 7], ciz = geo[bi * 10 + 8];
-    const double rt = geo[bi * 10 + 9] > 0.0 ? geo[bi * 10 + 9] : 1.0;
-    const int64_t e0 = lv.w_off[l][bi], e1 = lv.w_off[l][bi + 1];
-    const int32_t* widx = lv.w_idx[l];
+    const double cix = m2lq::uniform(geo[bi * 10 + 6]), ciy = m2lq::uniform(geo[bi * 10 + 7]);
+    const double ciz = m2lq::uniform(geo[bi * 10 + 8]), rt_ = m2lq::uniform(geo[bi * 10 + 9]);
+    const double rt = rt_ > 0.0 ? rt_ : 1.0;
+    const int32_t* wrow = lv.w_idx[l] + m2lq::uniform(lv.w_off[l][bi]);
+    const int ne = (int)m2lq::uniform(lv.w_off[l][bi + 1] - lv.w_off[l][bi]);
     const float* Mlev = Mf + (size_t)lv.gofs[l] * SD;
-    double acc[NF];
+    m2lq::Kept<double, NF + 2, PK> acc(parkd + threadIdx.x, 256);  // the sums, ca, sa
+    m2lq::Kept<float, 3, PK> fac(parkf + threadIdx.x, 256);        // in_base, out_base, out_mult
 #pragma unroll
-    for (int i = 0; i < NF; ++i) acc[i] = 0.0;
+    for (int i = 0; i < NF; ++i) acc.put(i, 0.0);
 
     // the next batch's source indexes are loaded while this batch runs
-    int32_t jn = e0 < e1 ? widx[e0 + lane < e1 ? e0 + lane : e0] : 0;
-    for (int64_t eb = e0; eb < e1; eb += 64) {
-      const int64_t e = eb + lane;
-      const bool valid = e < e1;
+    int32_t jn = ne > 0 ? wrow[lane < ne ? lane : 0] : 0;
+    for (int eb = 0; eb < ne; eb += 64) {
+      const int e = eb + lane;
+      const bool valid = e < ne;
       const int64_t j = jn;
-      jn = widx[e + 64 < e1 ? e + 64 : e0];
+      jn = wrow[e + 64 < ne ? e + 64 : 0];
       const double dx = geo[j * 10 + 6] - cix, dy = geo[j * 10 + 7] - ciy, dz = geo[j * 10 + 8] - ciz;
       const double rs = geo[j * 10 + 9] > 0.0 ? geo[j * 10 + 9] : 1.0;
       const double rxy2 = dx * dx + dy * dy;
-      const double irho = lane_rsqrt(rxy2 + dz * dz), irxy = lane_rsqrt(rxy2);
+      const double irho = m2lq::rsqrt0(rxy2 + dz * dz), irxy = m2lq::rsqrt0(rxy2);
       const double ca = dz * irho, sa = rxy2 * irxy * irho;
       const double cb = rxy2 > 0.0 ? dx * irxy : 1.0, sb = dy * irxy;
       // a lane past the end of the list translates the first source with zero factors
-      const float in_base = valid ? (float)(rs * irho) : 0.f;
-      const float out_base = valid ? (float)(rt * irho) : 0.f;
-      const float out_mult = valid ? (float)irho : 0.f;
+      fac.put(0, valid ? (float)(rs * irho) : 0.f);
+      fac.put(1, valid ? (float)(rt * irho) : 0.f);
+      fac.put(2, valid ? (float)irho : 0.f);
+      acc.put(NF, ca);
+      acc.put(NF + 1, sa);
 
       float X[NT];
       const float4* src = (const float4*)(Mlev + (size_t)j * SD);
@@ -442,9 +449,9 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       FMM_STEP(turn_in<P>(X, cb, sb, wb));
       FMM_STEP(japply_mf<P>(X, o1));
       FMM_STEP(Ops o2(tJ, lane));
-      FMM_STEP(turn_in<P>(X, ca, sa, wa));
+      FMM_STEP(turn_in<P>(X, acc.get(NF), acc.get(NF + 1), wa));
       FMM_STEP(japply_mf<P>(X, o2));
-      FMM_STEP(ztrans_mf<P>(X, tabs + 2 * GJ, lane, in_base, out_base, out_mult));
+      FMM_STEP(ztrans_mf<P>(X, tabs + 2 * GJ, lane, fac));
       FMM_STEP(japply_mf<P>(X, Ops(tJT, lane)));
       FMM_STEP(Ops o4(tJ, lane));
       FMM_STEP(turn_back<P>(X, wa));
@@ -462,7 +469,7 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       halve<lvl(NT, 4), 2>(h4, h5, lane);
       halve<lvl(NT, 5), 1>(h5, h6, lane);
 #pragma unroll
-      for (int i = 0; i < NF; ++i) acc[i] += (double)h6[i];
+      for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + (double)h6[i]);
     }
     // lane's values: standard index base + i, where each exchange added the
     // kept half's offset; entries past a half's end are padding
@@ -485,7 +492,7 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       if (i >= len) continue;
       const int k = base + i;
       const int n = deg_of(k);
-      double v = acc[i];
+      double v = acc.get(i);
       for (int q = 0; q < n; ++q) v *= irt;
       dst[pos[k]] = v;
     }
@@ -519,7 +526,7 @@ __global__ void k_scale_lane(LevelView lv, int S, const int* __restrict__ pos, c
 }
 
 __global__ void k_zero_queue_l(int* queue) {
-  if (threadIdx.x == 0) *queue = 0;
+  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = 0;
 }
 
 template <int P>
@@ -538,10 +545,11 @@ void launch_one_lane(const Tree& t, const Tables& tb, const double* Mx, double* 
   }();
   const int64_t need = (ntarget + 3) / 4;
   const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
-  int* queue = (int*)dalloc(sizeof(int), s);
+  int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
   k_zero_queue_l<<<1, 64, 0, s>>>(queue);
   HIPCHECK(hipGetLastError());
-  k_m2l_lane<P><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue);
+  k_m2l_lane<P><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue,
+                                       m2lq::run_length(ntarget));
   HIPCHECK(hipGetLastError());
   dfree(queue, s);
   dfree(Mf, s);

@@ -1,5 +1,8 @@
-// M2L on the matrix cores (Algorithm 3, M2L; rotational form of Section
-// 2.1.3), for expansion orders p <= 15, in FP64 (v_mfma_f64_16x16x4f64).
+// M2L of the mixed-precision mode at order 15 (Algorithm 3, M2L; rotational
+// form of Section 2.1.3) on the matrix cores: binary32 on radius-scaled
+// expansions, in 16x16 tiles (v_mfma_f32_16x16x4f32).  Lower orders run one
+// pair per lane (m2l_lane.hip), where the expansion fits a lane's registers;
+// binary64 and higher orders run four lanes per pair (m2l_quad.hip).
 //
 // A block of two waves computes the local expansion of one target box i:
 //   L_i = sum over weak pairs j of  O(Q)^T Z(rho) O(Q) M_j,
@@ -36,42 +39,11 @@
 namespace fmm {
 namespace {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef double d2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-
-// The kernel runs in binary64, or (mixed precision) in binary32 on
-// radius-scaled expansions: R is the arithmetic type of the translations.
-template <class R>
-struct Ar;
-template <>
-struct Ar<double> {
-  typedef d4 v4;
-  typedef d2 v2;
-  static constexpr int kRowStride = 18;  // pair-sum rows: 144 B, no bank conflicts
-};
-template <>
-struct Ar<float> {
-  typedef f4 v4;
-  typedef f2 v2;
-  static constexpr int kRowStride = 20;
-};
-
-// Waves per SIMD the kernel is compiled for (the register budget per lane
-// is 512 / that).  binary64: 2 (its operand fragments already spill a little
-// at 256 registers).  binary32: 4 up to order 8, 3 above; measured on the
-// 2^24-point Plummer cloud at theta 0.6 against 2 waves: 131 / 137.6 / 159.3
-// ms at order 8, 156.6 / 175.2 ms (3 / 2 waves) at order 10, 220.5 / 232.5 at
-// 12, 232.2 / 259.6 at 13 (4 waves lost above order 8, on spills).
-template <int P, class R>
-struct Occ {
-  static constexpr int kWavesPerEu = 2;
-};
-template <int P>
-struct Occ<P, float> {
-  static constexpr int kWavesPerEu = P <= 8 ? 4 : 3;
-};
+typedef float R;  // arithmetic type of the translations
+typedef R v4 __attribute__((ext_vector_type(4)));
+typedef R v2 __attribute__((ext_vector_type(2)));
+constexpr int kRowStride = 20;   // pair-sum rows: no bank conflicts
+constexpr int kWavesPerEu = 3;   // the register budget per lane is 512 / that
 
 // Orders this wave's LDS accesses around a point (other lanes of the wave
 // read what this lane wrote): a compiler barrier only, since the LDS unit
@@ -82,14 +54,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f4 mfma(float a, float b, f4 c) {
+__device__ __forceinline__ v4 mfma(R a, R b, v4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <int P, class R>
+template <int P>
 struct Cfg {
   static constexpr int T = tl::ntiles(P);
   static constexpr int NP = tl::npairs(P);
@@ -100,7 +69,7 @@ struct Cfg {
   // order by the zero-padded tail of its last k-step) and two more such rows;
   // the two waves' pair-sum rounds reuse it
   static constexpr int ZDUMMY = ZR;
-  static constexpr int RSTRIDE = Ar<R>::kRowStride;
+  static constexpr int RSTRIDE = kRowStride;
   static constexpr int ZBUF = 16 * (ZR + 3) > 2 * 64 * RSTRIDE ? 16 * (ZR + 3) : 2 * 64 * RSTRIDE;
   // per pair: (cos, sin)(m (theta + pi)), (cos, sin)(m (alpha + pi)), m = 0..P;
   // 16 more bytes per pair so that the 16 pair columns hit different banks
@@ -251,9 +220,8 @@ __host__ __device__ constexpr int reg_sine(int t, int i) {
 // (c, s) <- f (cos c - sgn sin s, sgn sin c + cos s) for every (cosine, sine)
 // partner pair, f = mult * base^n for a slot of degree n (SCALE) or 1; cs:
 // this lane's (cos, sin) table shifted by 2 (g - 4)
-template <int P, int W, bool SCALE, class R>
-__device__ __forceinline__ void rotz(typename Ar<R>::v4* st, const R* cs, R sgn, int g, R base, R mult) {
-  typedef typename Ar<R>::v2 v2;
+template <int P, int W, bool SCALE>
+__device__ __forceinline__ void rotz(v4* st, const R* cs, R sgn, int g, R base, R mult) {
   constexpr int NP = tl::npairs(P);
   R pw[SCALE ? P + 1 : 1];  // mult * base^n, built here to keep it short-lived
   pw[0] = mult;
@@ -315,13 +283,13 @@ __device__ __forceinline__ void rotz(typename Ar<R>::v4* st, const R* cs, R sgn,
 
 // st[t] <- J_t st[t] for the tiles of wave W; jr: this lane's operand
 // fragments of J (in registers)
-template <int P, int W, class R>
-__device__ __forceinline__ void japply(typename Ar<R>::v4* st, const R* jr) {
+template <int P, int W>
+__device__ __forceinline__ void japply(v4* st, const R* jr) {
   constexpr int T = tl::ntiles(P);
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     if (tile_owner<P>(t) != W) continue;
-    typename Ar<R>::v4 d = {0, 0, 0, 0};
+    v4 d = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (kstep_used<P>(t, k)) d = mfma(jr[t * 4 + k], st[t][k], d);
@@ -332,15 +300,14 @@ __device__ __forceinline__ void japply(typename Ar<R>::v4* st, const R* jr) {
 // z buffer addressing: zl[k] points at row zoff(m) - m of this lane's column
 // for m = k - 4 + g (so that row (m, n) is zl[k] + 16 n), zd at the
 // write-only row, zz at the zero row
-template <class R>
 struct ZView {
   R* zl[20];
   R* zd;
   const R* zz;
 };
 
-template <int P, class R>
-__device__ __forceinline__ R* zslot(const ZView<R>& z, int t, int i, int g, bool for_read) {
+template <int P>
+__device__ __forceinline__ R* zslot(const ZView& z, int t, int i, int g, bool for_read) {
   const Quad q = quad<P>(t, i);
   R* other = for_read ? (R*)z.zz : z.zd;
   R* a0 = q.pad[0] ? other : z.zl[q.m0[0] + 4] + 16 * q.n[0];
@@ -357,8 +324,8 @@ __device__ __forceinline__ R* zslot(const ZView<R>& z, int t, int i, int g, bool
 // the next rotation.  Both waves move their tiles to the order-major rows
 // and back; each computes its own orders.  hr: this lane's operand fragments
 // of the order-m matrices (in registers).
-template <int P, int W, int SINE, class R>
-__device__ __forceinline__ void ztrans_part(typename Ar<R>::v4* st, const ZView<R>& z, R* zcol, const R* hr,
+template <int P, int W, int SINE>
+__device__ __forceinline__ void ztrans_part(v4* st, const ZView& z, R* zcol, const R* hr,
                                             int lane) {
   constexpr int T = tl::ntiles(P);
   constexpr MSplit ms = m_split<P>();
@@ -369,7 +336,7 @@ __device__ __forceinline__ void ztrans_part(typename Ar<R>::v4* st, const ZView<
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (reg_sine<P>(t, i) != SINE || all_pad<P>(t, i)) continue;
-      *zslot<P, R>(z, t, i, g, false) = st[t][i];
+      *zslot<P>(z, t, i, g, false) = st[t][i];
     }
   }
   __syncthreads();
@@ -379,7 +346,7 @@ __device__ __forceinline__ void ztrans_part(typename Ar<R>::v4* st, const ZView<
     const int K = P + 1 - m;
     const int zo = tl::zoff(P, m);
     const int ho = tl::hoff(P, m);
-    typename Ar<R>::v4 d = {0, 0, 0, 0};
+    v4 d = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < tl::hsteps(P, m); ++k) d = mfma(hr[ho + k], zcol[(zo + 4 * k) * 16], d);
 #pragma unroll
@@ -396,25 +363,21 @@ __device__ __forceinline__ void ztrans_part(typename Ar<R>::v4* st, const ZView<
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (reg_sine<P>(t, i) != SINE || all_pad<P>(t, i)) continue;
-      st[t][i] = *zslot<P, R>(z, t, i, g, true);
+      st[t][i] = *zslot<P>(z, t, i, g, true);
     }
   }
   __syncthreads();
 }
 
 // the work of wave W of the block (both waves run the same loop structure
-// and meet at the same barriers).  R = double: Mx holds the multipoles
-// (binary64).  R = float: Mx holds them in binary32, scaled as
-// M~_n = M_n / s^n with s the box radius (1 for a box of zero extent), and
+// and meet at the same barriers).  Mx holds the multipoles in binary32, scaled
+// as M~_n = M_n / s^n with s the box radius (1 for a box of zero extent), and
 // the result is unscaled into binary64 at the store.
-template <int P, int W, class R>
+template <int P, int W>
 __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* __restrict__ mtab,
                                          const R* __restrict__ Mx, double* __restrict__ Lx, int64_t ntarget,
                                          const int32_t* __restrict__ order, int* __restrict__ queue) {
-  using C = Cfg<P, R>;
-  typedef typename Ar<R>::v4 v4;
-  typedef typename Ar<R>::v2 v2;
-  constexpr bool MIXED = sizeof(R) == 4;
+  using C = Cfg<P>;
   constexpr int T = C::T;
   constexpr int S = C::S;
   constexpr int NTW = tiles_of<P>(W);
@@ -442,7 +405,7 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
       for (int k = 0; k < tl::hsteps(P, m); ++k)
         hr[tl::hoff(P, m) + k] = mtab[T * 256 + (tl::hoff(P, m) + k) * 64 + lane];
 
-  ZView<R> z;
+  ZView z;
 #pragma unroll
   for (int k = 0; k < 20; ++k) {
     const int m = k - 4 + g;
@@ -467,7 +430,7 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
     const int64_t bi = gid - lv.gofs[l];
     const double* geo = lv.geom[l];
     const double cix = geo[bi * 10 + 6], ciy = geo[bi * 10 + 7], ciz = geo[bi * 10 + 8];
-    const double rt = geo[bi * 10 + 9] > 0.0 ? geo[bi * 10 + 9] : 1.0;  // target scale (MIXED)
+    const double rt = geo[bi * 10 + 9] > 0.0 ? geo[bi * 10 + 9] : 1.0;  // target scale
     const int64_t e0 = lv.w_off[l][bi], e1 = lv.w_off[l][bi + 1];
     const int32_t* widx = lv.w_idx[l];
     const R* Mlev = Mx + (size_t)lv.gofs[l] * S;
@@ -496,16 +459,10 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
       // scalings: M'(n) (1/rho)^n into the z translation, its output times
       // (1/rho)^(j+1); with scaled expansions (s/rho)^n and (rt/rho)^j / rho
       R in_base, out_base, out_mult;
-      if constexpr (MIXED) {
-        const double rs = geo[(int64_t)j * 10 + 9] > 0.0 ? geo[(int64_t)j * 10 + 9] : 1.0;
-        in_base = valid ? (R)(rs * irho) : (R)0;
-        out_base = valid ? (R)(rt * irho) : (R)0;
-        out_mult = valid ? (R)irho : (R)0;
-      } else {
-        in_base = valid ? irho : 0.0;
-        out_base = in_base;
-        out_mult = in_base;
-      }
+      const double rs = geo[(int64_t)j * 10 + 9] > 0.0 ? geo[(int64_t)j * 10 + 9] : 1.0;
+      in_base = valid ? (R)(rs * irho) : (R)0;
+      out_base = valid ? (R)(rt * irho) : (R)0;
+      out_mult = valid ? (R)irho : (R)0;
       R* tp = trig + buf * 16 * C::TRIG + r16 * C::TRIG;  // this lane's pair
       // (cos, sin)(m (angle + pi)) by the angle-addition recurrence (binary64):
       // wave 0 builds the theta table, wave 1 the alpha table (the four lane
@@ -542,17 +499,17 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
       const R* cs_a = tp + 2 * (P + 1) + 2 * (g - 4);
       // scheduling strategy for the long barrier-free stretches
       __builtin_amdgcn_iglp_opt(0);
-      rotz<P, W, false, R>(st, cs_t, (R)1, g, (R)0, (R)1);
-      japply<P, W, R>(st, jr);
-      rotz<P, W, true, R>(st, cs_a, (R)1, g, in_base, (R)1);
-      japply<P, W, R>(st, jr);
-      ztrans_part<P, W, 0, R>(st, z, zcol, hr, lane);
-      ztrans_part<P, W, 1, R>(st, z, zcol, hr, lane);
+      rotz<P, W, false>(st, cs_t, (R)1, g, (R)0, (R)1);
+      japply<P, W>(st, jr);
+      rotz<P, W, true>(st, cs_a, (R)1, g, in_base, (R)1);
+      japply<P, W>(st, jr);
+      ztrans_part<P, W, 0>(st, z, zcol, hr, lane);
+      ztrans_part<P, W, 1>(st, z, zcol, hr, lane);
       __builtin_amdgcn_iglp_opt(0);
-      japply<P, W, R>(st, jr);
-      rotz<P, W, true, R>(st, cs_a, (R)-1, g, out_base, out_mult);
-      japply<P, W, R>(st, jr);
-      rotz<P, W, false, R>(st, cs_t, (R)-1, g, (R)0, (R)1);
+      japply<P, W>(st, jr);
+      rotz<P, W, true>(st, cs_a, (R)-1, g, out_base, out_mult);
+      japply<P, W>(st, jr);
+      rotz<P, W, false>(st, cs_t, (R)-1, g, (R)0, (R)1);
 
       // sum over the 16 pairs, four of this wave's tiles per round; lane L
       // adds up row L (slot L % 16 of its tile 4 r + L / 16); each batch sum
@@ -569,23 +526,16 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
         wave_lds_fence();
         if (4 * r + 3 < NTW || 4 * r + (lane >> 4) < NTW) {
           const R* row = red + lane * C::RSTRIDE;
-          if constexpr (MIXED) {
-            // the 16 binary32 pair results are summed in binary64 (exact for
-            // all but extreme exponent spreads)
-            double sum = 0.0;
+          // the 16 binary32 pair results are summed in binary64 (exact for
+          // all but extreme exponent spreads)
+          double sum = 0.0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const v2 v = *(const v2*)(row + 2 * k);
-              sum += (double)v.x;
-              sum += (double)v.y;
-            }
-            acc[r] += sum;
-          } else {
-            v2 v = *(const v2*)row;
-#pragma unroll
-            for (int k = 1; k < 8; ++k) v += *(const v2*)(row + 2 * k);
-            acc[r] += (double)(v.x + v.y);
+          for (int k = 0; k < 8; ++k) {
+            const v2 v = *(const v2*)(row + 2 * k);
+            sum += (double)v.x;
+            sum += (double)v.y;
           }
+          acc[r] += sum;
         }
         wave_lds_fence();
       }
@@ -600,29 +550,26 @@ __device__ __forceinline__ void m2l_wave(R* smem, const LevelView& lv, const R* 
         const int t = owned_tile<P>(W, k);
         const Pos d = slot_pos<P>(t, lane & 15);
         double v = (d.m & 1) ? -acc[r] : acc[r];
-        if (MIXED) {
-          const double irt = 1.0 / rt;
-          for (int n = 0; n < d.n; ++n) v *= irt;
-        }
+        const double irt = 1.0 / rt;
+        for (int n = 0; n < d.n; ++n) v *= irt;
         dst[tl::spos(t, lane & 15)] = v;
       }
     }
   }
 }
 
-template <int P, class R>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(Occ<P, R>::kWavesPerEu,
-                                                                     Occ<P, R>::kWavesPerEu))) void k_m2l_mfma(
+template <int P>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(kWavesPerEu, kWavesPerEu))) void k_m2l_mfma(
     LevelView lv, const R* __restrict__ mtab, const R* __restrict__ Mx, double* __restrict__ Lx,
     int64_t ntarget, const int32_t* __restrict__ order, int* __restrict__ queue) {
-  __shared__ R smem[Cfg<P, R>::LDS];
+  __shared__ R smem[Cfg<P>::LDS];
   // every LDS word starts finite: buffer tails are read (and multiplied by 0)
-  for (int k = threadIdx.x; k < Cfg<P, R>::LDS; k += 128) smem[k] = (R)0;
+  for (int k = threadIdx.x; k < Cfg<P>::LDS; k += 128) smem[k] = (R)0;
   __syncthreads();
   if (threadIdx.x < 64)
-    m2l_wave<P, 0, R>(smem, lv, mtab, Mx, Lx, ntarget, order, queue);
+    m2l_wave<P, 0>(smem, lv, mtab, Mx, Lx, ntarget, order, queue);
   else
-    m2l_wave<P, 1, R>(smem, lv, mtab, Mx, Lx, ntarget, order, queue);
+    m2l_wave<P, 1>(smem, lv, mtab, Mx, Lx, ntarget, order, queue);
 }
 
 // binary32 copy of the multipoles of levels 1..L, scaled by s^-n (s the box
@@ -647,16 +594,17 @@ __global__ void k_zero_queue(int* queue) {
   if (threadIdx.x == 0) *queue = 0;
 }
 
-template <int P, class R>
+template <int P>
 void launch_one(const Tree& t, const Tables& tb, const R* Mx, double* Lx, hipStream_t s) {
   const int64_t ntarget = t.nbox_total - 1;
+  if (ntarget <= 0) return;
   // resident blocks of this instantiation on the device (initialised once,
   // thread-safe)
   static const int grid_max = [] {
     int dev = 0, ncu = 0, per = 0;
     HIPCHECK(hipGetDevice(&dev));
     HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_m2l_mfma<P, R>, 128, 0));
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_m2l_mfma<P>, 128, 0));
     return ncu * (per > 0 ? per : 1);
   }();
   const int64_t need = ntarget;
@@ -665,46 +613,12 @@ void launch_one(const Tree& t, const Tables& tb, const R* Mx, double* Lx, hipStr
   // cleared by a kernel, not a memset node, so that the launch may be captured in a graph
   k_zero_queue<<<1, 64, 0, s>>>(queue);
   HIPCHECK(hipGetLastError());
-  const R* mt;
-  if constexpr (sizeof(R) == 4)
-    mt = tb.mtab32;
-  else
-    mt = tb.mtab;
-  k_m2l_mfma<P, R><<<grid, 128, 0, s>>>(t.view(), mt, Mx, Lx, ntarget, t.m2l_order, queue);
+  k_m2l_mfma<P><<<grid, 128, 0, s>>>(t.view(), tb.mtab32, Mx, Lx, ntarget, t.m2l_order, queue);
   HIPCHECK(hipGetLastError());
   dfree(queue, s);
 }
 
-template <class R>
-bool launch_any(const Tree& t, const Tables& tb, const R* Mx, double* Lx, hipStream_t s) {
-  switch (tb.p) {
-    case 0: launch_one<0, R>(t, tb, Mx, Lx, s); break;
-    case 1: launch_one<1, R>(t, tb, Mx, Lx, s); break;
-    case 2: launch_one<2, R>(t, tb, Mx, Lx, s); break;
-    case 3: launch_one<3, R>(t, tb, Mx, Lx, s); break;
-    case 4: launch_one<4, R>(t, tb, Mx, Lx, s); break;
-    case 5: launch_one<5, R>(t, tb, Mx, Lx, s); break;
-    case 6: launch_one<6, R>(t, tb, Mx, Lx, s); break;
-    case 7: launch_one<7, R>(t, tb, Mx, Lx, s); break;
-    case 8: launch_one<8, R>(t, tb, Mx, Lx, s); break;
-    case 9: launch_one<9, R>(t, tb, Mx, Lx, s); break;
-    case 10: launch_one<10, R>(t, tb, Mx, Lx, s); break;
-    case 11: launch_one<11, R>(t, tb, Mx, Lx, s); break;
-    case 12: launch_one<12, R>(t, tb, Mx, Lx, s); break;
-    case 13: launch_one<13, R>(t, tb, Mx, Lx, s); break;
-    case 14: launch_one<14, R>(t, tb, Mx, Lx, s); break;
-    case 15: launch_one<15, R>(t, tb, Mx, Lx, s); break;
-    default: return false;
-  }
-  return true;
-}
-
 }  // namespace
-
-bool launch_m2l_mfma(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s) {
-  if (!tb.tiled) return false;
-  return launch_any<double>(t, tb, Mx, Lx, s);
-}
 
 bool launch_m2l_lane32(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s);
 
@@ -712,15 +626,16 @@ bool launch_m2l_mfma_mixed(const Tree& t, const Tables& tb, const double* Mx, do
   if (!tb.tiled) return false;
   // orders up to 14 one pair per lane (m2l_lane.hip), 15 in 16x16 tiles
   if (launch_m2l_lane32(t, tb, Mx, Lx, s)) return true;
+  if (tb.p != 15) return false;
   float* Mf = (float*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(float), s);
   if (t.nbox_total > 1) {
     k_scale_m32<<<(unsigned)((t.nbox_total - 1 + 3) / 4), 256, 0, s>>>(t.view(), tb.stride, tb.sdeg, Mx, Mf,
                                                                       t.nbox_total);
     HIPCHECK(hipGetLastError());
   }
-  const bool ok = launch_any<float>(t, tb, Mf, Lx, s);
+  launch_one<15>(t, tb, Mf, Lx, s);
   dfree(Mf, s);
-  return ok;
+  return true;
 }
 
 }  // namespace fmm

@@ -9,27 +9,33 @@
 // result unscaled by r_t^-n), here all in binary64.
 //
 // A wave takes 16 pairs of one target box; lane 16 k + q holds phase k of
-// pair q, i.e. the members m = k (mod 4) of every block (lane_ops.h: per
-// degree two blocks indexed by the order m, the two parity classes of J).
+// pair q (lane_ops.h: per degree two blocks indexed by the order m, the two
+// parity classes of J, their even and odd orders in registers of their own).
 // Hence:
 //   - a J block is a chain of v_mfma_f64_4x4x4f64, one per (k-step, output
 //     chunk of 4 rows): the instruction's k index runs over the four phase
 //     lanes of a pair, and its output row i lands in phase i of the same pair,
 //     so every step's result is the next step's operand in place; the
 //     operator values come from LDS (binary64 instructions take no broadcast
-//     of one block's operand, so every lane reads its value); J^T has a
+//     of one block's operand, so every lane reads its value); the parts that
+//     join orders of the wrong parity are zero and left out (368 instead of
+//     576 instructions per batch at order 12); J^T has a
 //     table of its own up to order 18 and above reads the table of J with
 //     the two chunk indices swapped and each 4x4 part transposed;
 //   - a z-turn multiplies the (cosine, sine) parts of (d, m), which share a
 //     lane and register, by the lane's own e^{i m theta};
 //   - the z translation of order m involves only order-m coefficients of
-//     all degrees, which share a lane: each lane runs it for its orders on the
-//     vector units (binary64 vector and matrix peaks are equal on this part);
+//     all degrees, which share a lane once the even and odd registers have
+//     exchanged halves: each lane runs it for its orders on the vector units (binary64 vector and matrix peaks are equal on this part);
 //   - the 16 pair results are summed across the lanes by halving exchanges
 //     through DPP (fixed order: deterministic) and the batches in binary64.
-// Padding is per 4x4 part of a block: 1.57x the algorithmic J products at
-// order 12, against 2.42x for the 16x16 tiles of m2l_mfma.hip.  Orders 16..20
-// run here too (one wave per SIMD), where the tiles stop.
+// What bounds it: binary64 matrix and vector issue, up to order 14 at better
+// than 85 % of the cycles; from order 15 on a few values still spill, and above
+// it one wave per SIMD hides no latency.  Measured on 2^22 Plummer points (5
+// levels, theta 0.6, 194 million pairs), M2L in ms: order 8 38, 10 59, 12 87,
+// 13 102, 14 120, 15 154, 16 289, 18 574, 20 833; with whole blocks of J and
+// values spilled instead of parked 46, 68, 106, 150, -, -, 375, 703, 1,091, and
+// in 16x16 tiles of two degree blocks 178 and 190 at orders 14 and 15.
 //
 // The same steps with the M2M or L2L core along z make k_xlate_quad (end of
 // the file), which runs M2M and L2L up to order 13.
@@ -37,6 +43,7 @@
 
 #include "fmm_internal.h"
 #include "lane_ops.h"
+#include "m2l_queue.h"
 #include "tile_layout.h"
 
 namespace fmm {
@@ -57,26 +64,19 @@ __host__ __device__ constexpr int qlvl(int nt, int s) {
   return v;
 }
 
-// degree of register R
-__host__ __device__ constexpr int qdeg(int R) {
-  int d = 0;
-  while (lops::qbase(d + 1, 0) <= R) ++d;
-  return d;
-}
-
 __device__ __forceinline__ double mfma64(double a, double b, double c) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
-// One block (d, x) of a J application: NR = qreg(d) k-steps times NR output
-// chunks; tl = the lane's slot in a 16-value operand, 4 k + i, or with T
+// One block (d, x) of a J application: NR = qreg(d) input registers times NR
+// output registers, less the parts without nonzero entries; tl = the lane's slot in a 16-value operand, 4 k + i, or with T
 // (J^T from the table of J, whose part (c, g) transposed is part (g, c) of
 // J^T) 4 i + k
 template <int D, int X>
 struct QBlk {
   static constexpr int NR = lops::qreg(D);
   static constexpr int R0 = lops::qbase(D, X);
-  static constexpr int U0 = lops::qj_offset(D, X);
+  static constexpr int U0 = lops::qp_offset(D, X);
   double acc[NR];
   __device__ __forceinline__ QBlk() {
     qfor<0, NR>([&](auto c) __attribute__((always_inline)) { acc[c] = 0.0; });
@@ -87,8 +87,10 @@ struct QBlk {
       const double xg = X_[R0 + G];
       qfor<0, NR>([&](auto c) __attribute__((always_inline)) {
         constexpr int C = decltype(c)::value;
-        constexpr int u = U0 + (T ? C * NR + G : G * NR + C);
-        acc[c] = mfma64(tab[16 * u + tl], xg, acc[c]);
+        if constexpr (lops::qpart(D, X, G, C)) {
+          constexpr int u = U0 + (T ? lops::qpart_rank(D, X, C, G) : lops::qpart_rank(D, X, G, C));
+          acc[c] = mfma64(tab[16 * u + tl], xg, acc[c]);
+        }
       });
     }
   }
@@ -131,42 +133,69 @@ __device__ __forceinline__ void qjapply(double* X, const double* tab, int tl) {
   });
 }
 
-// X <- Rz(sign * theta) X with (c1, s1) = (cos theta, sin theta): the lane's
-// members m = 4 g + k turn by e^{i m theta}; with block 0 holding c_m for
-// even m and s_m for odd m, the turn of (b0, b1) is (C b0 - S' b1, S' b0 +
-// C b1) with S' = S for even m and -S for odd m
+// X <- Rz(sign * theta) X with (c1, s1) = (cos theta, sin theta): each member
+// turns by e^{i m theta} of its order m; with block 0 holding c_m for even m
+// and s_m for odd m, the turn of (b0, b1) is (C b0 - S' b1, S' b0 + C b1) with
+// S' = S for even m and -S for odd m.  Per eight orders a lane holds one of the
+// even orders (8 b + 2 k), one of the odd (8 b + 2 k + 1) and, in a shared
+// register, one of the lowest four.
 template <int P>
 __device__ __forceinline__ void qrotz(double* X, double c1, double s1, double sign, int k) {
-  constexpr int NG = P / 4 + 1;
-  // e^{i k theta} and e^{i 4 theta}
+  constexpr int NB = P / 8 + 1;
   const double c2 = c1 * c1 - s1 * s1, s2 = 2.0 * s1 * c1;
   const double c3 = c2 * c1 - s2 * s1, s3 = s2 * c1 + c2 * s1;
   const double c4 = c2 * c2 - s2 * s2, s4 = 2.0 * s2 * c2;
-  double cc = k == 0 ? 1.0 : k == 1 ? c1 : k == 2 ? c2 : c3;
-  double ss = k == 0 ? 0.0 : k == 1 ? s1 : k == 2 ? s2 : s3;
-  const double par = (k & 1) ? -sign : sign;
-  double C[NG], S[NG];
+  const double c6 = c4 * c2 - s4 * s2, s6 = s4 * c2 + c4 * s2;
+  const double c8 = c4 * c4 - s4 * s4, s8 = 2.0 * s4 * c4;
+  double C[NB][3], S[NB][3];  // even, odd, shared
+  C[0][0] = k == 0 ? 1.0 : k == 1 ? c2 : k == 2 ? c4 : c6;
+  S[0][0] = sign * (k == 0 ? 0.0 : k == 1 ? s2 : k == 2 ? s4 : s6);
+  C[0][1] = C[0][0] * c1 - sign * S[0][0] * s1;
+  S[0][1] = -(S[0][0] * c1 + sign * C[0][0] * s1);
+  C[0][2] = k < 2 ? C[0][0] : k == 2 ? c1 : c3;
+  S[0][2] = k < 2 ? S[0][0] : -sign * (k == 2 ? s1 : s3);
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    C[g] = cc;
-    S[g] = par * ss;
-    const double nc = cc * c4 - ss * s4, ns = ss * c4 + cc * s4;
-    cc = nc;
-    ss = ns;
-  }
+  for (int b = 1; b < NB; ++b)
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      // the signed sine of an odd order turns the other way
+      const double sg = t == 0 ? sign : t == 1 ? -sign : (k < 2 ? sign : -sign);
+      C[b][t] = C[b - 1][t] * c8 - sg * S[b - 1][t] * s8;
+      S[b][t] = S[b - 1][t] * c8 + sg * C[b - 1][t] * s8;
+    }
   qfor<0, P + 1>([&](auto dI) __attribute__((always_inline)) {
     constexpr int d = decltype(dI)::value;
     qfor<0, lops::qreg(d)>([&](auto g) __attribute__((always_inline)) {
       constexpr int G = decltype(g)::value;
+      constexpr int t = lops::qpaired(d, G) ? G & 1 : 2;
       constexpr int r0 = lops::qbase(d, 0) + G, r1 = lops::qbase(d, 1) + G;
       const double b0 = X[r0], b1 = X[r1];
-      X[r0] = C[G] * b0 - S[G] * b1;
-      X[r1] = S[G] * b0 + C[G] * b1;
+      X[r0] = C[G / 2][t] * b0 - S[G / 2][t] * b1;
+      X[r1] = S[G / 2][t] * b0 + C[G / 2][t] * b1;
     });
   });
 }
 
-// the z-axis translation: the lane's orders m = 4 g + k, both blocks, with
+// exchanges the two halves of the wave between the even and the odd register
+// of every pair: (even, odd orders) <-> (lower, upper four of the eight)
+template <int P>
+__device__ __forceinline__ void qsort_orders(double* X) {
+  qfor<4, P + 1>([&](auto dI) __attribute__((always_inline)) {
+    constexpr int d = decltype(dI)::value;
+    qfor<0, lops::qreg(d) / 2>([&](auto bI) __attribute__((always_inline)) {
+      qfor<0, 2>([&](auto xI) __attribute__((always_inline)) {
+        constexpr int r = lops::qbase(d, decltype(xI)::value) + 2 * decltype(bI)::value;
+        const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(X[r]), __double2loint(X[r + 1]), false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(X[r]), __double2hiint(X[r + 1]), false, false);
+        X[r] = __hiloint2double(h[0], l[0]);
+        X[r + 1] = __hiloint2double(h[1], l[1]);
+      });
+    });
+  });
+}
+
+// the z-axis translation: the lane's orders m = 4 g + qshared(k), both blocks
+// (the registers sorted by order meanwhile), with
 // the core A[m][d][n] of its own order (Az, orders above P zero).  Input
 // degree n is first multiplied by in_base^n and output degree d by out_mult
 // out_base^d; with EXP also by 2^(in_exp n) and 2^(out_exp d) (ldexp: exact,
@@ -188,11 +217,13 @@ __device__ __forceinline__ void qztrans(double* X, const double* __restrict__ Az
       w *= in_base;
     });
   }
+  qsort_orders<P>(X);
+  const int ks = lops::qshared(k);
   qfor<0, P / 4 + 1>([&](auto gI) __attribute__((always_inline)) {
     constexpr int G = decltype(gI)::value;
     constexpr int N0 = 4 * G;  // lowest degree holding register G
     // the lane's order, orders above P reading the zero slot P + 1
-    const double* Am = Az + (4 * G + k <= P ? 4 * G + k : P + 1) * P1 * P1;
+    const double* Am = Az + (4 * G + ks <= P ? 4 * G + ks : P + 1) * P1 * P1;
     double y0[P1 - N0], y1[P1 - N0];
     qfor<0, P1 - N0>([&](auto r) __attribute__((always_inline)) { y0[r] = y1[r] = 0.0; });
     // input degree by input degree: only one column of the core is loaded
@@ -214,6 +245,7 @@ __device__ __forceinline__ void qztrans(double* X, const double* __restrict__ Az
       X[lops::qbase(d, 1) + G] = y1[d - N0];
     });
   });
+  qsort_orders<P>(X);
   {
     double w = out_mult;
     qfor<0, P + 1>([&](auto dI) __attribute__((always_inline)) {
@@ -235,17 +267,20 @@ __device__ __forceinline__ int qlevel_of(const LevelView& lv, int64_t gid) {
   return l;
 }
 
-// Waves per SIMD: 2 up to order 13, 1 from 16 on.  One block per CU (512
-// threads for two waves per SIMD, 256 for one), so that the tables (J, J^T up
-// to order 18, the z core: 55 KB at order 12, 158 KB at 18, 143 KB at 20) are
-// staged into LDS once per CU.
+// Waves per SIMD: 2 up to order 15, 1 above.  One block per CU (512 threads
+// for two waves per SIMD, 256 for one), so that the tables (J, J^T up to order
+// 18, the z core) are staged into LDS once per CU, and beside them the values
+// that a lane parks while the translation runs: the angles, the distance
+// factors, the sums over the batches.
 template <int P>
 struct QuadCfg {
-  static constexpr int kWaves = P <= 13 ? 2 : 1;
-  static constexpr int kThreads = 256 * kWaves;
-  static constexpr int kJ = 16 * lops::qj_count(P);  // doubles of the J table
-  static constexpr int kLds = lops::qtable_doubles(P);
-  static_assert(kLds * 8 <= 160 * 1024, "the tables must fit in LDS");
+  static constexpr int kThreads = lops::qthreads(P);
+  static constexpr int kWaves = kThreads / 256;
+  static constexpr int kJ = 16 * lops::qp_count(P);  // doubles of the J table
+  static constexpr int kLds = lops::qp_doubles(P);
+  static constexpr int kSums = lops::qsums(P);
+  static_assert(kLds * 8 + lops::qpark_bytes(P) <= 160 * 1024, "tables and parked values must fit in LDS");
+  static_assert(kSums == qlvl(lops::nq(P), 4) && lops::qp_count(P) <= lops::qj_count(P), "");
 };
 
 // One step of the translation, kept apart from its neighbours by the
@@ -286,58 +321,89 @@ __device__ __forceinline__ void qhalve(const double* src, double* dst, int lane)
   }
 }
 
+// Storage position of the coefficient in (register, phase) = (t / 4, t % 4) and
+// its degree times 65536; -1 for a zero slot.  All degrees at once: the loop
+// unrolls into a few comparisons.
+template <int P>
+__device__ __forceinline__ int qslot(int t, const int* __restrict__ pos) {
+  const int R = t >> 2, ph = t & 3;
+  int w = -1;
+  qfor<0, P + 1>([&](auto dI) __attribute__((always_inline)) {
+    constexpr int d = decltype(dI)::value;
+    if (R >= lops::qbase(d, 0) && R < lops::qbase(d + 1, 0)) {
+      const int x = R - lops::qbase(d, 0) >= lops::qreg(d) ? 1 : 0;
+      const int g = R - lops::qbase(d, 0) - x * lops::qreg(d);
+      const int mi = lops::qmember(d, x, lops::qorder(d, g, ph));
+      if (mi >= 0) w = pos[d * d + mi] | (d << 16);
+    }
+  });
+  return w;
+}
+
 template <int P>
 __global__ __launch_bounds__(QuadCfg<P>::kThreads)
 __attribute__((amdgpu_waves_per_eu(QuadCfg<P>::kWaves, QuadCfg<P>::kWaves))) void
 k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict__ pos, int S,
            const double* __restrict__ Mq, double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order,
-           int* __restrict__ queue) {
+           int* __restrict__ queue, int run) {
   constexpr int NQ = lops::nq(P);
   constexpr int NJ = QuadCfg<P>::kJ;
-  constexpr int NF = qlvl(NQ, 4);  // values a lane holds after the exchanges
+  constexpr int NF = QuadCfg<P>::kSums;  // values a lane holds after the exchanges
   constexpr int NL = QuadCfg<P>::kLds;
+  constexpr int NTH = QuadCfg<P>::kThreads;
   __shared__ double tabs[NL];
+  __shared__ double park[(6 + NF) * NTH];
+  __shared__ int slot[NQ * 4];
   for (int i = threadIdx.x; i < NL; i += blockDim.x) tabs[i] = qtab[i];
+  for (int t = threadIdx.x; t < NQ * 4; t += blockDim.x) slot[t] = qslot<P>(t, pos);
   __syncthreads();
-  constexpr bool HJT = lops::qtable_has_jt(P);
+  constexpr bool HJT = lops::qp_has_jt(P);
   const double* Az = tabs + (HJT ? 2 : 1) * NJ;
   const int lane = threadIdx.x & 63;
   const int k = lane >> 4, q = lane & 15;
   const int tl = 4 * k + (lane & 3);   // this lane's value in a 4x4 part of J
   const int tlt = 4 * (lane & 3) + k;  // and of J^T
+  m2lq::Cursor cur;
   for (;;) {
-    int kq = 0;
-    if (lane == 0) kq = atomicAdd(queue, 1);
-    kq = __builtin_amdgcn_readfirstlane(kq);
-    if (kq >= ntarget) break;
-    const int64_t gid = lv.gofs[1] + order[kq];
+    const int64_t kq = m2lq::next(cur, queue, ntarget, run, lane);
+    if (kq < 0) break;
+    // the target's data are the same in all lanes: kept in scalar registers
+    const int64_t gid = lv.gofs[1] + m2lq::uniform(order[kq]);
     const int l = qlevel_of(lv, gid);
     const int64_t bi = gid - lv.gofs[l];
     const double* geo = lv.geom[l];
-    const double cix = geo[bi * 10 + 6], ciy = geo[bi * 10 + 7], ciz = geo[bi * 10 + 8];
-    const double rt = geo[bi * 10 + 9] > 0.0 ? geo[bi * 10 + 9] : 1.0;
-    const int64_t e0 = lv.w_off[l][bi], e1 = lv.w_off[l][bi + 1];
-    const int32_t* widx = lv.w_idx[l];
+    const double cix = m2lq::uniform(geo[bi * 10 + 6]), ciy = m2lq::uniform(geo[bi * 10 + 7]);
+    const double ciz = m2lq::uniform(geo[bi * 10 + 8]), rt_ = m2lq::uniform(geo[bi * 10 + 9]);
+    const double rt = rt_ > 0.0 ? rt_ : 1.0;
+    const int32_t* wrow = lv.w_idx[l] + m2lq::uniform(lv.w_off[l][bi]);
+    const int ne = (int)m2lq::uniform(lv.w_off[l][bi + 1] - lv.w_off[l][bi]);
     const double* Mlev = Mq + (size_t)lv.gofs[l] * NQ * 4;
-    double acc[NF];
+    m2lq::Kept<double, NF, true> acc(park + 6 * NTH + threadIdx.x, NTH);
+    m2lq::Kept<double, 6, true> geom(park + threadIdx.x, NTH);  // ca, sa, cb, sb, out_base, out_mult
 #pragma unroll
-    for (int i = 0; i < NF; ++i) acc[i] = 0.0;
+    for (int i = 0; i < NF; ++i) acc.put(i, 0.0);
 
-    for (int64_t eb = e0; eb < e1; eb += 16) {
-      const int64_t e = eb + q;
-      const bool valid = e < e1;
-      const int64_t j = widx[valid ? e : e0];
+    // the next batch's source indexes are loaded while this batch runs
+    int32_t jn = ne > 0 ? wrow[q < ne ? q : 0] : 0;
+    for (int eb = 0; eb < ne; eb += 16) {
+      const int e = eb + q;
+      const bool valid = e < ne;
+      const int64_t j = jn;
+      jn = wrow[e + 16 < ne ? e + 16 : 0];
       const double dx = geo[j * 10 + 6] - cix, dy = geo[j * 10 + 7] - ciy, dz = geo[j * 10 + 8] - ciz;
       const double rs = geo[j * 10 + 9] > 0.0 ? geo[j * 10 + 9] : 1.0;
       const double rxy2 = dx * dx + dy * dy;
-      const double rho = sqrt(rxy2 + dz * dz), rxy = sqrt(rxy2);
-      const double irho = 1.0 / rho;
-      const double ca = dz * irho, sa = rxy * irho;
-      const double cb = rxy > 0.0 ? dx / rxy : 1.0, sb = rxy > 0.0 ? dy / rxy : 0.0;
+      const double irho = m2lq::rsqrt0(rxy2 + dz * dz), irxy = m2lq::rsqrt0(rxy2);
+      const double ca = dz * irho, sa = rxy2 * irxy * irho;
+      const double cb = rxy2 > 0.0 ? dx * irxy : 1.0, sb = dy * irxy;
       // a pair past the end of the list translates the first source with zero factors
       const double in_base = valid ? rs * irho : 0.0;
-      const double out_base = valid ? rt * irho : 0.0;
-      const double out_mult = valid ? irho : 0.0;
+      geom.put(0, ca);
+      geom.put(1, sa);
+      geom.put(2, cb);
+      geom.put(3, sb);
+      geom.put(4, valid ? rt * irho : 0.0);
+      geom.put(5, valid ? irho : 0.0);
 
       double X[NQ];
       const double* src = Mlev + (size_t)j * NQ * 4 + k;
@@ -346,13 +412,13 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
 
       FMM_QSTEP(qrotz<P>(X, cb, sb, -1.0, k));
       FMM_QSTEP((qjapply<P, !HJT>(X, HJT ? tabs + NJ : tabs, HJT ? tl : tlt)));
-      FMM_QSTEP(qrotz<P>(X, ca, sa, -1.0, k));
+      FMM_QSTEP(qrotz<P>(X, geom.get(0), geom.get(1), -1.0, k));
       FMM_QSTEP((qjapply<P, false>(X, tabs, tl)));
-      FMM_QSTEP(qztrans<P>(X, Az, k, in_base, out_base, out_mult));
+      FMM_QSTEP(qztrans<P>(X, Az, k, in_base, geom.get(4), geom.get(5)));
       FMM_QSTEP((qjapply<P, !HJT>(X, HJT ? tabs + NJ : tabs, HJT ? tl : tlt)));
-      FMM_QSTEP(qrotz<P>(X, ca, sa, 1.0, k));
+      FMM_QSTEP(qrotz<P>(X, geom.get(0), geom.get(1), 1.0, k));
       FMM_QSTEP((qjapply<P, false>(X, tabs, tl)));
-      FMM_QSTEP(qrotz<P>(X, cb, sb, 1.0, k));
+      FMM_QSTEP(qrotz<P>(X, geom.get(2), geom.get(3), 1.0, k));
 
       // sum over the 16 pairs (lane bits 0..3): four halving exchanges
       double h1[qlvl(NQ, 1)], h2[qlvl(NQ, 2)], h3[qlvl(NQ, 3)], h4[qlvl(NQ, 4)];
@@ -361,7 +427,7 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
       qhalve<qlvl(NQ, 2), qlvl(NQ, 3), 2>(h2, h3, lane);
       qhalve<qlvl(NQ, 3), qlvl(NQ, 4), 1>(h3, h4, lane);
 #pragma unroll
-      for (int i = 0; i < NF; ++i) acc[i] += h4[i];
+      for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + h4[i]);
     }
     // lane's values: registers base + i of phase k, where each exchange
     // added the kept half's offset; entries past a half's end are padding
@@ -382,15 +448,11 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
     qfor<0, NF>([&](auto iI) __attribute__((always_inline)) {
       constexpr int i = decltype(iI)::value;
       if (i < len) {
-        const int R = base + i;
-        const int d = qdeg(R);
-        const int x = R - lops::qbase(d, 0) >= lops::qreg(d) ? 1 : 0;
-        const int g = R - lops::qbase(d, x);
-        const int mi = lops::qmember(d, x, 4 * g + k);
-        if (mi >= 0) {
-          double v = acc[i];
-          for (int t = 0; t < d; ++t) v *= irt;
-          dst[pos[d * d + mi]] = v;
+        const int w = slot[4 * (base + i) + k];
+        if (w >= 0) {
+          double v = acc.get(i);
+          for (int t = w >> 16; t > 0; --t) v *= irt;
+          dst[w & 0xffff] = v;
         }
       }
     });
@@ -410,22 +472,18 @@ __global__ void k_quad_copy(LevelView lv, int S, const int* __restrict__ pos, co
   const double r = lv.geom[l][(gid - lv.gofs[l]) * 10 + 9];
   const double is = r > 0.0 ? 1.0 / r : 1.0;
   for (int t = threadIdx.x & 63; t < 4 * NQ; t += 64) {
-    const int R = t >> 2, k = t & 3;
-    const int d = qdeg(R);
-    const int x = R - lops::qbase(d, 0) >= lops::qreg(d) ? 1 : 0;
-    const int g = R - lops::qbase(d, x);
-    const int mi = lops::qmember(d, x, 4 * g + k);
+    const int w = qslot<P>(t, pos);
     double v = 0.0;
-    if (mi >= 0) {
-      v = Mx[(size_t)gid * S + pos[d * d + mi]];
-      for (int u = 0; u < d; ++u) v *= is;
+    if (w >= 0) {
+      v = Mx[(size_t)gid * S + (w & 0xffff)];
+      for (int u = w >> 16; u > 0; --u) v *= is;
     }
     Mq[(size_t)gid * NQ * 4 + t] = v;
   }
 }
 
 __global__ void k_zero_queue_q(int* queue) {
-  if (threadIdx.x == 0) *queue = 0;
+  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = 0;
 }
 
 template <int P>
@@ -445,11 +503,11 @@ void launch_one_quad(const Tree& t, const Tables& tb, const double* Mx, double* 
   }();
   const int64_t need = (ntarget + QuadCfg<P>::kThreads / 64 - 1) / (QuadCfg<P>::kThreads / 64);
   const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
-  int* queue = (int*)dalloc(sizeof(int), s);
+  int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
   k_zero_queue_q<<<1, 64, 0, s>>>(queue);
   HIPCHECK(hipGetLastError());
   k_m2l_quad<P><<<grid, QuadCfg<P>::kThreads, 0, s>>>(t.view(), tb.quad, tb.pos, tb.stride, Mq, Lx, ntarget,
-                                                       t.m2l_order, queue);
+                                                       t.m2l_order, queue, m2lq::run_length(ntarget));
   HIPCHECK(hipGetLastError());
   dfree(queue, s);
   dfree(Mq, s);
@@ -476,16 +534,13 @@ k_xlate_quad(LevelView lv, int l, const double* __restrict__ qtab, const int* __
   constexpr int NJ = QuadCfg<P>::kJ;
   constexpr int NL = QuadCfg<P>::kLds;
   constexpr int NF = qlvl(NQ, 3);  // values a lane holds after the M2M exchanges
-  static_assert(lops::qtable_has_jt(P), "orders whose table holds J^T");
+  static_assert(lops::qp_has_jt(P), "orders whose table holds J^T");
   __shared__ double tabs[NL];
   __shared__ int spos[NQ * 4];  // storage position of (register, phase); -1: zero slot
   for (int i = threadIdx.x; i < NL; i += blockDim.x) tabs[i] = qtab[i];
   for (int t = threadIdx.x; t < NQ * 4; t += blockDim.x) {
-    const int R = t >> 2, ph = t & 3;
-    const int d = qdeg(R);
-    const int x = R - lops::qbase(d, 0) >= lops::qreg(d) ? 1 : 0;
-    const int mi = lops::qmember(d, x, 4 * (R - lops::qbase(d, x)) + ph);
-    spos[t] = mi >= 0 ? pos[d * d + mi] : -1;
+    const int w = qslot<P>(t, pos);
+    spos[t] = w >= 0 ? w & 0xffff : -1;
   }
   __syncthreads();
   const double* Az = tabs + 2 * NJ;
@@ -620,9 +675,7 @@ bool launch_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStream_t
 
 }  // namespace
 
-// binary64 M2L with this kernel: orders up to 13 and 16..20; false for 14
-// and 15 (the 16x16 tile kernel is faster there, the two-wave quad kernel
-// spills)
+// binary64 M2L with this kernel, at every order
 bool launch_m2l_quad64(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s) {
   switch (tb.p) {
     case 0: launch_one_quad<0>(t, tb, Mx, Lx, s); break;
@@ -639,6 +692,8 @@ bool launch_m2l_quad64(const Tree& t, const Tables& tb, const double* Mx, double
     case 11: launch_one_quad<11>(t, tb, Mx, Lx, s); break;
     case 12: launch_one_quad<12>(t, tb, Mx, Lx, s); break;
     case 13: launch_one_quad<13>(t, tb, Mx, Lx, s); break;
+    case 14: launch_one_quad<14>(t, tb, Mx, Lx, s); break;
+    case 15: launch_one_quad<15>(t, tb, Mx, Lx, s); break;
     case 16: launch_one_quad<16>(t, tb, Mx, Lx, s); break;
     case 17: launch_one_quad<17>(t, tb, Mx, Lx, s); break;
     case 18: launch_one_quad<18>(t, tb, Mx, Lx, s); break;

@@ -507,7 +507,6 @@ void far_field(const Tree& t, const double* qt, int p, int prec, const int32_t* 
   const Tables& tb = tables_for(p, s);
   double* Mx = (double*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(double), s);
   double* Lx = (double*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(double), s);
-  for (int k = 0; k < 4; ++k) far[k] = (double*)dalloc(std::max<int64_t>(1, npts) * sizeof(double), s);
   tm.begin(FMM_PH_P2M, s);
   launch_p2m(t, tb, qt, Mx, s);
   tm.end(FMM_PH_P2M, s);
@@ -520,6 +519,8 @@ void far_field(const Tree& t, const double* qt, int p, int prec, const int32_t* 
   tm.begin(FMM_PH_L2L, s);
   for (int l = 2; l <= L; ++l) launch_l2l(t, l, tb, Lx, s);
   tm.end(FMM_PH_L2L, s);
+  // after M2L has given back its copy of the multipoles
+  for (int k = 0; k < 4; ++k) far[k] = (double*)dalloc(std::max<int64_t>(1, npts) * sizeof(double), s);
   tm.begin(FMM_PH_L2P, s);
   launch_l2p(t, tb, Lx, start, px, py, pz, far[0], far[1], far[2], far[3], s);
   tm.end(FMM_PH_L2P, s);
@@ -588,24 +589,22 @@ void evaluate(const Tree& t, const double* q, int p, int parts, int prec, double
 }
 
 size_t eval_scratch_bytes(const Tree& t, int p, int prec) {
-  // what evaluate() allocates, at its peak (far_field inside the charges'
-  // lifetime, then the near field's partial sums while the far field lives)
+  // what evaluate() allocates, at its peak: the charges all along, then the
+  // expansions with M2L's copy of the multipoles and its queue, the expansions
+  // with the far field, or the far field with the near field's partial sums
   const size_t stride = p <= tl::kMaxP ? (size_t)tl::stride(p) : (size_t)nterms(p);
   const size_t nbox = (size_t)t.nbox_total;
+  // the copy, per box: binary32 dense (per-lane kernel, orders up to 14) or
+  // tiled (order 15), else binary64 in the quad layout
+  size_t copy;
+  if (prec != FMM_PREC_F64 && p <= 14) copy = (size_t)lops::dense_stride(p) * 4;
+  else if (prec != FMM_PREC_F64 && p <= tl::kMaxP) copy = stride * 4;
+  else copy = (size_t)lops::nq(p) * 4 * 8;
   auto one = [&](int64_t npts, int64_t npart) {
-    const size_t qt = (size_t)t.n * 8;
-    const size_t far = t.L >= 1 ? 4 * (size_t)std::max<int64_t>(1, npts) * 8 : 0;
-    // the M2L kernel's own copy of the multipoles, per box: binary32 dense
-    // (per-lane kernel, orders up to 14) or tiled (order 15), else binary64
-    // in the quad layout (orders up to 13 and 16..20)
-    size_t copy = 0;
-    if (prec != FMM_PREC_F64 && p <= 14) copy = (size_t)lops::dense_stride(p) * 4;
-    else if (prec != FMM_PREC_F64 && p <= tl::kMaxP) copy = stride * 4;
-    else if (p <= 13 || p >= 16) copy = (size_t)lops::nq(p) * 4 * 8;
-    size_t expn = 0;
-    if (t.L >= 1) expn = 2 * nbox * stride * 8 + 256 + nbox * copy;  // multipoles, locals, M2L queue, copy
     const size_t part = (size_t)std::max<int64_t>(0, npart) * 32;
-    return qt + far + std::max(expn, part);
+    if (t.L == 0) return (size_t)t.n * 8 + part;
+    const size_t expn = 2 * nbox * stride * 8, far = 4 * (size_t)std::max<int64_t>(1, npts) * 8;
+    return (size_t)t.n * 8 + std::max({expn + 256 + nbox * copy, expn + far, far + part});
   };
   size_t b = one(t.n, t.p2p_npart);
   if (t.m > 0) b = std::max(b, one(t.m, t.p2p_ntpart));

@@ -65,6 +65,60 @@ int main() {
 """
 
 
+QUAD = r"""
+#define __host__
+#define __device__
+#include <cstdio>
+#include <set>
+#include <utility>
+#include "lane_ops.h"
+using namespace fmm::lops;
+int main() {
+  int fails = 0;
+  for (int p = 0; p <= 20; ++p) {
+    int u = 0;
+    for (int d = 0; d <= p; ++d)
+      for (int x = 0; x < 2; ++x) {
+        // every order 0..d in exactly one (register, phase)
+        std::set<int> orders;
+        for (int g = 0; g < qreg(d); ++g)
+          for (int k = 0; k < 4; ++k) {
+            const int m = qorder(d, g, k);
+            if (m <= d) fails += !orders.insert(m).second;
+            // the exchange of wave halves sorts a pair of registers by order
+            const int e = 4 * g + qshared(k);
+            if (qpaired(d, g)) {
+              const int src = (g & ~1) + (k >> 1), ph = 2 * (g & 1) + (k & 1);
+              fails += qorder(d, src, ph) != e;
+            } else {
+              fails += m != e;
+            }
+          }
+        fails += (int)orders.size() != d + 1;
+        // kept parts: numbered without gaps, in order; the others hold no nonzero entry
+        fails += qp_offset(d, x) != u;
+        for (int g = 0; g < qreg(d); ++g)
+          for (int c = 0; c < qreg(d); ++c) {
+            bool any = false;
+            for (int k = 0; k < 4; ++k)
+              for (int i = 0; i < 4; ++i) {
+                const int m = qorder(d, g, k), r = qorder(d, c, i);
+                any = any || (qmember(d, x, m) >= 0 && qmember(d, x, r) >= 0 && (m + r + d + x) % 2 == 0);
+              }
+            fails += any != qpart(d, x, g, c);
+            fails += qpart(d, x, g, c) != qpart(d, x, c, g);
+            if (any) fails += qp_offset(d, x) + qpart_rank(d, x, g, c) != u++;
+          }
+      }
+    fails += qp_count(p) != u;
+    fails += qp_has_jt(p) != (p <= 18) || qp_doubles(p) * 8 + qpark_bytes(p) > 160 * 1024;
+  }
+  std::printf("%d failures\n", fails);
+  return fails != 0;
+}
+"""
+
+
 def run_host(tmp_path, program):
     gxx = shutil.which("g++")
     if gxx is None:
@@ -76,8 +130,9 @@ def run_host(tmp_path, program):
     assert out.returncode == 0, out.stdout[-2000:]
 
 
-def test_lane_sub_blocks(tmp_path):
-    run_host(tmp_path, LANE)
+@pytest.mark.parametrize("program", [LANE, QUAD], ids=["lane", "quad"])
+def test_split_layouts(tmp_path, program):
+    run_host(tmp_path, program)
 
 
 def harmonics(p, v):
