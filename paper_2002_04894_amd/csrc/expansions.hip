@@ -301,12 +301,14 @@ std::vector<float> lane_tables(const HostTables& h, int p) {
     for (int st = 0; st < ju_steps(p); ++st)
       for (int b = 0; b < 4; ++b) {
         const int n = ju_degree(p, st, b), cls = st & 1, a = b & 1, rows = ju_rows(p, st, b);
-        for (int k = 0; k < ju_cols(p, st, b); ++k)
-          for (int r = 0; r < rows; ++r) {
+        const int lead = ju_lead(p, st, b);
+        for (int k = -lead; k < ju_cols(p, st, b); ++k)  // -1: the leading column 0
+          for (int r = 0; r < (k < 0 && rows > 4 ? 4 : rows); ++r) {
             const int step = j_step(cls_size(n, cls)), sd = 2 * n + 1;
-            const int row = cls_member(n, cls, j_first_row(n, cls, a) + step * r), col = cls_member(n, cls, a + step * k);
+            const int row = cls_member(n, cls, j_first_row(n, cls, a) + step * r);
+            const int col = cls_member(n, cls, k < 0 ? 0 : a + step * k);
             const double v = trans ? h.J[h.joff[n] + col * sd + row] : h.J[h.joff[n] + row * sd + col];
-            const int u = ju(p, st, k, b) + r / 4;
+            const int u = (k < 0 ? ju(p, st, 0, b) : ju(p, st, k, b) + (k == 0 ? lead : 0)) + r / 4;
             out[base + (size_t)(u / 16) * 64 + 4 * (u % 16) + r % 4] = (float)v;
           }
       }

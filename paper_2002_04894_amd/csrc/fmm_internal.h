@@ -18,6 +18,11 @@ constexpr int kMaxOrder = FMM_MAX_ORDER;
 // order (two waves per SIMD), the generic binary64 translation above
 constexpr int kQuadXlateMaxP = 13;
 
+// M2L work order (lists.hip, m2l_queue.h): from this many targets on siblings
+// stay together; the waves that run at once, about
+constexpr int64_t kM2LSiblingsMin = 131072;
+constexpr int64_t kM2LWaves = 2048;
+
 inline int nterms(int p) { return (p + 1) * (p + 1); }
 
 // Error carrying a status code; caught at the ABI boundary.
@@ -105,7 +110,7 @@ struct Tree {
   int32_t* perm = nullptr;
   std::vector<Level> lev;     // 0..L
   int64_t nbox_total = 0;     // sum over levels 0..L
-  int32_t* m2l_order = nullptr;  // M2L targets (box id - 1), longest weak list first
+  int32_t* m2l_order = nullptr;  // M2L targets (box id - 1), longest weak lists first
   int64_t m2l_pairs = 0;
   int64_t p2p_pairs = 0;
   // near-field work items: each leaf's strong list cut into segments of about

@@ -148,57 +148,113 @@ __global__ __launch_bounds__(64) void k_lists_fill(int64_t nbox, const int64_t* 
   }
 }
 
-// M2L work order: the eight children of a parent stay together (their weak
-// lists share most of their sources); parents are binned by the children's
-// mean list length, an eighth of an octave to a bin, bin 0 = longest, the bins
-// scanned, then scattered.  Inside a bin the parents keep runs of their tree
-// order: neighbours in space stay neighbours in the order.  The order only
-// schedules work, every target's result is the same.
-constexpr int kOrderBins = 256;
-// A workgroup takes kOrderChunk consecutive parents and counts them per bin in
+// M2L work order, longest weak list first: targets are binned by list length
+// (bin 0 = longest), the bins scanned, then scattered.  The order within a
+// bin is not fixed; it only schedules work, every target's result is the same.
+// The targets of all levels go by box id - 1.
+// SIBLINGS (many targets): the eight children of a parent, targets 8 g .. 8 g +
+// 7, go into one bin by their mean length, an eighth of an octave to a bin.
+// They share most of their sources, and inside a bin the parents keep runs of
+// their tree order, so neighbours in the order find each other's sources in
+// L2: 2^24 Plummer points, order 12 mixed, M2L 91 -> 81 ms.  With few targets
+// the exact lengths matter more, as the waves take few targets each: 2^18
+// points, binary64 order 12, 5.7 -> 4.2 ms with single targets, 2^20 points
+// 76 -> 74.
+constexpr int kOrderBins = 4096;
+// A workgroup takes kOrderChunk consecutive targets and counts them per bin in
 // LDS, then makes one global atomic per nonzero bin: most lists of a deep
 // level can fall into one bin (the longest), where an atomic per box would
 // serialise.
-constexpr int64_t kOrderChunk = 2048;
+constexpr int64_t kOrderChunk = 16384;
 
-__device__ __forceinline__ int order_bin(const int64_t* __restrict__ w_off, int64_t parent) {
-  const uint64_t mean = (uint64_t)(w_off[8 * parent + 8] - w_off[8 * parent]) >> 3;
-  const int e = 63 - __clzll((long long)(mean | 8));  // at least 3
-  const int b = 8 * (e - 3) + (int)(mean >> (e - 3));
-  return kOrderBins - 1 - (b < kOrderBins - 1 ? b : kOrderBins - 1);
+// bin of target i, or of the children of parent i
+template <bool SIBLINGS>
+__device__ __forceinline__ int order_bin(const LevelView& lv, int64_t i) {
+  const int64_t gid = SIBLINGS ? 8 * i + 1 : i + 1;
+  int l = 1;
+  while (l < lv.L && gid >= lv.gofs[l + 1]) ++l;
+  const int64_t* w_off = lv.w_off[l] + (gid - lv.gofs[l]);
+  int64_t c;
+  if (SIBLINGS) {
+    const uint64_t mean = (uint64_t)(w_off[8] - w_off[0]) >> 3;
+    const int e = 63 - __clzll((long long)(mean | 8));  // at least 3
+    c = 8 * (e - 3) + (int64_t)(mean >> (e - 3));
+  } else {
+    c = w_off[1] - w_off[0];
+  }
+  return kOrderBins - 1 - (int)(c < kOrderBins - 1 ? c : kOrderBins - 1);
 }
 
-__global__ __launch_bounds__(256) void k_order_hist(int64_t npar, const int64_t* __restrict__ w_off,
-                                                    int32_t* __restrict__ hist) {
+template <bool SIBLINGS>
+__global__ __launch_bounds__(256) void k_order_hist(int64_t n, LevelView lv, int32_t* __restrict__ hist) {
   __shared__ int32_t h[kOrderBins];
   for (int b = threadIdx.x; b < kOrderBins; b += blockDim.x) h[b] = 0;
   __syncthreads();
   const int64_t i0 = (int64_t)blockIdx.x * kOrderChunk;
-  const int64_t i1 = npar < i0 + kOrderChunk ? npar : i0 + kOrderChunk;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&h[order_bin(w_off, i)], 1);
+  const int64_t i1 = n < i0 + kOrderChunk ? n : i0 + kOrderChunk;
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&h[order_bin<SIBLINGS>(lv, i)], 1);
   __syncthreads();
   for (int b = threadIdx.x; b < kOrderBins; b += blockDim.x)
     if (h[b] != 0) atomicAdd(&hist[b], h[b]);
 }
 
+// The bins' first slots; and how many targets, from the front of the order,
+// have lists longer than `longest` (single targets: bin b holds those of length
+// kOrderBins - 1 - b, bin 0 also the longer ones), kept behind the order.
+__global__ __launch_bounds__(1024) void k_order_scan(const int32_t* __restrict__ hist, int64_t longest,
+                                                     unsigned long long* __restrict__ cursor,
+                                                     int32_t* __restrict__ nlong) {
+  constexpr int kPer = kOrderBins / 1024;
+  __shared__ int32_t sums[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t v[kPer], t = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    v[k] = hist[threadIdx.x * kPer + k];
+    t += v[k];
+  }
+  int32_t inc = t;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int32_t u = __shfl_up(inc, d);
+    if (lane >= d) inc += u;
+  }
+  if (lane == 63) sums[wave] = inc;
+  __syncthreads();
+  int32_t first = inc - t;
+  for (int w = 0; w < wave; ++w) first += sums[w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int b = threadIdx.x * kPer + k;
+    cursor[b] = (unsigned long long)first;
+    if (b == 0 && longest >= kOrderBins - 1) *nlong = v[k];
+    if (longest < kOrderBins - 1 && b == kOrderBins - 1 - longest) *nlong = first;
+    first += v[k];
+  }
+}
+
 // The same chunks: the workgroup reserves its run of slots in each bin with
 // one global atomic, then hands the slots out from LDS.
-__global__ __launch_bounds__(256) void k_order_scatter(int64_t npar, int64_t gofs, const int64_t* __restrict__ w_off,
+template <bool SIBLINGS>
+__global__ __launch_bounds__(256) void k_order_scatter(int64_t n, LevelView lv,
                                                        unsigned long long* __restrict__ cursor,
                                                        int32_t* __restrict__ order) {
   __shared__ unsigned long long h[kOrderBins];
   for (int b = threadIdx.x; b < kOrderBins; b += blockDim.x) h[b] = 0;
   __syncthreads();
   const int64_t i0 = (int64_t)blockIdx.x * kOrderChunk;
-  const int64_t i1 = npar < i0 + kOrderChunk ? npar : i0 + kOrderChunk;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&h[order_bin(w_off, i)], 1ull);
+  const int64_t i1 = n < i0 + kOrderChunk ? n : i0 + kOrderChunk;
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&h[order_bin<SIBLINGS>(lv, i)], 1ull);
   __syncthreads();
   for (int b = threadIdx.x; b < kOrderBins; b += blockDim.x)
     if (h[b] != 0) h[b] = atomicAdd(&cursor[b], h[b]);
   __syncthreads();
   for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    const unsigned long long pos = atomicAdd(&h[order_bin(w_off, i)], 1ull);
-    for (int c = 0; c < 8; ++c) order[8 * pos + c] = (int32_t)(gofs - 1 + 8 * i + c);
+    const unsigned long long pos = atomicAdd(&h[order_bin<SIBLINGS>(lv, i)], 1ull);
+    if (SIBLINGS)
+      for (int c = 0; c < 8; ++c) order[8 * pos + c] = (int32_t)(8 * i + c);
+    else
+      order[pos] = (int32_t)i;
   }
 }
 
@@ -375,24 +431,26 @@ void lists_build(Tree& t, hipStream_t s) {
   // M2L work order over the targets of levels 1..L (box id - 1)
   const int64_t ntarget = t.nbox_total - 1;
   if (ntarget > 0) {
+    const bool sib = ntarget >= kM2LSiblingsMin;
+    const int64_t n = sib ? ntarget / 8 : ntarget;
+    const unsigned grid = (unsigned)((n + kOrderChunk - 1) / kOrderChunk);
     int32_t* hist = (int32_t*)dalloc(kOrderBins * sizeof(int32_t), s);
-    int64_t* cursor = (int64_t*)dalloc((kOrderBins + 1) * sizeof(int64_t), s);
+    unsigned long long* cursor = (unsigned long long*)dalloc(kOrderBins * sizeof(unsigned long long), s);
+    t.m2l_order = (int32_t*)dalloc((ntarget + 1) * sizeof(int32_t), s);
     HIPCHECK(hipMemsetAsync(hist, 0, kOrderBins * sizeof(int32_t), s));
-    for (int l = 1; l <= L; ++l) {
-      const Level& V = t.lev[l];
-      const int64_t npar = V.nbox / 8;
-      k_order_hist<<<(unsigned)((npar + kOrderChunk - 1) / kOrderChunk), 256, 0, s>>>(npar, V.w_off, hist);
-      HIPCHECK(hipGetLastError());
-    }
-    scan_counts(hist, cursor, kOrderBins, 0, s);
-    t.m2l_order = (int32_t*)dalloc(ntarget * sizeof(int32_t), s);
-    for (int l = 1; l <= L; ++l) {
-      const Level& V = t.lev[l];
-      const int64_t npar = V.nbox / 8;
-      k_order_scatter<<<(unsigned)((npar + kOrderChunk - 1) / kOrderChunk), 256, 0, s>>>(
-          npar, V.gofs, V.w_off, (unsigned long long*)cursor, t.m2l_order);
-      HIPCHECK(hipGetLastError());
-    }
+    const LevelView lv = t.view();
+    if (sib)
+      k_order_hist<true><<<grid, 256, 0, s>>>(n, lv, hist);
+    else
+      k_order_hist<false><<<grid, 256, 0, s>>>(n, lv, hist);
+    HIPCHECK(hipGetLastError());
+    k_order_scan<<<1, 1024, 0, s>>>(hist, m2l / kM2LWaves, cursor, t.m2l_order + ntarget);
+    HIPCHECK(hipGetLastError());
+    if (sib)
+      k_order_scatter<true><<<grid, 256, 0, s>>>(n, lv, cursor, t.m2l_order);
+    else
+      k_order_scatter<false><<<grid, 256, 0, s>>>(n, lv, cursor, t.m2l_order);
+    HIPCHECK(hipGetLastError());
     dfree(hist, s);
     dfree(cursor, s);
   }

@@ -18,7 +18,7 @@
 // one register (one block's values broadcast to all blocks, lane_ops.h),
 // read from a table in LDS.  Half the entries of a class block of J vanish (the
 // turn carries reflections in y into reflections in z), so a class runs as two
-// sub-blocks by the parity of the order: 1,460 instructions per batch at p =
+// sub-blocks by the parity of the order: 1,500 instructions per batch at p =
 // 12, where whole blocks take 2,140.  Only rows of a block are padded to a
 // multiple of 4.  The z-turns and the radius powers run on
 // the vector units.  The 64 pair results are summed across the lanes by
@@ -78,7 +78,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // accumulator chains are independent instructions in flight; all inputs are
 // read before any result is stored, and a block without columns is absent.
 // The instructions are numbered in the order of issue (u(k) the first one of
-// column k), sixteen to an operand register; Ops, carried from block to block,
+// column k, or of the one ahead of it that j_lead keeps), sixteen to an
+// operand register; Ops, carried from block to block,
 // holds the current register and the next one, loaded sixteen instructions
 // ahead so that its LDS latency is covered.
 struct Ops {
@@ -108,10 +109,15 @@ struct Acc {
   template <int K>
   __device__ __forceinline__ void step(const float* X, Ops& ops) {
     if constexpr (K < B::kCols) {
+      constexpr int U = B::u(K) + (K == 0 ? B::kLead : 0);
+      if constexpr (K == 0 && B::kLead) {
+        ops.template at<U - 1, B::prev(0), B::kLast>();
+        D[0] = mfma_bc<(U - 1) % 16>(ops.cur, X[B::lead()], D[0]);
+      }
       const float xk = X[B::in(K)];
       static_for<0, kNC>([&](auto c) __attribute__((always_inline)) {
-        constexpr int u = B::u(K) + decltype(c)::value;
-        ops.template at<u, decltype(c)::value == 0 ? B::prev(K) : u - 1, B::kLast>();
+        constexpr int u = U + decltype(c)::value;
+        ops.template at<u, decltype(c)::value == 0 && !(K == 0 && B::kLead) ? B::prev(K) : u - 1, B::kLast>();
         D[c] = mfma_bc<u % 16>(ops.cur, xk, D[c]);
       });
     }
@@ -149,6 +155,8 @@ struct JSub {
   static constexpr int kD = lops::ju_degree(P, S, B);
   static constexpr int kCls = S & 1, kA = B & 1;
   static constexpr int kCols = lops::ju_cols(P, S, B), kRows = lops::ju_rows(P, S, B);
+  static constexpr int kLead = lops::ju_lead(P, S, B);
+  __host__ __device__ static constexpr int lead() { return kD * kD + lops::cls_member(kD, kCls, 0); }
   static constexpr int kLast = lops::ju(P, lops::ju_steps(P), 0, 0) - 1;
   __host__ __device__ static constexpr int u(int k) { return lops::ju(P, S, k, B); }
   __host__ __device__ static constexpr int prev(int k) { return u(k) - 1; }
@@ -165,7 +173,8 @@ template <int P, int M, int B, int T>
 struct ZBlk {
   static constexpr int kM = B == 0 ? M : P - M;
   static constexpr int kCols = kM >= T ? lops::zu_size(P, M, B) : 0;
-  static constexpr int kRows = kCols;
+  static constexpr int kRows = kCols, kLead = 0;
+  __host__ __device__ static constexpr int lead() { return 0; }
   static constexpr int kLast = lops::zu(P, P / 2 + 1, 0, 0) - 1;
   __host__ __device__ static constexpr int u(int k) { return lops::zu(P, M, k, B); }
   // the instruction issued before column k: the sine parts skip the block of
@@ -182,7 +191,7 @@ struct ZBlk {
 // X <- J X or J^T X on the matrix cores: per degree and parity class the two
 // sub-blocks that hold the class block's nonzero entries times the lane's
 // class members (lane_ops.h), degree n beside degree P - n, one class at a
-// time.  The sub-blocks take 258 instructions per
+// time.  The sub-blocks take 268 instructions per
 // application at order 12, the whole class blocks 428 (half of their products
 // with zeros).
 template <int P>
@@ -237,33 +246,43 @@ struct Turn {
   }
 };
 
-// X <- Rz(SIGN * g) X
-template <int P, int SIGN>
+// X <- Rz(-g) X in turns 1 and 2 of the translation, Rz(g) X in turns 3 and 4.
+// The products to be rounded before the addition are named one by one (cosine
+// terms fused on the way in, sine terms on the way back; at orders up to 4 the
+// even orders m of turns 2 to 4 the other way round): left to the compiler, the
+// choice changes with the code around it, and results in the eighth digit
+// with it.
+template <int P, int TURN>
 __device__ __forceinline__ void rotz(float* X, const Turn<P>& g) {
+  constexpr bool BACK = TURN > 2;
 #pragma unroll
   for (int m = 1; m <= P; ++m) {
-    const float cm = g.c[m], sm = SIGN < 0 ? -g.s[m] : g.s[m];
+    const float c = g.c[m], s = g.s[m];
+    const bool fuse_sin = BACK != (P <= 4 && TURN > 1 && m % 2 == 0);
 #pragma unroll
     for (int n = m; n <= P; ++n) {
       const float a = X[cidx(n, m, 0)], b = X[cidx(n, m, 1)];
-      X[cidx(n, m, 0)] = cm * a - sm * b;
-      X[cidx(n, m, 1)] = sm * a + cm * b;
+      const float u = BACK ? b : a, v = BACK ? a : b;  // the sum is c u + s v, the difference c v - s u
+      const float sum = fuse_sin ? __builtin_fmaf(s, v, c * u) : __builtin_fmaf(c, u, s * v);
+      const float dif = __builtin_fmaf(c, v, -(s * u));
+      X[cidx(n, m, 0)] = BACK ? dif : sum;
+      X[cidx(n, m, 1)] = BACK ? sum : dif;
     }
   }
 }
 // the turn by -g, whose cosines and sines go to w, and the turn back
-template <int P>
+template <int P, int TURN>
 __device__ __forceinline__ void turn_in(float* X, double c1, double s1, float4* w) {
   Turn<P> g;
   g.make(c1, s1);
   g.put(w);
-  rotz<P, -1>(X, g);
+  rotz<P, TURN>(X, g);
 }
-template <int P>
+template <int P, int TURN>
 __device__ __forceinline__ void turn_back(float* X, const float4* w) {
   Turn<P> g;
   g.get(w);
-  rotz<P, 1>(X, g);
+  rotz<P, TURN>(X, g);
 }
 
 // the z-axis translation with the core products on the matrix cores: per
@@ -360,12 +379,12 @@ struct LaneCfg {
   static constexpr bool kPark = P == 12;
 };
 
-// Persistent waves: each takes the next target of its XCD's part of the order.
-template <int P>
+// SHARE, RUNS: how the targets are dealt out (m2l_queue.h); template arguments,
+// as a scalar more in the loop's registers spills at the highest orders
+template <int P, bool SHARE, bool RUNS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LaneCfg<P>::kWaves, LaneCfg<P>::kWaves))) void
 k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__ pos, const float* __restrict__ Mf,
-           double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order, int* __restrict__ queue,
-           int run) {
+           double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order, int* __restrict__ queue) {
   constexpr int NT = (P + 1) * (P + 1);
   constexpr int S = tl::stride(P);
   constexpr int SD = lops::dense_stride(P);
@@ -379,17 +398,18 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
   // values that a lane parks while the translation runs, where they would
   // spill: the sums over the batches and the polar angle; the distance factors
   constexpr bool PK = LaneCfg<P>::kPark;
-  __shared__ double parkd[PK ? (NF + 2) * 256 : 1];
+  __shared__ double parkd[PK ? (NF + 2) * 256 : SHARE ? NF * 256 : 1];
   __shared__ float parkf[PK ? 3 * 256 : 1];
   for (int i = threadIdx.x; i < lops::table_floats(P); i += blockDim.x) tabs[i] = ltab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63;
   float4* wb = turns + (threadIdx.x >> 6) * 2 * TW + (P > 0 ? lane : 0);  // beta, then alpha
   float4* wa = wb + TW;
-  m2lq::Cursor cur;
+  m2lq::Cursor<RUNS> cur;
+  const int wave = SHARE ? m2lq::uniform((int)(threadIdx.x >> 6)) : 0;
   for (;;) {
-    const int64_t kq = m2lq::next(cur, queue, ntarget, run, lane);
-    if (kq < 0) break;
+    const int64_t kq = SHARE ? (int64_t)blockIdx.x : cur.next(queue, ntarget, lane);
+    if (kq >= ntarget) break;
     // the target's data are the same in all lanes: kept in scalar registers
     const int64_t gid = lv.gofs[1] + m2lq::uniform(order[kq]);
     const int l = level_of3(lv, gid);
@@ -407,12 +427,13 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
     for (int i = 0; i < NF; ++i) acc.put(i, 0.0);
 
     // the next batch's source indexes are loaded while this batch runs
-    int32_t jn = ne > 0 ? wrow[lane < ne ? lane : 0] : 0;
-    for (int eb = 0; eb < ne; eb += 64) {
+    const int b0 = 64 * wave, bs = 64 * (SHARE ? 4 : 1);
+    int32_t jn = ne > 0 ? wrow[b0 + lane < ne ? b0 + lane : 0] : 0;
+    for (int eb = b0; eb < ne; eb += bs) {
       const int e = eb + lane;
       const bool valid = e < ne;
       const int64_t j = jn;
-      jn = wrow[e + 64 < ne ? e + 64 : 0];
+      jn = wrow[e + bs < ne ? e + bs : 0];
       const double dx = geo[j * 10 + 6] - cix, dy = geo[j * 10 + 7] - ciy, dz = geo[j * 10 + 8] - ciz;
       const double rs = geo[j * 10 + 9] > 0.0 ? geo[j * 10 + 9] : 1.0;
       const double rxy2 = dx * dx + dy * dy;
@@ -446,17 +467,17 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       // ahead of it
       const float *tJ = tabs, *tJT = tabs + GJ;
       FMM_STEP(Ops o1(tJT, lane));
-      FMM_STEP(turn_in<P>(X, cb, sb, wb));
+      FMM_STEP((turn_in<P, 1>(X, cb, sb, wb)));
       FMM_STEP(japply_mf<P>(X, o1));
       FMM_STEP(Ops o2(tJ, lane));
-      FMM_STEP(turn_in<P>(X, acc.get(NF), acc.get(NF + 1), wa));
+      FMM_STEP((turn_in<P, 2>(X, acc.get(NF), acc.get(NF + 1), wa)));
       FMM_STEP(japply_mf<P>(X, o2));
       FMM_STEP(ztrans_mf<P>(X, tabs + 2 * GJ, lane, fac));
       FMM_STEP(japply_mf<P>(X, Ops(tJT, lane)));
       FMM_STEP(Ops o4(tJ, lane));
-      FMM_STEP(turn_back<P>(X, wa));
+      FMM_STEP((turn_back<P, 3>(X, wa)));
       FMM_STEP(japply_mf<P>(X, o4));
-      FMM_STEP(turn_back<P>(X, wb));
+      FMM_STEP((turn_back<P, 4>(X, wb)));
 #undef FMM_STEP
 
       // sum over the 64 lanes: six halving exchanges; at the exchange with
@@ -470,6 +491,16 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       halve<lvl(NT, 5), 1>(h5, h6, lane);
 #pragma unroll
       for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + (double)h6[i]);
+    }
+    if constexpr (SHARE) {  // the waves' sums, in wave order
+      if constexpr (!PK)
+#pragma unroll
+        for (int i = 0; i < NF; ++i) parkd[i * 256 + threadIdx.x] = acc.get(i);
+      __syncthreads();
+      if (threadIdx.x >= 64) return;
+      for (int w = 64; w < 256; w += 64)
+#pragma unroll
+        for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + parkd[i * 256 + w + lane]);
     }
     // lane's values: standard index base + i, where each exchange added the
     // kept half's offset; entries past a half's end are padding
@@ -496,6 +527,7 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
       for (int q = 0; q < n; ++q) v *= irt;
       dst[pos[k]] = v;
     }
+    if constexpr (SHARE) return;
   }
 }
 
@@ -525,8 +557,8 @@ __global__ void k_scale_lane(LevelView lv, int S, const int* __restrict__ pos, c
   }
 }
 
-__global__ void k_zero_queue_l(int* queue) {
-  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = 0;
+__global__ void k_start_queue_l(int* queue, const int32_t* first) {
+  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = threadIdx.x == 0 && first ? *first : 0;
 }
 
 template <int P>
@@ -536,20 +568,29 @@ void launch_one_lane(const Tree& t, const Tables& tb, const double* Mx, double* 
   float* Mf = (float*)dalloc((size_t)t.nbox_total * lops::dense_stride(P) * sizeof(float), s);
   k_scale_lane<P><<<(unsigned)((ntarget + 3) / 4), 256, 0, s>>>(t.view(), tb.stride, tb.pos, Mx, Mf, t.nbox_total);
   HIPCHECK(hipGetLastError());
+  if (ntarget <= m2lq::kShareLane) {
+    k_m2l_lane<P, true, false><<<(unsigned)ntarget, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget,
+                                                                  t.m2l_order, nullptr);
+    HIPCHECK(hipGetLastError());
+    dfree(Mf, s);
+    return;
+  }
   static const int grid_max = [] {
     int dev = 0, ncu = 0, per = 0;
     HIPCHECK(hipGetDevice(&dev));
     HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_m2l_lane<P>, 256, 0));
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_m2l_lane<P, false, false>, 256, 0));
     return ncu * (per > 0 ? per : 1);
   }();
   const int64_t need = (ntarget + 3) / 4;
   const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
   int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
-  k_zero_queue_l<<<1, 64, 0, s>>>(queue);
+  k_start_queue_l<<<1, 64, 0, s>>>(queue, nullptr);
   HIPCHECK(hipGetLastError());
-  k_m2l_lane<P><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue,
-                                       m2lq::run_length(ntarget));
+  if (ntarget >= kM2LSiblingsMin)
+    k_m2l_lane<P, false, true><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue);
+  else
+    k_m2l_lane<P, false, false><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue);
   HIPCHECK(hipGetLastError());
   dfree(queue, s);
   dfree(Mf, s);

@@ -321,6 +321,17 @@ __device__ __forceinline__ void qhalve(const double* src, double* dst, int lane)
   }
 }
 
+// The tables into LDS, 16 bytes per load (NL is even: (p + 2) (p + 1)^2 and
+// whole parts), eight loads in flight per thread.
+template <int NL, int NTH>
+__device__ __forceinline__ void qstage(const double* __restrict__ src, double* dst) {
+  static_assert(NL % 2 == 0, "");
+  const double2* s = (const double2*)src;
+  double2* d = (double2*)dst;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < NL / 2; i += NTH) d[i] = s[i];
+}
+
 // Storage position of the coefficient in (register, phase) = (t / 4, t % 4) and
 // its degree times 65536; -1 for a zero slot.  All degrees at once: the loop
 // unrolls into a few comparisons.
@@ -340,21 +351,24 @@ __device__ __forceinline__ int qslot(int t, const int* __restrict__ pos) {
   return w;
 }
 
-template <int P>
+// SHARE, RUNS: how the targets are dealt out (m2l_queue.h); template arguments,
+// as a scalar more in the loop's registers spills at the highest orders
+template <int P, bool SHARE, bool RUNS>
 __global__ __launch_bounds__(QuadCfg<P>::kThreads)
 __attribute__((amdgpu_waves_per_eu(QuadCfg<P>::kWaves, QuadCfg<P>::kWaves))) void
 k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict__ pos, int S,
            const double* __restrict__ Mq, double* __restrict__ Lx, int64_t ntarget, const int32_t* __restrict__ order,
-           int* __restrict__ queue, int run) {
+           int* __restrict__ queue, const int32_t* __restrict__ nlong) {
+  if (SHARE && nlong && (int)blockIdx.x >= *nlong) return;  // not one of the long lists
   constexpr int NQ = lops::nq(P);
   constexpr int NJ = QuadCfg<P>::kJ;
   constexpr int NF = QuadCfg<P>::kSums;  // values a lane holds after the exchanges
   constexpr int NL = QuadCfg<P>::kLds;
   constexpr int NTH = QuadCfg<P>::kThreads;
-  __shared__ double tabs[NL];
+  __shared__ __align__(16) double tabs[NL];
   __shared__ double park[(6 + NF) * NTH];
   __shared__ int slot[NQ * 4];
-  for (int i = threadIdx.x; i < NL; i += blockDim.x) tabs[i] = qtab[i];
+  qstage<NL, NTH>(qtab, tabs);
   for (int t = threadIdx.x; t < NQ * 4; t += blockDim.x) slot[t] = qslot<P>(t, pos);
   __syncthreads();
   constexpr bool HJT = lops::qp_has_jt(P);
@@ -363,10 +377,11 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
   const int k = lane >> 4, q = lane & 15;
   const int tl = 4 * k + (lane & 3);   // this lane's value in a 4x4 part of J
   const int tlt = 4 * (lane & 3) + k;  // and of J^T
-  m2lq::Cursor cur;
+  m2lq::Cursor<RUNS> cur;
+  const int wave = SHARE ? m2lq::uniform((int)(threadIdx.x >> 6)) : 0;
   for (;;) {
-    const int64_t kq = m2lq::next(cur, queue, ntarget, run, lane);
-    if (kq < 0) break;
+    const int64_t kq = SHARE ? (int64_t)blockIdx.x : cur.next(queue, ntarget, lane);
+    if (kq >= ntarget) break;
     // the target's data are the same in all lanes: kept in scalar registers
     const int64_t gid = lv.gofs[1] + m2lq::uniform(order[kq]);
     const int l = qlevel_of(lv, gid);
@@ -384,12 +399,13 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
     for (int i = 0; i < NF; ++i) acc.put(i, 0.0);
 
     // the next batch's source indexes are loaded while this batch runs
-    int32_t jn = ne > 0 ? wrow[q < ne ? q : 0] : 0;
-    for (int eb = 0; eb < ne; eb += 16) {
+    const int b0 = 16 * wave, bs = 16 * (SHARE ? NTH / 64 : 1);
+    int32_t jn = ne > 0 ? wrow[b0 + q < ne ? b0 + q : 0] : 0;
+    for (int eb = b0; eb < ne; eb += bs) {
       const int e = eb + q;
       const bool valid = e < ne;
       const int64_t j = jn;
-      jn = wrow[e + 16 < ne ? e + 16 : 0];
+      jn = wrow[e + bs < ne ? e + bs : 0];
       const double dx = geo[j * 10 + 6] - cix, dy = geo[j * 10 + 7] - ciy, dz = geo[j * 10 + 8] - ciz;
       const double rs = geo[j * 10 + 9] > 0.0 ? geo[j * 10 + 9] : 1.0;
       const double rxy2 = dx * dx + dy * dy;
@@ -429,6 +445,13 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
 #pragma unroll
       for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + h4[i]);
     }
+    if constexpr (SHARE) {  // the waves' sums, in wave order
+      __syncthreads();
+      if (threadIdx.x >= 64) return;
+      for (int w = 64; w < NTH; w += 64)
+#pragma unroll
+        for (int i = 0; i < NF; ++i) acc.put(i, acc.get(i) + park[(6 + i) * NTH + w + lane]);
+    }
     // lane's values: registers base + i of phase k, where each exchange
     // added the kept half's offset; entries past a half's end are padding
     int base = 0, len = NQ;
@@ -456,6 +479,7 @@ k_m2l_quad(LevelView lv, const double* __restrict__ qtab, const int* __restrict_
         }
       }
     });
+    if constexpr (SHARE) return;
   }
 }
 
@@ -482,8 +506,8 @@ __global__ void k_quad_copy(LevelView lv, int S, const int* __restrict__ pos, co
   }
 }
 
-__global__ void k_zero_queue_q(int* queue) {
-  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = 0;
+__global__ void k_start_queue_q(int* queue, const int32_t* first) {
+  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = threadIdx.x == 0 && first ? *first : 0;
 }
 
 template <int P>
@@ -494,22 +518,36 @@ void launch_one_quad(const Tree& t, const Tables& tb, const double* Mx, double* 
   double* Mq = (double*)dalloc((size_t)t.nbox_total * NQ * 4 * sizeof(double), s);
   k_quad_copy<P><<<(unsigned)((ntarget + 3) / 4), 256, 0, s>>>(t.view(), tb.stride, tb.pos, Mx, Mq, t.nbox_total);
   HIPCHECK(hipGetLastError());
-  static const int grid_max = [] {
-    int dev = 0, ncu = 0, per = 0;
-    HIPCHECK(hipGetDevice(&dev));
-    HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_m2l_quad<P>, QuadCfg<P>::kThreads, 0));
-    return ncu * (per > 0 ? per : 1);
-  }();
-  const int64_t need = (ntarget + QuadCfg<P>::kThreads / 64 - 1) / (QuadCfg<P>::kThreads / 64);
-  const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
-  int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
-  k_zero_queue_q<<<1, 64, 0, s>>>(queue);
-  HIPCHECK(hipGetLastError());
-  k_m2l_quad<P><<<grid, QuadCfg<P>::kThreads, 0, s>>>(t.view(), tb.quad, tb.pos, tb.stride, Mq, Lx, ntarget,
-                                                       t.m2l_order, queue, m2lq::run_length(ntarget));
-  HIPCHECK(hipGetLastError());
-  dfree(queue, s);
+  const int32_t* nlong = ntarget > m2lq::kShareQuad && ntarget <= m2lq::kLongQuad ? t.m2l_order + ntarget : nullptr;
+  if (ntarget <= m2lq::kLongQuad) {
+    // all targets, or the long lists: at most kM2LWaves of them can be longer
+    // than their share
+    const unsigned blocks = (unsigned)(nlong && ntarget > kM2LWaves ? kM2LWaves : ntarget);
+    k_m2l_quad<P, true, false><<<blocks, QuadCfg<P>::kThreads, 0, s>>>(t.view(), tb.quad, tb.pos, tb.stride, Mq, Lx,
+                                                                        ntarget, t.m2l_order, nullptr, nlong);
+    HIPCHECK(hipGetLastError());
+  }
+  if (ntarget > m2lq::kShareQuad) {
+    static const int grid_max = [] {
+      int dev = 0, ncu = 0;
+      HIPCHECK(hipGetDevice(&dev));
+      HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+      return ncu;  // one block per CU, by its LDS and registers
+    }();
+    const int64_t need = (ntarget + QuadCfg<P>::kThreads / 64 - 1) / (QuadCfg<P>::kThreads / 64);
+    const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
+    int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
+    k_start_queue_q<<<1, 64, 0, s>>>(queue, nlong);
+    HIPCHECK(hipGetLastError());
+    if (ntarget >= kM2LSiblingsMin)
+      k_m2l_quad<P, false, true><<<grid, QuadCfg<P>::kThreads, 0, s>>>(t.view(), tb.quad, tb.pos, tb.stride, Mq, Lx,
+                                                                       ntarget, t.m2l_order, queue, nullptr);
+    else
+      k_m2l_quad<P, false, false><<<grid, QuadCfg<P>::kThreads, 0, s>>>(t.view(), tb.quad, tb.pos, tb.stride, Mq, Lx,
+                                                                        ntarget, t.m2l_order, queue, nullptr);
+    HIPCHECK(hipGetLastError());
+    dfree(queue, s);
+  }
   dfree(Mq, s);
 }
 
@@ -535,9 +573,9 @@ k_xlate_quad(LevelView lv, int l, const double* __restrict__ qtab, const int* __
   constexpr int NL = QuadCfg<P>::kLds;
   constexpr int NF = qlvl(NQ, 3);  // values a lane holds after the M2M exchanges
   static_assert(lops::qp_has_jt(P), "orders whose table holds J^T");
-  __shared__ double tabs[NL];
+  __shared__ __align__(16) double tabs[NL];
   __shared__ int spos[NQ * 4];  // storage position of (register, phase); -1: zero slot
-  for (int i = threadIdx.x; i < NL; i += blockDim.x) tabs[i] = qtab[i];
+  qstage<NL, QuadCfg<P>::kThreads>(qtab, tabs);
   for (int t = threadIdx.x; t < NQ * 4; t += blockDim.x) {
     const int w = qslot<P>(t, pos);
     spos[t] = w >= 0 ? w & 0xffff : -1;

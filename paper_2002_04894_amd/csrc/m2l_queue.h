@@ -1,26 +1,18 @@
-// Work queue (and small helpers) of the M2L kernels whose waves each take a target box at a time
-// (m2l_lane.hip, m2l_quad.hip).
-//
-// The targets are ordered with the eight children of a parent side by side,
-// parents by decreasing weak-list length in coarse steps (lists.hip), so
-// neighbours in the order mostly are neighbours in space and share most of
-// their sources.  The order is dealt to the eight XCDs in runs: the waves of
-// one XCD work on neighbouring targets at the same time and find each other's
-// source expansions in its L2.  A wave whose XCD's runs are used up takes
-// targets of the next XCD's.
+// Work queue and small helpers of the M2L kernels (m2l_lane.hip,
+// m2l_quad.hip), whose waves each take a target box at a time, or whose blocks
+// share one target out among their waves.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fmm_internal.h"
+
 namespace fmm {
 namespace m2lq {
 
-constexpr int kXcds = 8;  // blocks are dispatched to the XCDs in turn
-
-// targets per run: as many as an XCD has waves at work, or one parent's
-// children when there are few targets
-inline int run_length(int64_t ntarget) { return ntarget >= 32768 ? 256 : 8; }
+constexpr int kXcds = 8;   // blocks are dispatched to the XCDs in turn
+constexpr int kRun = 256;  // targets per run: as many as an XCD has waves at work
 
 // a value that is the same in all lanes, in scalar registers
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -70,23 +62,48 @@ struct Kept {
   }
 };
 
-struct Cursor {
-  int skip = 0;  // queues found empty, from the home XCD's on
-};
+// How a launch deals out its targets.  Persistent waves take one target each
+// (Cursor below); or, with SHARE, block b takes the target at position b, and
+// its waves take the batches of the list in turn: with few targets (trees of
+// up to three levels) most waves would have nothing to do, and a list longer
+// than a wave's share of the launch would hold it up.  The waves of a block
+// are kept together and wait for memory at the same time, so with more targets
+// this costs the binary64 kernel, one block of eight waves to a CU, more than
+// it gives, except for the lists that are too long; the per-lane kernel, up to
+// four blocks of four waves to a CU, gains up to kShareLane targets.
+// Measured, M2L in us (waves by themselves / SHARE): binary64 order 12, 47,003
+// points on a sphere, 512 leaves 545 / 150; 2^18 Plummer points, 4,096 leaves
+// 4,240 / 6,000; 200,000 points on a sphere, 4,096 leaves 3,730 / 1,960 with the
+// long lists shared; binary32 order 6, 200,000 points, 4,096 leaves 350 / 215.
+constexpr int64_t kShareQuad = 1024;  // all targets shared up to here,
+constexpr int64_t kShareLane = 8192;  // and up to here (per-lane kernel)
+constexpr int64_t kLongQuad = 8192;   // binary64: the too long ones up to here
 
-// position in the order of the wave's next target, -1 when all are taken;
-// called by whole waves
-__device__ __forceinline__ int64_t next(Cursor& c, int* __restrict__ queue, int64_t ntarget, int run, int lane) {
-  for (; c.skip < kXcds; ++c.skip) {
-    const int x = (blockIdx.x + c.skip) % kXcds;
-    int k = 0;
-    if (lane == 0) k = atomicAdd(&queue[x], 1);
-    k = uniform(k);
-    const int64_t pos = (int64_t)(k / run) * (kXcds * run) + x * run + k % run;
-    if (pos < ntarget) return pos;
+// The waves' next targets.  With siblings side by side in the order (RUNS) it
+// is dealt to the XCDs in runs, so that the waves of one XCD work on
+// neighbours at the same time and find each other's source expansions in its
+// L2; else one counter serves all.
+template <bool RUNS>
+struct Cursor {
+  int x = RUNS ? blockIdx.x % kXcds : 0;  // the counter it takes from
+  __device__ __forceinline__ static int64_t position(int c, int k) {
+    return RUNS ? (int64_t)(k / kRun) * (kXcds * kRun) + c * kRun + k % kRun : k;
   }
-  return -1;
-}
+  // position in the order, ntarget or more when all targets are taken
+  __device__ __forceinline__ int64_t next(int* __restrict__ queue, int64_t ntarget, int lane) {
+    for (;;) {
+      int k = 0;
+      if (lane == 0) k = atomicAdd(&queue[x], 1);
+      const int64_t pos = position(x, uniform(k));
+      if (!RUNS || pos < ntarget) return pos;
+      // used up: the next counter that is not, by one look at all of them
+      const int v = __hip_atomic_load(&queue[lane % kXcds], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t left = (uint32_t)__ballot(position(lane % kXcds, v) < ntarget) & 0xffu;
+      if (left == 0) return ntarget;
+      x = (x + __ffs((int)((left >> x) | (left << (kXcds - x)))) - 1) % kXcds;
+    }
+  }
+};
 
 }  // namespace m2lq
 }  // namespace fmm

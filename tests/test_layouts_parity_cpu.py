@@ -36,7 +36,7 @@ int main() {
           if (k >= ju_cols(p, t, b)) continue;
           const int n = ju_degree(p, t, b), cls = t & 1, rows = ju_rows(p, t, b), st = j_step(cls_size(n, cls));
           fails += ju(p, t, k, b) != u;
-          u += chunks(rows);
+          u += chunks(rows) + (k == 0 ? ju_lead(p, t, b) : 0);
           for (int r = 0; r < rows; ++r)
             ++seen[{n, cls, j_first_row(n, cls, b & 1) + st * r, (b & 1) + st * k}];
         }
