@@ -8,10 +8,11 @@
 // (gather form: no atomics, deterministic).  On clustered data the strong
 // lists of a few leaves hold far more sources than the rest, so each list is
 // cut into segments of about kP2PSeg source points (a plan made once per
-// tree); one 64-lane workgroup takes one segment.  A leaf with one segment
+// tree); one workgroup takes one segment.  A leaf with one segment
 // writes its result directly; the segments of a split leaf write partial sums
 // that a second pass adds up in segment order.
 #include <algorithm>
+#include <type_traits>
 
 #include "fmm_internal.h"
 #include "lane_ops.h"
@@ -128,22 +129,28 @@ __global__ void k_sum64(int64_t n, const int64_t* __restrict__ v, unsigned long 
   if ((threadIdx.x & 63) == 0) atomicAdd(acc, x);
 }
 
-// One 64-lane workgroup per segment.  Each lane holds two targets, t and
-// t + TT, and one of R = 64 / TT source streams, so every source read from
-// LDS serves two interactions.  Sources are staged in chunks of up to kP2PBuf
-// points gathered from consecutive entries of the segment: the lanes take the
-// chunk's points in a flat order, so all their loads are in flight together.
-// The targets of leaf b are [tstart[b], tstart[b+1]) of (tx, ty, tz), written
-// to index tperm[.] of the outputs: the leaf's own sources (tstart = start,
-// tx = px, tperm = perm) or the separate targets grouped by leaf.
+// One workgroup of W waves per segment.  A wave's lanes hold T targets each (tl,
+// tl + TT, ...) and one of R source streams, R TT <= 64, so every source read
+// from LDS serves T interactions.  Sources are staged in chunks of up to
+// kP2PBuf points gathered from consecutive entries of the segment: the lanes
+// take the chunk's points in a flat order, so all their loads are in flight
+// together.  The targets of leaf b are [tstart[b], tstart[b+1]) of (tx, ty,
+// tz), written to index tperm[.] of the outputs: the leaf's own sources
+// (tstart = start, tx = px, tperm = perm) or the separate targets grouped by
+// leaf.
+// Binary64: T, TT and R by the number of targets (p2p_split), and the waves take
+// contiguous parts of the segment's entries.
 // Binary32 near field (F32): coordinates are taken relative to the target
 // leaf's cell centre in binary64 and rounded to binary32, so that the
 // differences of nearby points keep binary32 accuracy; 1/r is the hardware
 // binary32 reciprocal square root; each lane sums the interactions of one
 // staged chunk in binary32 and adds the chunk sums into compensated binary32
-// accumulators (Kahan); the results are widened to binary64 before the far
-// field is added.  Two distinct points whose relative coordinates round to
-// the same binary32 values count as coincident (contribute nothing).
+// accumulators (Kahan); the results are widened to binary64 before the far field
+// is added.  The chunks, a lane's share of them and the order of their sums are
+// the same for every W, as they fix the binary32 roundings: the waves take the
+// chunks in turn, and the chunk sums of a round meet in LDS, where every wave
+// adds up some of the accumulators in chunk order.  Two distinct points whose relative coordinates round to the same
+// binary32 values count as coincident (contribute nothing).
 struct Kahan {
   float s = 0.f, c = 0.f;
   __device__ __forceinline__ void add(float v) {
@@ -155,231 +162,399 @@ struct Kahan {
   __device__ __forceinline__ double get() const { return (double)s - (double)c; }
 };
 
+// Orders a wave's LDS accesses around a point (other lanes of the wave read
+// what this lane wrote): the LDS unit executes a wave's instructions in order.
+__device__ __forceinline__ void p2p_wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The near field of one segment: its entries, in LDS as far as they fit
+// (kP2PEntries: the first point of the source leaf, its points), so that a
+// chunk waits for its points only and not for two loads before them.
+constexpr int kP2PEntries = 512;
+constexpr int kP2PSlots = 2;  // binary32: chunks of a wave in a round
+struct P2PSeg {
+  const int32_t* s_idx;  // the segment's first entry
+  const int32_t* start;
+  int ne;                // entries
+  const int32_t* base;   // LDS
+  const int32_t* cnt;
+  __device__ __forceinline__ void entry(int i, int& b, int& n) const {
+    if (i < kP2PEntries) {
+      b = base[i];
+      n = cnt[i];
+    } else {
+      const int j = s_idx[i];
+      b = start[j];
+      n = start[j + 1] - b;
+    }
+  }
+};
+
+// Stages the next chunk of entries [e, e1) (off: points of entry e staged
+// before) into buf, moves (e, off) past it and returns its points; with STAGE
+// false only moves on.
+template <bool F32, bool STAGE, class V>
+__device__ __forceinline__ int p2p_chunk(const P2PSeg& sg, int e1, int& e, int& off, V* buf, int lane,
+                                         const double* __restrict__ px, const double* __restrict__ py,
+                                         const double* __restrict__ pz, const double* __restrict__ qt, double ccx,
+                                         double ccy, double ccz) {
+  // up to 16 entries from e on: lane q < 16 takes entry e + q
+  int base = 0, cnt = 0;
+  if (lane < 16 && e + lane < e1) {
+    sg.entry(e + lane, base, cnt);
+    if (lane == 0) {
+      base += off;
+      cnt -= off;
+    }
+  }
+  int pre = cnt;  // inclusive prefix over lanes 0..15
+#pragma unroll
+  for (int d = 1; d < 16; d <<= 1) {
+    const int v = __shfl_up(pre, d, 16);
+    if ((lane & 15) >= d) pre += v;
+  }
+  const int all = __shfl(pre, 15);
+  const int fill = all < kP2PBuf ? all : kP2PBuf;
+  const int avail = e1 - e < 16 ? e1 - e : 16;
+  if constexpr (STAGE) {
+    // flat point f of the chunk lies in entry q: pre[q-1] <= f < pre[q];
+    // all loads of the chunk are issued before the LDS stores
+    constexpr int kIt = kP2PBuf / 64;
+    double4 v[kIt];
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+      const int f = it * 64 + lane;
+      int q = 0;
+#pragma unroll
+      for (int k = 0; k < 15; ++k) q += (__shfl(pre, k) <= f) ? 1 : 0;
+      const int lo = __shfl(pre, q) - __shfl(cnt, q);
+      const int u = __shfl(base, q) + (f - lo);
+      if (f < fill) v[it] = make_double4(px[u], py[u], pz[u], qt[u]);
+    }
+#pragma unroll
+    for (int it = 0; it < kIt; ++it) {
+      const int f = it * 64 + lane;
+      if (f < fill) {
+        if constexpr (F32)
+          buf[f] = make_float4((float)(v[it].x - ccx), (float)(v[it].y - ccy), (float)(v[it].z - ccz), (float)v[it].w);
+        else
+          buf[f] = v[it];
+      }
+    }
+  }
+  // entries staged completely, and how far into the next one
+  const int done = __popcll(__ballot(lane < avail && pre <= fill));
+  if (done < avail) {
+    const int prev = done == 0 ? 0 : __shfl(pre, done - 1);
+    off = (done == 0 ? off : 0) + (fill - prev);
+  } else {
+    off = 0;
+  }
+  e += done;
+  return fill;
+}
+
+// Targets per lane T (1 .. 4), lanes per target row TT and source streams R of a
+// leaf with nt targets in binary64: the T of least time per source, T / R, the
+// largest on ties (fewer LDS reads).  Two targets per lane and powers of two
+// for TT left a third of the lanes idle at 39 targets (20,000 points, 512
+// leaves: T 4, TT 10, R 6) and a quarter at 92.
+struct P2PSplit {
+  int T, TT, R;
+};
+__device__ __forceinline__ P2PSplit p2p_split(int nt) {
+  P2PSplit best{1, nt < 64 ? (nt > 0 ? nt : 1) : 64, 1};
+  best.R = 64 / best.TT;
+  int rows = (nt + 63) / 64;
+  // cost T / R, times the passes over the sources; compared as fractions
+#pragma unroll
+  for (int T = 2; T <= 4; ++T) {
+    int tt = (nt + T - 1) / T;
+    tt = tt < 1 ? 1 : tt > 64 ? 64 : tt;
+    const int r = 64 / tt, pass = (nt + T * tt - 1) / (T * tt);
+    if (T * pass * best.R <= best.T * rows * r) {
+      best = P2PSplit{T, tt, r};
+      rows = pass;
+    }
+  }
+  return best;
+}
+
+// What the waves of a workgroup share.
 template <bool F32>
-__global__ __launch_bounds__(64) void k_p2p(int64_t nseg, const int32_t* __restrict__ seg_leaf,
-                                            const int64_t* __restrict__ seg_e0, const int64_t* __restrict__ leaf_seg,
-                                            const int64_t* __restrict__ leaf_part, const int32_t* __restrict__ start,
-                                            const int64_t* __restrict__ s_off, const int32_t* __restrict__ s_idx,
+struct P2PShared {
+  typedef typename std::conditional<F32, float4, double4>::type V;
+};
+
+struct P2POut {
+  double4* part;  // partial sums by target - t0, or null: then the far field is
+                  // added and the results go to the outputs
+  const double *f0, *f1, *f2, *f3;
+  const int32_t* perm;
+  double *pot, *ex, *ey, *ez;
+  __device__ __forceinline__ void put(int t, int t0, double f, double gx, double gy, double gz) const {
+    if (part) {
+      part[t - t0] = make_double4(f, gx, gy, gz);
+      return;
+    }
+    if (f0) {
+      f += f0[t];
+      gx += f1[t];
+      gy += f2[t];
+      gz += f3[t];
+    }
+    const int o = perm[t];
+    pot[o] = f;
+    ex[o] = gx;
+    ey[o] = gy;
+    ez[o] = gz;
+  }
+};
+
+// The targets [t0, t1) of a leaf against the segment; red: 4 T W 64 doubles of
+// LDS for the sums of the waves (W > 1; it may be the waves' buffers).
+template <bool F32, int T, int W, class V>
+__device__ __forceinline__ void p2p_targets(const P2PSeg& sg, int t0, int t1, int TT, int R, V* buf, double* red,
                                             const double* __restrict__ px, const double* __restrict__ py,
                                             const double* __restrict__ pz, const double* __restrict__ qt,
-                                            const int32_t* __restrict__ tstart, const double* __restrict__ tx,
-                                            const double* __restrict__ ty, const double* __restrict__ tz,
-                                            const int32_t* __restrict__ perm, const double* __restrict__ f0,
-                                            const double* __restrict__ f1, const double* __restrict__ f2,
-                                            const double* __restrict__ f3, double4* __restrict__ part,
-                                            double* __restrict__ pot, double* __restrict__ ex,
-                                            double* __restrict__ ey, double* __restrict__ ez,
-                                            const double* __restrict__ lgeom) {
-  __shared__ double4 buf[F32 ? 1 : kP2PBuf];
-  __shared__ float4 bufs[F32 ? kP2PBuf : 1];
-  const int64_t g = xcd_leaf(nseg);
-  if (g >= nseg) return;
-  const int lane = threadIdx.x;
-  const int64_t b = seg_leaf[g];
-  const int64_t sb = leaf_seg[b], ns = leaf_seg[b + 1] - sb, r = g - sb;
-  const int64_t e0 = seg_e0[g], e1 = r + 1 < ns ? seg_e0[g + 1] : s_off[b + 1];
-  const int t0 = tstart[b], t1 = tstart[b + 1];
-  const int nt = t1 - t0;
-  double4* pout = ns > 1 ? part + leaf_part[b] + r * nt : nullptr;  // partial sums, by target - t0
-  // lanes = (target pair, source stream)
-  const int TT = nt <= 16 ? 8 : (nt <= 32 ? 16 : (nt <= 64 ? 32 : 64));
-  const int R = 64 / TT;
+                                            const double* __restrict__ tx, const double* __restrict__ ty,
+                                            const double* __restrict__ tz, double ccx, double ccy, double ccz,
+                                            const P2POut& out) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tl = lane % TT, h = lane / TT;
-  double ccx = 0.0, ccy = 0.0, ccz = 0.0;  // binary32 mode: the target leaf's centre
-  if (F32) {
-    ccx = lgeom[b * 10 + 6];
-    ccy = lgeom[b * 10 + 7];
-    ccz = lgeom[b * 10 + 8];
-  }
-  for (int c0 = t0; c0 < t1; c0 += 2 * TT) {
-    const int ta = c0 + tl, tb = c0 + tl + TT;
-    const bool va = ta < t1, vb = tb < t1;
-    const int ua = va ? ta : t0, ub = vb ? tb : t0;
-    const double xa = tx[ua], ya = ty[ua], za = tz[ua];
-    const double xb = tx[ub], yb = ty[ub], zb = tz[ub];
-    double fa = 0.0, gxa = 0.0, gya = 0.0, gza = 0.0;
-    double fb = 0.0, gxb = 0.0, gyb = 0.0, gzb = 0.0;
-    // binary32: relative target coordinates, chunk sums, compensated totals
-    const float xfa = (float)(xa - ccx), yfa = (float)(ya - ccy), zfa = (float)(za - ccz);
-    const float xfb = (float)(xb - ccx), yfb = (float)(yb - ccy), zfb = (float)(zb - ccz);
-    float sa[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
-    Kahan ka[4], kb[4];
-    auto interact32 = [&](const float4 s) {
-      {
-        const float dx = xfa - s.x, dy = yfa - s.y, dz = zfa - s.z;
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        const float inv = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
-        const float qi = s.w * inv;
-        const float qi3 = qi * inv * inv;
-        sa[0] += qi;
-        sa[1] += qi3 * dx;
-        sa[2] += qi3 * dy;
-        sa[3] += qi3 * dz;
-      }
-      {
-        const float dx = xfb - s.x, dy = yfb - s.y, dz = zfb - s.z;
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        const float inv = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
-        const float qi = s.w * inv;
-        const float qi3 = qi * inv * inv;
-        sb[0] += qi;
-        sb[1] += qi3 * dx;
-        sb[2] += qi3 * dy;
-        sb[3] += qi3 * dz;
-      }
-    };
-    auto interact = [&](const double4 s) {
-      {
-        const double dx = xa - s.x, dy = ya - s.y, dz = za - s.z;
-        const double inv = rsqrt_nr(dx * dx + dy * dy + dz * dz);
-        const double qi = s.w * inv;
-        const double qi3 = qi * inv * inv;
-        fa += qi;
-        gxa += qi3 * dx;
-        gya += qi3 * dy;
-        gza += qi3 * dz;
-      }
-      {
-        const double dx = xb - s.x, dy = yb - s.y, dz = zb - s.z;
-        const double inv = rsqrt_nr(dx * dx + dy * dy + dz * dz);
-        const double qi = s.w * inv;
-        const double qi3 = qi * inv * inv;
-        fb += qi;
-        gxb += qi3 * dx;
-        gyb += qi3 * dy;
-        gzb += qi3 * dz;
-      }
-    };
-    int64_t e = e0;  // next entry
-    int off = 0;     // points of entry e already staged
-    while (e < e1) {
-      // up to 16 entries from e on: lane q < 16 takes entry e + q
-      int base = 0, cnt = 0;
-      if (lane < 16 && e + lane < e1) {
-        const int j = s_idx[e + lane];
-        base = start[j] + (lane == 0 ? off : 0);
-        cnt = start[j + 1] - base;
-      }
-      int pre = cnt;  // inclusive prefix over lanes 0..15
+  const bool lane_on = h < R;
+  for (int c0 = t0; c0 < t1; c0 += T * TT) {
+    double f[T][4] = {};
+    double x[T], y[T], z[T];
 #pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
-        const int v = __shfl_up(pre, d, 16);
-        if ((lane & 15) >= d) pre += v;
+    for (int i = 0; i < T; ++i) {
+      const int t = c0 + tl + i * TT, u = t < t1 ? t : t0;
+      x[i] = tx[u];
+      y[i] = ty[u];
+      z[i] = tz[u];
+    }
+    // this wave's entries
+    int e = F32 ? 0 : (int)((int64_t)sg.ne * w / W), off = 0;
+    const int e1 = F32 ? sg.ne : (int)((int64_t)sg.ne * (w + 1) / W);
+    if constexpr (F32) {
+      float xf[T], yf[T], zf[T], s[T][4] = {};
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        xf[i] = (float)(x[i] - ccx);
+        yf[i] = (float)(y[i] - ccy);
+        zf[i] = (float)(z[i] - ccz);
       }
-      const int all = __shfl(pre, 15);
-      const int fill = all < kP2PBuf ? all : kP2PBuf;
-      const int avail = (int)(e1 - e < 16 ? e1 - e : 16);
-      // flat point f of the chunk lies in entry q: pre[q-1] <= f < pre[q];
-      // all loads of the chunk are issued before the LDS stores
-      constexpr int kIt = kP2PBuf / 64;
-      double4 v[kIt];
+      auto interact = [&](const float4 v) __attribute__((always_inline)) {
 #pragma unroll
-      for (int it = 0; it < kIt; ++it) {
-        const int f = it * 64 + lane;
-        int q = 0;
-#pragma unroll
-        for (int k = 0; k < 15; ++k) q += (__shfl(pre, k) <= f) ? 1 : 0;
-        const int lo = __shfl(pre, q) - __shfl(cnt, q);
-        const int u = __shfl(base, q) + (f - lo);
-        if (f < fill) v[it] = make_double4(px[u], py[u], pz[u], qt[u]);
-      }
-#pragma unroll
-      for (int it = 0; it < kIt; ++it) {
-        const int f = it * 64 + lane;
-        if (f < fill) {
-          if (F32)
-            bufs[f] = make_float4((float)(v[it].x - ccx), (float)(v[it].y - ccy), (float)(v[it].z - ccz),
-                                  (float)v[it].w);
-          else
-            buf[f] = v[it];
+        for (int i = 0; i < T; ++i) {
+          const float dx = xf[i] - v.x, dy = yf[i] - v.y, dz = zf[i] - v.z;
+          const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dx, dx, dy * dy));
+          const float inv = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
+          const float qi = v.w * inv;
+          const float qi3 = qi * inv * inv;
+          s[i][0] = __builtin_fmaf(v.w, inv, s[i][0]);
+          s[i][1] = __builtin_fmaf(qi3, dx, s[i][1]);
+          s[i][2] = __builtin_fmaf(qi3, dy, s[i][2]);
+          s[i][3] = __builtin_fmaf(qi3, dz, s[i][3]);
         }
-      }
-      // entries staged completely, and how far into the next one
-      int done = 0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) done += (k < avail && __shfl(pre, k) <= fill) ? 1 : 0;
-      if (done < avail) {
-        const int prev = done == 0 ? 0 : __shfl(pre, done - 1);
-        off = (done == 0 ? off : 0) + (fill - prev);
-      } else {
-        off = 0;
-      }
-      e += done;
-      __syncthreads();
-      int u = h;
-      if (F32) {
+      };
+      // the sums of the next chunk, in s
+      auto chunk = [&] {
+        const int fill = p2p_chunk<F32, true>(sg, e1, e, off, buf, lane, px, py, pz, qt, ccx, ccy, ccz);
+        p2p_wave_fence();
+        int u = h;
         for (; u + 3 * R < fill; u += 4 * R) {
-          const float4 s0 = bufs[u], s1 = bufs[u + R], s2 = bufs[u + 2 * R], s3 = bufs[u + 3 * R];
-          interact32(s0);
-          interact32(s1);
-          interact32(s2);
-          interact32(s3);
-        }
-        for (; u < fill; u += R) interact32(bufs[u]);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          ka[k].add(sa[k]);
-          kb[k].add(sb[k]);
-          sa[k] = 0.f;
-          sb[k] = 0.f;
-        }
-      } else {
-        for (; u + 3 * R < fill; u += 4 * R) {
-          const double4 s0 = buf[u], s1 = buf[u + R], s2 = buf[u + 2 * R], s3 = buf[u + 3 * R];
+          const float4 s0 = buf[u], s1 = buf[u + R], s2 = buf[u + 2 * R], s3 = buf[u + 3 * R];
           interact(s0);
           interact(s1);
           interact(s2);
           interact(s3);
         }
         for (; u < fill; u += R) interact(buf[u]);
-      }
-      __syncthreads();
-    }
-    if (F32) {
-      fa = ka[0].get();
-      gxa = ka[1].get();
-      gya = ka[2].get();
-      gza = ka[3].get();
-      fb = kb[0].get();
-      gxb = kb[1].get();
-      gyb = kb[2].get();
-      gzb = kb[3].get();
-    }
-    // sum the source streams (fixed order)
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      if (d >= TT) {
-        fa += __shfl_xor(fa, d);
-        gxa += __shfl_xor(gxa, d);
-        gya += __shfl_xor(gya, d);
-        gza += __shfl_xor(gza, d);
-        fb += __shfl_xor(fb, d);
-        gxb += __shfl_xor(gxb, d);
-        gyb += __shfl_xor(gyb, d);
-        gzb += __shfl_xor(gzb, d);
-      }
-    }
-    if (h == 0) {
-      auto put = [&](int t, double f, double gx, double gy, double gz) {
-        if (pout) {
-          pout[t - t0] = make_double4(f, gx, gy, gz);
-          return;
-        }
-        if (f0) {
-          f += f0[t];
-          gx += f1[t];
-          gy += f2[t];
-          gz += f3[t];
-        }
-        const int o = perm[t];
-        pot[o] = f;
-        ex[o] = gx;
-        ey[o] = gy;
-        ez[o] = gz;
+        p2p_wave_fence();
       };
-      if (va) put(ta, fa, gxa, gya, gza);
-      if (vb) put(tb, fb, gxb, gyb, gzb);
+      if constexpr (W == 1) {
+        Kahan k[T][4];
+        while (e < e1) {
+          chunk();
+#pragma unroll
+          for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              k[i][j].add(s[i][j]);
+              s[i][j] = 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) f[i][j] = k[i][j].get();
+      } else {
+        constexpr int NQ = T * 4 / W;  // accumulators of a wave: w, w + W, ...
+        static_assert(NQ * W == T * 4, "");
+        float* cs = (float*)red;       // [slot][accumulator][lane]
+        Kahan k[NQ];
+        while (e < e1) {
+          int slot = 0;
+          for (; slot < kP2PSlots * W && e < e1; ++slot) {
+            if (slot % W != w) {
+              p2p_chunk<F32, false>(sg, e1, e, off, buf, lane, px, py, pz, qt, ccx, ccy, ccz);
+              continue;
+            }
+            chunk();
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                cs[(slot * T * 4 + i * 4 + j) * 64 + lane] = s[i][j];
+                s[i][j] = 0.f;
+              }
+          }
+          __syncthreads();
+          for (int c = 0; c < slot; ++c)
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) k[i].add(cs[(c * T * 4 + w + i * W) * 64 + lane]);
+          __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) red[(w + i * W) * 64 + lane] = k[i].get();
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) f[i][j] = red[(i * 4 + j) * 64 + lane];
+      }
+    } else {
+      auto interact = [&](const double4 v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+          const double dx = x[i] - v.x, dy = y[i] - v.y, dz = z[i] - v.z;
+          const double inv = rsqrt_nr(dx * dx + dy * dy + dz * dz);
+          const double qi = v.w * inv;
+          const double qi3 = qi * inv * inv;
+          f[i][0] += qi;
+          f[i][1] += qi3 * dx;
+          f[i][2] += qi3 * dy;
+          f[i][3] += qi3 * dz;
+        }
+      };
+      while (e < e1) {
+        const int fill = p2p_chunk<F32, true>(sg, e1, e, off, buf, lane, px, py, pz, qt, ccx, ccy, ccz);
+        p2p_wave_fence();
+        int u = lane_on ? h : fill;
+        for (; u + R < fill; u += 2 * R) {
+          const double4 s0 = buf[u], s1 = buf[u + R];
+          interact(s0);
+          interact(s1);
+        }
+        for (; u < fill; u += R) interact(buf[u]);
+        p2p_wave_fence();
+      }
     }
+    // sum the source streams (fixed order): binary32 has powers of two and
+    // halves them, as for any W
+    if constexpr (F32) {
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        if (d >= TT) {
+#pragma unroll
+          for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[i][j] += __shfl_xor(f[i][j], d);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double v = f[i][j];
+          for (int r = 1; r < R; ++r) f[i][j] += __shfl(v, tl + r * TT);
+        }
+    }
+    if constexpr (!F32 && W > 1) {  // the waves' sums, in wave order
+      __syncthreads();
+      if (w > 0 && lane < TT)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) red[((w - 1) * T * 4 + i * 4 + j) * 64 + lane] = f[i][j];
+      __syncthreads();
+      if (w == 0 && lane < TT)
+        for (int v = 0; v < W - 1; ++v)
+#pragma unroll
+          for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[i][j] += red[(v * T * 4 + i * 4 + j) * 64 + lane];
+    }
+    if (w == 0 && lane < TT) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int t = c0 + tl + i * TT;
+        if (t < t1) out.put(t, t0, f[i][0], f[i][1], f[i][2], f[i][3]);
+      }
+    }
+    if constexpr (W > 1) __syncthreads();  // red read before the buffers are filled again
+  }
+}
+
+template <bool F32, int W>
+__global__ __launch_bounds__(64 * W) void k_p2p(
+    int64_t nseg, const int32_t* __restrict__ seg_leaf, const int64_t* __restrict__ seg_e0,
+    const int64_t* __restrict__ leaf_seg, const int64_t* __restrict__ leaf_part, const int32_t* __restrict__ start,
+    const int64_t* __restrict__ s_off, const int32_t* __restrict__ s_idx, const double* __restrict__ px,
+    const double* __restrict__ py, const double* __restrict__ pz, const double* __restrict__ qt,
+    const int32_t* __restrict__ tstart, const double* __restrict__ tx, const double* __restrict__ ty,
+    const double* __restrict__ tz, const int32_t* __restrict__ perm, const double* __restrict__ f0,
+    const double* __restrict__ f1, const double* __restrict__ f2, const double* __restrict__ f3,
+    double4* __restrict__ part, double* __restrict__ pot, double* __restrict__ ex, double* __restrict__ ey,
+    double* __restrict__ ez, const double* __restrict__ lgeom) {
+  typedef typename P2PShared<F32>::V V;
+  // the waves' chunks (8 KB each, 4 KB in binary32); in binary64 later their
+  // sums, at most 4 x 4 x 64 doubles a wave
+  constexpr int kBytes = (int)sizeof(V) * kP2PBuf;
+  static_assert(F32 || kBytes >= 4 * 4 * 64 * 8, "");
+  constexpr int kSums = F32 && W > 1 ? kP2PSlots * W * 2 * 4 * 64 * 4 : 0;  // binary32: the chunk sums of a round
+  __shared__ __align__(16) char lds[W * kBytes + kSums];
+  __shared__ int32_t ebase[kP2PEntries], ecnt[kP2PEntries];
+  const int64_t g = xcd_leaf(nseg);
+  if (g >= nseg) return;
+  const int64_t b = seg_leaf[g];
+  const int64_t sb = leaf_seg[b], ns = leaf_seg[b + 1] - sb, r = g - sb;
+  const int64_t e0 = seg_e0[g], e1 = r + 1 < ns ? seg_e0[g + 1] : s_off[b + 1];
+  const int t0 = tstart[b], t1 = tstart[b + 1];
+  const int nt = t1 - t0;
+  const P2PSeg sg{s_idx + e0, start, (int)(e1 - e0), ebase, ecnt};
+  for (int i = threadIdx.x; i < sg.ne && i < kP2PEntries; i += 64 * W) {
+    const int j = sg.s_idx[i], u = start[j];
+    ebase[i] = u;
+    ecnt[i] = start[j + 1] - u;
+  }
+  __syncthreads();
+  const P2POut out{ns > 1 ? part + leaf_part[b] + r * nt : nullptr, f0, f1, f2, f3, perm, pot, ex, ey, ez};
+  V* buf = (V*)(lds + (threadIdx.x >> 6) * kBytes);
+  double* red = (double*)(F32 ? lds + W * kBytes : lds);
+  if constexpr (F32) {
+    const double ccx = lgeom[b * 10 + 6], ccy = lgeom[b * 10 + 7], ccz = lgeom[b * 10 + 8];
+    const int TT = nt <= 16 ? 8 : (nt <= 32 ? 16 : (nt <= 64 ? 32 : 64));
+    p2p_targets<true, 2, W>(sg, t0, t1, TT, 64 / TT, buf, red, px, py, pz, qt, tx, ty, tz, ccx, ccy, ccz, out);
+  } else {
+    const P2PSplit sp = p2p_split(nt);
+    auto go = [&](auto t) __attribute__((always_inline)) {
+      p2p_targets<false, decltype(t)::value, W>(sg, t0, t1, sp.TT, sp.R, buf, red, px, py, pz, qt, tx, ty, tz, 0.0, 0.0,
+                                                0.0, out);
+    };
+    if (sp.T == 4)
+      go(std::integral_constant<int, 4>{});
+    else if (sp.T == 3)
+      go(std::integral_constant<int, 3>{});
+    else if (sp.T == 2)
+      go(std::integral_constant<int, 2>{});
+    else
+      go(std::integral_constant<int, 1>{});
   }
 }
 
@@ -543,14 +718,31 @@ void near_field_and_store(const Tree& t, const double* qt, int parts, int prec, 
   if (parts & FMM_PART_NEAR) {
     double4* part = npart > 0 ? (double4*)dalloc(npart * sizeof(double4), s) : nullptr;
     const unsigned grid = (unsigned)(8 * ((t.p2p_nseg + 7) / 8));
+    auto go = [&](auto f32, auto w) {
+      k_p2p<decltype(f32)::value, decltype(w)::value><<<grid, 64 * decltype(w)::value, 0, s>>>(
+          t.p2p_nseg, t.p2p_seg_leaf, t.p2p_seg_e0, t.p2p_leaf_seg, leaf_part, V.start, V.s_off, V.s_idx, t.px, t.py,
+          t.pz, qt, start, px, py, pz, perm, far[0], far[1], far[2], far[3], part, pot, ex, ey, ez, V.geom);
+    };
+    auto go_w = [&](auto f32) {
+      // Waves per segment: about four on every SIMD (1,024 of them).  One wave
+      // takes 150 us over a full segment, so few segments left the launch
+      // waiting for single waves; with many, more waves per segment only add
+      // barriers.  Measured, one wave / here: 20,000 uniform points, 512 leaves
+      // 228 / 88 us (of which the split of the lanes a third), 47,003 points on
+      // a sphere 1,001 / 531, 3,000 points binary32 141 / 35; from 2,048
+      // segments on within 2 % (issue-bound: 1.42e12 interactions/s on 2^22
+      // Plummer points).
+      if (t.p2p_nseg <= 512)
+        go(f32, std::integral_constant<int, 8>{});
+      else if (t.p2p_nseg <= 2048)
+        go(f32, std::integral_constant<int, 4>{});
+      else
+        go(f32, std::integral_constant<int, 1>{});
+    };
     if (prec == FMM_PREC_F32)
-      k_p2p<true><<<grid, 64, 0, s>>>(t.p2p_nseg, t.p2p_seg_leaf, t.p2p_seg_e0, t.p2p_leaf_seg, leaf_part, V.start,
-                                      V.s_off, V.s_idx, t.px, t.py, t.pz, qt, start, px, py, pz, perm, far[0], far[1],
-                                      far[2], far[3], part, pot, ex, ey, ez, V.geom);
+      go_w(std::true_type{});
     else
-      k_p2p<false><<<grid, 64, 0, s>>>(t.p2p_nseg, t.p2p_seg_leaf, t.p2p_seg_e0, t.p2p_leaf_seg, leaf_part, V.start,
-                                       V.s_off, V.s_idx, t.px, t.py, t.pz, qt, start, px, py, pz, perm, far[0],
-                                       far[1], far[2], far[3], part, pot, ex, ey, ez, V.geom);
+      go_w(std::false_type{});
     HIPCHECK(hipGetLastError());
     if (part) {
       k_p2p_final<1><<<gfin, 256, 0, s>>>(V.nbox, start, t.p2p_leaf_seg, leaf_part, part, perm, far[0], far[1],
