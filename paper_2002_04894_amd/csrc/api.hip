@@ -379,6 +379,15 @@ fmm_tree* build_impl(const double* x, const double* y, const double* z, int64_t 
   t.build_stream = s;
   t.alloc = fmm::current_allocator();
   fmm::CallScope scope(t.alloc, s);  // frees everything allocated here if the build fails
+  // kernels of the build write into this thread's pinned words: a build that
+  // fails waits for them, so that none writes into a later build's
+  struct Drain {
+    hipStream_t s;
+    bool on = true;
+    ~Drain() {
+      if (on) (void)hipStreamSynchronize(s);
+    }
+  } drain{s};
   fmm::timer().reset();
   fmm::timer().begin(FMM_PH_TREE, s);
   fmm::tree_build(t, x, y, z, tx, ty, tz, s);
@@ -394,6 +403,7 @@ fmm_tree* build_impl(const double* x, const double* y, const double* z, int64_t 
   HIPCHECK(hipEventCreateWithFlags(&t.built, hipEventDisableTiming));
   HIPCHECK(hipEventRecord(t.built, s));
   t.bytes = scope.keep();
+  drain.on = false;
   return h.release();
 }
 

@@ -70,6 +70,16 @@ bool capturing(hipStream_t s);
 // once per thread; kStageWords int64 values).
 constexpr int kStageWords = 64;
 int64_t* host_stage();
+// word of host_stage that the tree build's last kernel sets when a coordinate
+// is not acceptable; looked at after the next wait for the stream (throws)
+constexpr int kBadWord = kStageWords - 1;
+void check_points_flag();
+
+// up to this many items (boxes of a level, targets) a build takes one-block
+// kernels: levels up to 4
+constexpr int64_t kSmallScan = 8192;
+void scan_plan_small(const int32_t* nseg, const int32_t* start, const int64_t* work, int64_t* leaf_seg,
+                     int64_t* leaf_part, int64_t nleaf, int64_t* totals, hipStream_t s);
 
 // Per-level box geometry / lists in device memory.
 struct Level {

@@ -45,28 +45,31 @@ __device__ __forceinline__ int64_t xcd_box(int64_t nbox) {
 }
 
 // Candidate centre and radius as one 32-byte record per box (one load per
-// candidate instead of four at the 80-byte stride of the box geometry).
-__global__ void k_centre_radius(int64_t nbox, const double* __restrict__ geom, double4* __restrict__ cr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nbox) cr[i] = make_double4(geom[i * 10 + 6], geom[i * 10 + 7], geom[i * 10 + 8], geom[i * 10 + 9]);
+// candidate instead of four at the 80-byte stride of the box geometry), for
+// all levels at once.
+__global__ void k_centre_radius(int64_t nbox_total, LevelView lv, double4* __restrict__ cr) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= nbox_total) return;
+  int l = 0;
+  while (l < lv.L && g >= lv.gofs[l + 1]) ++l;
+  const double* geom = lv.geom[l] + (g - lv.gofs[l]) * 10;
+  cr[g] = make_double4(geom[6], geom[7], geom[8], geom[9]);
 }
 
-// 64-bit mask words per child of each parent: ceil(8 |strong(parent)| / 64)
-__global__ void k_mask_words(int64_t npar, const int64_t* __restrict__ ps_off, int32_t* __restrict__ words) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < npar) words[p] = (int32_t)((ps_off[p + 1] - ps_off[p] + 7) / 8);
-}
+// Mask words of a child of parent p, ceil(8 S / 64) with S = |strong(p)|, and
+// the first one, in units of the eight children: the parents' rows may not
+// overlap, and floor(o / 8) + p, o the parent's offset into the strong
+// entries, leaves at least ceil(S / 8) between neighbours, so no scan is needed.
+__device__ __forceinline__ int64_t mask_words(int64_t S) { return (S + 7) / 8; }
+__device__ __forceinline__ int64_t mask_first(int64_t o, int64_t p) { return o / 8 + p; }
 
 // Count pass: the theta test of every candidate of box i; the weak outcome
-// of each group of 64 candidates is kept as one mask word (box i's words
-// start at 8 wofs[parent] + child * words[parent]), and the counts of the
-// row are written.
+// of each group of 64 candidates is kept as one mask word, and the counts of
+// the row are written.
 __global__ __launch_bounds__(64) void k_lists_count(int64_t nbox, const double* __restrict__ geom,
                                                      const double4* __restrict__ cr,
                                                      const int64_t* __restrict__ ps_off,
                                                      const int32_t* __restrict__ ps_idx, double theta,
-                                                     const int64_t* __restrict__ wofs,
-                                                     const int32_t* __restrict__ words,
                                                      uint64_t* __restrict__ mask, int32_t* __restrict__ ns,
                                                      int32_t* __restrict__ nw) {
   const int lane = threadIdx.x & 63;
@@ -76,7 +79,7 @@ __global__ __launch_bounds__(64) void k_lists_count(int64_t nbox, const double* 
   const double* gi = geom + i * 10;
   const int64_t e0 = ps_off[par];
   const int64_t ncand = 8 * (ps_off[par + 1] - e0);
-  uint64_t* mrow = mask + 8 * wofs[par] + (i & 7) * (int64_t)words[par];
+  uint64_t* mrow = mask + 8 * mask_first(e0, par) + (i & 7) * mask_words(ncand / 8);
   int64_t cs = 0, cw = 0;
   for (int64_t k0 = 0; k0 < ncand; k0 += 64 * kListGroups) {
     int64_t j[kListGroups];
@@ -111,8 +114,6 @@ __global__ __launch_bounds__(64) void k_lists_count(int64_t nbox, const double* 
 // by the count pass's mask words (no geometry, no test).
 __global__ __launch_bounds__(64) void k_lists_fill(int64_t nbox, const int64_t* __restrict__ ps_off,
                                                     const int32_t* __restrict__ ps_idx,
-                                                    const int64_t* __restrict__ wofs,
-                                                    const int32_t* __restrict__ words,
                                                     const uint64_t* __restrict__ mask,
                                                     const int64_t* __restrict__ s_off, int32_t* __restrict__ s_idx,
                                                     const int64_t* __restrict__ w_off, int32_t* __restrict__ w_idx) {
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(64) void k_lists_fill(int64_t nbox, const int64_t* 
   const int64_t par = i >> 3;
   const int64_t e0 = ps_off[par];
   const int64_t ncand = 8 * (ps_off[par + 1] - e0);
-  const uint64_t* mrow = mask + 8 * wofs[par] + (i & 7) * (int64_t)words[par];
+  const uint64_t* mrow = mask + 8 * mask_first(e0, par) + (i & 7) * mask_words(ncand / 8);
   const uint64_t below = (1ull << lane) - 1ull;
   const int64_t so = s_off[i], wo = w_off[i];
   int64_t cs = 0, cw = 0;
@@ -327,6 +328,99 @@ __global__ void k_scan_add(int64_t* __restrict__ out, int64_t n, const int64_t* 
   if (i < n) out[i] += tile_off[i / kScanTile];
 }
 
+// ---- the same for few items, one block per array: a launch instead of three
+// per scan, and the totals go to pinned host words instead of a copy each.  A
+// build of 1,000 points spends its time launching: 76 -> 37 launches.
+constexpr int kSmallBS = 1024;
+
+// out[i] = sum of get(0 .. i-1), i = 0 .. n (n <= kSmallScan)
+template <class F>
+__device__ __forceinline__ int64_t block_scan_to(F get, int64_t* __restrict__ out, int n) {
+  __shared__ int64_t sm[kSmallBS / 64];
+  const int per = (n + kSmallBS - 1) / kSmallBS;
+  const int i0 = threadIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
+  int64_t t = 0;
+  for (int i = i0; i < i1; ++i) t += get(i);
+  const int64_t inc = wave_incl_scan(t);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (lane == 63) sm[wid] = inc;
+  __syncthreads();
+  int64_t off = inc - t, tot = 0;
+  for (int w = 0; w < kSmallBS / 64; ++w) {
+    off += w < wid ? sm[w] : 0;
+    tot += sm[w];
+  }
+  if (out) {
+    for (int i = i0; i < i1; ++i) {
+      out[i] = off;
+      off += get(i);
+    }
+    if (threadIdx.x == 0) out[n] = tot;
+  }
+  return tot;
+}
+
+// block 0: the strong, block 1: the weak counts of a level
+__global__ __launch_bounds__(kSmallBS) void k_scan_level(const int32_t* __restrict__ ns, const int32_t* __restrict__ nw,
+                                                         int64_t* __restrict__ s_off, int64_t* __restrict__ w_off, int n,
+                                                         int64_t* __restrict__ totals) {
+  const int32_t* in = blockIdx.x == 0 ? ns : nw;
+  const int64_t tot = block_scan_to([&](int i) { return (int64_t)in[i]; }, blockIdx.x == 0 ? s_off : w_off, n);
+  if (threadIdx.x == 0) totals[blockIdx.x] = tot;
+}
+
+// the near-field plan (p2p.hip): block 0 the leaves' segments, block 1 the
+// partial sums of the split leaves, block 2 the interactions
+__global__ __launch_bounds__(kSmallBS) void k_scan_plan(const int32_t* __restrict__ nseg,
+                                                        const int32_t* __restrict__ start,
+                                                        const int64_t* __restrict__ work, int64_t* __restrict__ leaf_seg,
+                                                        int64_t* __restrict__ leaf_part, int n,
+                                                        int64_t* __restrict__ totals) {
+  int64_t tot;
+  if (blockIdx.x == 0)
+    tot = block_scan_to([&](int i) { return (int64_t)nseg[i]; }, leaf_seg, n);
+  else if (blockIdx.x == 1)
+    tot = block_scan_to([&](int i) { return nseg[i] > 1 ? (int64_t)nseg[i] * (start[i + 1] - start[i]) : (int64_t)0; },
+                        leaf_part, n);
+  else
+    tot = block_scan_to([&](int i) { return work[i]; }, nullptr, n);
+  if (threadIdx.x == 0) totals[blockIdx.x] = tot;
+}
+
+// the work order of few targets in one block: count, scan, scatter in LDS
+__global__ __launch_bounds__(kSmallBS) void k_order_small(int n, LevelView lv, int64_t longest,
+                                                          int32_t* __restrict__ order) {
+  __shared__ int32_t h[kOrderBins];
+  __shared__ int32_t sums[kSmallBS / 64];
+  constexpr int kPer = kOrderBins / kSmallBS;
+  for (int b = threadIdx.x; b < kOrderBins; b += kSmallBS) h[b] = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kSmallBS) atomicAdd(&h[order_bin<false>(lv, i)], 1);
+  __syncthreads();
+  int32_t v[kPer], t = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    v[k] = h[threadIdx.x * kPer + k];
+    t += v[k];
+  }
+  const int32_t inc = (int32_t)wave_incl_scan(t);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (lane == 63) sums[wid] = inc;
+  __syncthreads();
+  int32_t first = inc - t;
+  for (int w = 0; w < wid; ++w) first += sums[w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int b = threadIdx.x * kPer + k;
+    h[b] = first;
+    if (b == 0 && longest >= kOrderBins - 1) order[n] = v[k];
+    if (longest < kOrderBins - 1 && b == kOrderBins - 1 - longest) order[n] = first;
+    first += v[k];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kSmallBS) order[atomicAdd(&h[order_bin<false>(lv, i)], 1)] = i;
+}
+
 }  // namespace
 
 namespace {
@@ -366,6 +460,12 @@ void scan_counts(const int64_t* in, int64_t* out, int64_t n, int64_t base, hipSt
   scan_any(in, out, n, base, s);
 }
 
+void scan_plan_small(const int32_t* nseg, const int32_t* start, const int64_t* work, int64_t* leaf_seg,
+                     int64_t* leaf_part, int64_t nleaf, int64_t* totals, hipStream_t s) {
+  k_scan_plan<<<3, kSmallBS, 0, s>>>(nseg, start, work, leaf_seg, leaf_part, (int)nleaf, totals);
+  HIPCHECK(hipGetLastError());
+}
+
 void lists_build(Tree& t, hipStream_t s) {
   const int L = t.L;
   // level 0: root strongly connected to itself
@@ -382,55 +482,57 @@ void lists_build(Tree& t, hipStream_t s) {
   }
   int64_t* tot = host_stage();
   int64_t m2l = 0;
+  double4* cr = (double4*)dalloc(t.nbox_total * sizeof(double4), s);
+  if (L > 0) {
+    k_centre_radius<<<(unsigned)((t.nbox_total + 255) / 256), 256, 0, s>>>(t.nbox_total, t.view(), cr);
+    HIPCHECK(hipGetLastError());
+  }
   for (int l = 1; l <= L; ++l) {
     Level& P = t.lev[l - 1];
     Level& V = t.lev[l];
     const int64_t nb = V.nbox;
     const int64_t npar = P.nbox;
-    int32_t* ns = (int32_t*)dalloc(nb * sizeof(int32_t), s);
-    int32_t* nw = (int32_t*)dalloc(nb * sizeof(int32_t), s);
-    double4* cr = (double4*)dalloc(nb * sizeof(double4), s);
-    int32_t* words = (int32_t*)dalloc(npar * sizeof(int32_t), s);
-    int64_t* wofs = (int64_t*)dalloc((npar + 1) * sizeof(int64_t), s);
-    k_centre_radius<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(nb, V.geom, cr);
-    HIPCHECK(hipGetLastError());
-    k_mask_words<<<(unsigned)((npar + 255) / 256), 256, 0, s>>>(npar, P.s_off, words);
-    HIPCHECK(hipGetLastError());
-    scan_counts(words, wofs, npar, 0, s);
-    // mask words in all: 8 sum_p ceil(S_p / 8) <= (the parents' strong
-    // entries) + 8 npar, known on the host without a read-back
+    int32_t* ns = (int32_t*)dalloc(2 * nb * sizeof(int32_t), s);
+    int32_t* nw = ns + nb;
+    // mask words in all, known on the host without a read-back
     const int64_t nwords = P.s_nnz + 8 * npar;
     uint64_t* mask = (uint64_t*)dalloc(std::max<int64_t>(1, nwords) * sizeof(uint64_t), s);
     const unsigned grid = (unsigned)(8 * ((nb + 7) / 8));
-    k_lists_count<<<grid, 64, 0, s>>>(nb, V.geom, cr, P.s_off, P.s_idx, t.theta, wofs, words, mask, ns, nw);
+    k_lists_count<<<grid, 64, 0, s>>>(nb, V.geom, cr + V.gofs, P.s_off, P.s_idx, t.theta, mask, ns, nw);
     HIPCHECK(hipGetLastError());
     V.s_off = (int64_t*)dalloc((nb + 1) * sizeof(int64_t), s);
     V.w_off = (int64_t*)dalloc((nb + 1) * sizeof(int64_t), s);
-    scan_counts(ns, V.s_off, nb, 0, s);
-    scan_counts(nw, V.w_off, nb, 0, s);
-    HIPCHECK(hipMemcpyAsync(&tot[0], V.s_off + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipMemcpyAsync(&tot[1], V.w_off + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    if (nb <= kSmallScan) {
+      k_scan_level<<<2, kSmallBS, 0, s>>>(ns, nw, V.s_off, V.w_off, (int)nb, tot);
+      HIPCHECK(hipGetLastError());
+    } else {
+      scan_counts(ns, V.s_off, nb, 0, s);
+      scan_counts(nw, V.w_off, nb, 0, s);
+      HIPCHECK(hipMemcpyAsync(&tot[0], V.s_off + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+      HIPCHECK(hipMemcpyAsync(&tot[1], V.w_off + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    }
     HIPCHECK(hipStreamSynchronize(s));
+    check_points_flag();
     V.s_nnz = tot[0];
     V.w_nnz = tot[1];
     m2l += V.w_nnz;
     V.s_idx = (int32_t*)dalloc(std::max<int64_t>(1, V.s_nnz) * sizeof(int32_t), s);
     V.w_idx = (int32_t*)dalloc(std::max<int64_t>(1, V.w_nnz) * sizeof(int32_t), s);
-    k_lists_fill<<<grid, 64, 0, s>>>(nb, P.s_off, P.s_idx, wofs, words, mask, V.s_off, V.s_idx, V.w_off,
-                                      V.w_idx);
+    k_lists_fill<<<grid, 64, 0, s>>>(nb, P.s_off, P.s_idx, mask, V.s_off, V.s_idx, V.w_off, V.w_idx);
     HIPCHECK(hipGetLastError());
     dfree(mask, s);
-    dfree(wofs, s);
-    dfree(words, s);
-    dfree(cr, s);
     dfree(ns, s);
-    dfree(nw, s);
   }
+  dfree(cr, s);
   t.m2l_pairs = m2l;
 
   // M2L work order over the targets of levels 1..L (box id - 1)
   const int64_t ntarget = t.nbox_total - 1;
-  if (ntarget > 0) {
+  if (ntarget > 0 && ntarget <= kSmallScan) {
+    t.m2l_order = (int32_t*)dalloc((ntarget + 1) * sizeof(int32_t), s);
+    k_order_small<<<1, kSmallBS, 0, s>>>((int)ntarget, t.view(), m2l / kM2LWaves, t.m2l_order);
+    HIPCHECK(hipGetLastError());
+  } else if (ntarget > 0) {
     const bool sib = ntarget >= kM2LSiblingsMin;
     const int64_t n = sib ? ntarget / 8 : ntarget;
     const unsigned grid = (unsigned)((n + kOrderChunk - 1) / kOrderChunk);

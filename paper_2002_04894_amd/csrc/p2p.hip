@@ -633,25 +633,32 @@ void p2p_plan(Tree& t, hipStream_t s) {
   const int64_t nleaf = V.nbox;
   int32_t* nseg = (int32_t*)dalloc(nleaf * sizeof(int32_t), s);
   int64_t* work = (int64_t*)dalloc(nleaf * sizeof(int64_t), s);
-  int64_t* pcnt = (int64_t*)dalloc(nleaf * sizeof(int64_t), s);
-  unsigned long long* acc = (unsigned long long*)dalloc(sizeof(unsigned long long), s);
-  HIPCHECK(hipMemsetAsync(acc, 0, sizeof(unsigned long long), s));
   const unsigned gw = (unsigned)((nleaf + 3) / 4);
   k_seg_plan<false><<<gw, 256, 0, s>>>(nleaf, V.start, V.s_off, V.s_idx, nseg, work, nullptr, nullptr, nullptr);
   HIPCHECK(hipGetLastError());
   t.p2p_leaf_seg = (int64_t*)dalloc((nleaf + 1) * sizeof(int64_t), s);
   t.p2p_leaf_part = (int64_t*)dalloc((nleaf + 1) * sizeof(int64_t), s);
-  scan_counts(nseg, t.p2p_leaf_seg, nleaf, 0, s);
-  k_part_count<<<(unsigned)((nleaf + 255) / 256), 256, 0, s>>>(nleaf, V.start, nseg, pcnt);
-  HIPCHECK(hipGetLastError());
-  scan_counts(pcnt, t.p2p_leaf_part, nleaf, 0, s);
-  k_sum64<<<(unsigned)((nleaf + 255) / 256), 256, 0, s>>>(nleaf, work, acc);
-  HIPCHECK(hipGetLastError());
   int64_t* h = host_stage();
-  HIPCHECK(hipMemcpyAsync(&h[0], t.p2p_leaf_seg + nleaf, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipMemcpyAsync(&h[1], t.p2p_leaf_part + nleaf, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipMemcpyAsync(&h[2], acc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  if (nleaf <= kSmallScan) {
+    scan_plan_small(nseg, V.start, work, t.p2p_leaf_seg, t.p2p_leaf_part, nleaf, h, s);
+  } else {
+    int64_t* pcnt = (int64_t*)dalloc(nleaf * sizeof(int64_t), s);
+    unsigned long long* acc = (unsigned long long*)dalloc(sizeof(unsigned long long), s);
+    HIPCHECK(hipMemsetAsync(acc, 0, sizeof(unsigned long long), s));
+    scan_counts(nseg, t.p2p_leaf_seg, nleaf, 0, s);
+    k_part_count<<<(unsigned)((nleaf + 255) / 256), 256, 0, s>>>(nleaf, V.start, nseg, pcnt);
+    HIPCHECK(hipGetLastError());
+    scan_counts(pcnt, t.p2p_leaf_part, nleaf, 0, s);
+    k_sum64<<<(unsigned)((nleaf + 255) / 256), 256, 0, s>>>(nleaf, work, acc);
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpyAsync(&h[0], t.p2p_leaf_seg + nleaf, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipMemcpyAsync(&h[1], t.p2p_leaf_part + nleaf, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipMemcpyAsync(&h[2], acc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    dfree(pcnt, s);
+    dfree(acc, s);
+  }
   HIPCHECK(hipStreamSynchronize(s));
+  check_points_flag();
   t.p2p_nseg = h[0];
   t.p2p_npart = h[1];
   t.p2p_pairs = h[2] - t.n;  // minus the n self pairs
@@ -662,8 +669,6 @@ void p2p_plan(Tree& t, hipStream_t s) {
   HIPCHECK(hipGetLastError());
   dfree(nseg, s);
   dfree(work, s);
-  dfree(pcnt, s);
-  dfree(acc, s);
 }
 
 // prec: FMM_PREC_F64; FMM_PREC_MIXED for the binary32 M2L; FMM_PREC_F32 for

@@ -71,14 +71,18 @@ __global__ void k_bbox_partial(const double* __restrict__ x, const double* __res
   }
 }
 
-__global__ void k_bbox_final(const double* __restrict__ part, int nparts, int64_t n, double* __restrict__ cells,
-                             int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_n) {
-  if (threadIdx.x < 6) {
-    const int k = threadIdx.x;
-    double r = part[k];
-    for (int i = 1; i < nparts; ++i) r = k < 3 ? fmin(r, part[i * 6 + k]) : fmax(r, part[i * 6 + k]);
-    cells[k] = r;
+// one block; a wave per value (six of them) over the partials
+__global__ __launch_bounds__(384) void k_bbox_final(const double* __restrict__ part, int nparts, int64_t n,
+                                                    double* __restrict__ cells, int32_t* __restrict__ seg_start,
+                                                    int32_t* __restrict__ seg_n) {
+  const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double r = part[k];
+  for (int i = lane; i < nparts; i += 64) r = k < 3 ? fmin(r, part[i * 6 + k]) : fmax(r, part[i * 6 + k]);
+  for (int d = 32; d >= 1; d >>= 1) {
+    const double o = __shfl_xor(r, d);
+    r = k < 3 ? fmin(r, o) : fmax(r, o);
   }
+  if (lane == 0) cells[k] = r;
   if (threadIdx.x == 0) {
     seg_start[0] = 0;
     seg_n[0] = (int32_t)n;
@@ -749,27 +753,36 @@ __global__ void k_to_int32(int64_t n, const int64_t* __restrict__ in, int32_t* _
   if (i <= n) out[i] = (int32_t)in[i];
 }
 
-// centre = cell centre, radius = half the cell diagonal (Section 2.1.1)
-__global__ void k_box_geom(const double* __restrict__ cells, const int32_t* __restrict__ seg_start, int depth,
-                           int64_t nbox, double* __restrict__ geom, int32_t* __restrict__ start, int32_t n) {
+// centre = cell centre, radius = half the cell diagonal (Section 2.1.1), for
+// the boxes of all levels; also the point ranges' ends and, for the host, the
+// flag of unacceptable coordinates
+struct GeomOut {
+  int L;
+  int64_t gofs[kMaxLevels + 2];
+  double* geom[kMaxLevels + 1];
+  int32_t* start[kMaxLevels + 1];
+};
+__global__ void k_box_geom(const double* __restrict__ cells, const int32_t* __restrict__ seg_start, GeomOut o, int32_t n,
+                           const int* __restrict__ bad, int64_t* __restrict__ host_bad) {
 #pragma clang fp contract(off)
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b > nbox) return;
-  if (b == nbox) {
-    start[nbox] = n;
-    return;
-  }
-  const int64_t c = ((int64_t)1 << depth) - 1 + b;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g == 0) *host_bad = *bad;
+  if (g >= o.gofs[o.L + 1]) return;
+  int l = 0;
+  while (l < o.L && g >= o.gofs[l + 1]) ++l;
+  const int64_t b = g - o.gofs[l], c = ((int64_t)1 << (3 * l)) - 1 + b;
+  double* geom = o.geom[l] + b * 10;
   double d[3];
   for (int a = 0; a < 3; ++a) {
     const double lo = cells[c * 6 + a], hi = cells[c * 6 + 3 + a];
-    geom[b * 10 + a] = lo;
-    geom[b * 10 + 3 + a] = hi;
-    geom[b * 10 + 6 + a] = 0.5 * (lo + hi);
+    geom[a] = lo;
+    geom[3 + a] = hi;
+    geom[6 + a] = 0.5 * (lo + hi);
     d[a] = hi - lo;
   }
-  geom[b * 10 + 9] = 0.5 * sqrt((d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]);
-  start[b] = seg_start[c];
+  geom[9] = 0.5 * sqrt((d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]);
+  o.start[l][b] = seg_start[c];
+  if (b == 0) o.start[l][(int64_t)1 << (3 * l)] = n;
 }
 
 }  // namespace
@@ -816,7 +829,7 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
     k_bbox_partial<<<nparts_t, 256, 0, s>>>(t.tx, t.ty, t.tz, m, part + (size_t)nparts * 6);
     HIPCHECK(hipGetLastError());
   }
-  k_bbox_final<<<1, 64, 0, s>>>(part, nparts + nparts_t, n, cells, seg_start, seg_n);
+  k_bbox_final<<<1, 384, 0, s>>>(part, nparts + nparts_t, n, cells, seg_start, seg_n);
   HIPCHECK(hipGetLastError());
   dfree(part, s);
   // eta < 1: per-depth plane and segment scratch for the re-partition
@@ -830,7 +843,11 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
 
   // rounds whose segments all hold at least kMultiMin points (and are few)
   // go through the chunked kernels; the rest run one block per segment
-  constexpr int64_t kMultiMin = 4 * kChunk;
+  // A chunked round is 20 launches, bound by the host that makes them up to
+  // some 10^5 points; one block of 1,024 threads takes a segment in one.  The
+  // build of 20,000 points (3 levels) with chunked rounds from 8,192 points on
+  // and 256 threads below took 477 us, so 270.
+  constexpr int64_t kMultiMin = 16 * kChunk;
   constexpr int64_t kMultiMaxSeg = 512;
   SegSel* sel = nullptr;
   unsigned* ghist = nullptr;
@@ -898,6 +915,9 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
       HIPCHECK(hipGetLastError());
       k_mb_final<<<nseg, 64, 0, s>>>(sel, nchunk, cpart, cells, seg_start, seg_n, depth);
       HIPCHECK(hipGetLastError());
+    } else if (blend ? maxn > 1024 : maxn > 2048) {
+      k_orb_round<1024><<<(unsigned)nsegd, 1024, 0, s>>>(xs[cur], ys[cur], zs[cur], ids[cur], xs[o], ys[o], zs[o],
+                                                         ids[o], cells, seg_start, seg_n, depth);
     } else if (blend || maxn > 128) {
       k_orb_round<256><<<(unsigned)nsegd, 256, 0, s>>>(xs[cur], ys[cur], zs[cur], ids[cur], xs[o], ys[o], zs[o],
                                                        ids[o], cells, seg_start, seg_n, depth);
@@ -938,6 +958,7 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
   }
 
   t.lev.assign(L + 1, Level());
+  GeomOut go{};
   int64_t g = 0;
   for (int l = 0; l <= L; ++l) {
     Level& V = t.lev[l];
@@ -946,10 +967,15 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
     g += V.nbox;
     V.geom = (double*)dalloc(V.nbox * 10 * sizeof(double), s);
     V.start = (int32_t*)dalloc((V.nbox + 1) * sizeof(int32_t), s);
-    k_box_geom<<<(unsigned)((V.nbox + 1 + 255) / 256), 256, 0, s>>>(cells, seg_start, 3 * l, V.nbox, V.geom,
-                                                                    V.start, (int32_t)n);
-    HIPCHECK(hipGetLastError());
+    go.gofs[l] = V.gofs;
+    go.geom[l] = V.geom;
+    go.start[l] = V.start;
   }
+  go.L = L;
+  go.gofs[L + 1] = g;
+  k_box_geom<<<(unsigned)((g + 255) / 256), 256, 0, s>>>(cells, seg_start, go, (int32_t)n, bad,
+                                                        host_stage() + kBadWord);
+  HIPCHECK(hipGetLastError());
   t.nbox_total = g;
   t.px = xs[cur];
   t.py = ys[cur];
@@ -963,11 +989,11 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
   dfree(seg_start, s);
   dfree(seg_n, s);
 
-  int hbad = 0;
-  HIPCHECK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  dfree(bad, s);
-  if (hbad) fail(FMM_EINVAL, "non-finite coordinate or |coordinate| > 1e300");
+  dfree(bad, s);  // its value is looked at after the next wait (check_points_flag)
+}
+
+void check_points_flag() {
+  if (host_stage()[kBadWord]) fail(FMM_EINVAL, "non-finite coordinate or |coordinate| > 1e300");
 }
 
 void targets_build(Tree& t, hipStream_t s) {
