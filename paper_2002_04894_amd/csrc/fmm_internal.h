@@ -15,8 +15,8 @@ constexpr int kWave = 64;
 constexpr int kMaxLevels = FMM_MAX_LEVELS;
 constexpr int kMaxOrder = FMM_MAX_ORDER;
 // M2M and L2L run four lanes per translation on the matrix cores up to this
-// order (two waves per SIMD), the generic binary64 translation above
-constexpr int kQuadXlateMaxP = 13;
+// order (as far as the table holds J^T), the generic binary64 translation above
+constexpr int kQuadXlateMaxP = 18;
 
 // M2L work order (lists.hip, m2l_queue.h): from this many targets on siblings
 // stay together; the waves that run at once, about

@@ -38,7 +38,7 @@
 // in 16x16 tiles of two degree blocks 178 and 190 at orders 14 and 15.
 //
 // The same steps with the M2M or L2L core along z make k_xlate_quad (end of
-// the file), which runs M2M and L2L up to order 13.
+// the file), which runs M2M and L2L up to order 18.
 #include <type_traits>
 
 #include "fmm_internal.h"
@@ -587,8 +587,9 @@ k_xlate_quad(LevelView lv, int l, const double* __restrict__ qtab, const int* __
   const int tl = 4 * k + (lane & 3);
   const double* gch = lv.geom[l];
   const double* gpa = lv.geom[l - 1];
+  // few groups are spread over blocks first: a wave by itself on its SIMD
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t cg = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); cg < ngroup; cg += nw) {
+  for (int64_t cg = (int64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x; cg < ngroup; cg += nw) {
     const int64_t ch = 16 * cg + q, par = ch >> 3;
     const double dx = gch[ch * 10 + 6] - gpa[par * 10 + 6];
     const double dy = gch[ch * 10 + 7] - gpa[par * 10 + 7];
@@ -681,8 +682,7 @@ void launch_one_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStre
     HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_xlate_quad<P, L2L>, QuadCfg<P>::kThreads, 0));
     return ncu * (per > 0 ? per : 1);
   }();
-  const int64_t need = (ngroup + QuadCfg<P>::kThreads / 64 - 1) / (QuadCfg<P>::kThreads / 64);
-  const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
+  const unsigned grid = (unsigned)(ngroup < grid_max ? ngroup : grid_max);
   k_xlate_quad<P, L2L><<<grid, QuadCfg<P>::kThreads, 0, s>>>(t.view(), l, L2L ? tb.quad_l2l : tb.quad_m2m, tb.pos,
                                                               tb.ipos, tb.stride, E, ngroup);
   HIPCHECK(hipGetLastError());
@@ -705,9 +705,14 @@ bool launch_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStream_t
     case 11: launch_one_xlate<11, L2L>(t, l, tb, E, s); break;
     case 12: launch_one_xlate<12, L2L>(t, l, tb, E, s); break;
     case 13: launch_one_xlate<13, L2L>(t, l, tb, E, s); break;
+    case 14: launch_one_xlate<14, L2L>(t, l, tb, E, s); break;
+    case 15: launch_one_xlate<15, L2L>(t, l, tb, E, s); break;
+    case 16: launch_one_xlate<16, L2L>(t, l, tb, E, s); break;
+    case 17: launch_one_xlate<17, L2L>(t, l, tb, E, s); break;
+    case 18: launch_one_xlate<18, L2L>(t, l, tb, E, s); break;
     default: return false;
   }
-  static_assert(kQuadXlateMaxP == 13, "the cases above cover orders 0 .. kQuadXlateMaxP");
+  static_assert(kQuadXlateMaxP == 18, "the cases above cover orders 0 .. kQuadXlateMaxP");
   return true;
 }
 
