@@ -144,7 +144,8 @@ struct Tree {
   int64_t p2p_ntpart = 0;
   // memory and stream bookkeeping (api.hip)
   Allocator alloc;                 // allocator of the tree's own device memory
-  size_t bytes = 0;                // device bytes the tree owns
+  std::vector<std::pair<void*, size_t>> blocks;  // the device memory the tree owns
+  size_t bytes = 0;                // and its bytes
   hipEvent_t built = nullptr;      // recorded on the build stream when the build is enqueued
   hipStream_t build_stream = nullptr;
   std::vector<std::pair<hipStream_t, hipEvent_t>> uses;  // last evaluation enqueued on each stream
@@ -220,6 +221,9 @@ size_t noalloc_scratch_bytes();
 // peak scratch bytes of one evaluation (evaluate, plus evaluate_targets when
 // the tree has targets) at order p and precision prec
 size_t eval_scratch_bytes(const Tree& t, int p, int prec);
+// the same cut out of one block (no buffer is used twice but M2L's copy)
+size_t arena_bytes(const Tree& t, int p, int prec);
+constexpr size_t kOneBlock = (size_t)32 << 20;  // evaluations up to this take one block
 
 // exclusive scan of int32 counts into int64 offsets (out[n] = total + base)
 void scan_counts(const int32_t* in, int64_t* out, int64_t n, int64_t base, hipStream_t s);

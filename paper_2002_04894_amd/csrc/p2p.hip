@@ -686,7 +686,9 @@ void far_field(const Tree& t, const double* qt, int p, int prec, const int32_t* 
   PhaseTimer& tm = timer();
   const Tables& tb = tables_for(p, s);
   double* Mx = (double*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(double), s);
-  double* Lx = (double*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(double), s);
+  // M2L reads its own copy of the multipoles and writes every local expansion
+  // of levels 1..L, which take the multipoles' place
+  double* Lx = Mx;
   tm.begin(FMM_PH_P2M, s);
   launch_p2m(t, tb, qt, Mx, s);
   tm.end(FMM_PH_P2M, s);
@@ -705,7 +707,6 @@ void far_field(const Tree& t, const double* qt, int p, int prec, const int32_t* 
   launch_l2p(t, tb, Lx, start, px, py, pz, far[0], far[1], far[2], far[3], s);
   tm.end(FMM_PH_L2P, s);
   dfree(Mx, s);
-  dfree(Lx, s);
 }
 
 // Near field (P2P) at the points grouped by leaf as [start[b], start[b+1]) of
@@ -785,10 +786,12 @@ void evaluate(const Tree& t, const double* q, int p, int parts, int prec, double
   dfree(qt, s);
 }
 
-size_t eval_scratch_bytes(const Tree& t, int p, int prec) {
-  // what evaluate() allocates, at its peak: the charges all along, then the
-  // expansions with M2L's copy of the multipoles and its queue, the expansions
-  // with the far field, or the far field with the near field's partial sums
+namespace {
+// What evaluate() holds: the charges all along; the expansions with M2L's copy
+// of the multipoles and its queue, then the expansions with the far field, then
+// the far field with the near field's partial sums.  In one block the
+// expansions' place is not used again.
+size_t scratch_bytes(const Tree& t, int p, int prec, bool one_block) {
   const size_t stride = p <= tl::kMaxP ? (size_t)tl::stride(p) : (size_t)nterms(p);
   const size_t nbox = (size_t)t.nbox_total;
   // the copy, per box: binary32 dense (per-lane kernel, orders up to 14) or
@@ -800,12 +803,24 @@ size_t eval_scratch_bytes(const Tree& t, int p, int prec) {
   auto one = [&](int64_t npts, int64_t npart) {
     const size_t part = (size_t)std::max<int64_t>(0, npart) * 32;
     if (t.L == 0) return (size_t)t.n * 8 + part;
-    const size_t expn = 2 * nbox * stride * 8, far = 4 * (size_t)std::max<int64_t>(1, npts) * 8;
-    return (size_t)t.n * 8 + std::max({expn + 256 + nbox * copy, expn + far, far + part});
+    const size_t expn = nbox * stride * 8, far = 4 * (size_t)std::max<int64_t>(1, npts) * 8;
+    const size_t m2l = expn + 256 + nbox * copy;
+    return (size_t)t.n * 8 + (one_block ? std::max(m2l, expn + far + part) : std::max({m2l, expn + far, far + part}));
   };
   size_t b = one(t.n, t.p2p_npart);
   if (t.m > 0) b = std::max(b, one(t.m, t.p2p_ntpart));
   return b;
+}
+}  // namespace
+
+size_t arena_bytes(const Tree& t, int p, int prec) {
+  // at most 12 buffers; each may lose 255 bytes to alignment
+  return scratch_bytes(t, p, prec, true) + 12 * 256;
+}
+
+size_t eval_scratch_bytes(const Tree& t, int p, int prec) {
+  const size_t a = arena_bytes(t, p, prec);
+  return a <= kOneBlock ? a : scratch_bytes(t, p, prec, false);
 }
 
 // phi and E at the tree's separate targets (outputs in the caller's target
