@@ -666,13 +666,21 @@ __global__ __launch_bounds__(64) void k_l2l(LevelView lv, int l, int64_t nbox, X
   store_coefs(acc, dst, tb);
 }
 
-// ---- P2M: one 64-lane workgroup per leaf, lanes over points ----
+// ---- P2M: one workgroup of W waves per leaf, lanes over points, 64 points
+// per wave and pass ----
 // For each order m every lane puts its point's terms of degrees m..p (cosine
 // and sine parts: the columns) into one LDS row; then each column is summed
 // over the 64 rows in a fixed order by g lanes (g the largest power of two
 // with g * columns <= 64), each adding every g-th row, and g - 1 exchanges
 // add their partial sums.  The row stride p2m_stride(p) is odd, so the row
 // writes and the column reads are free of bank conflicts.
+// Bound by latency: a wave's chain over the orders, 64 points at a time (64
+// leaves at order 12 take 19 us, 27 with the constants in global memory), in
+// long launches by LDS (2^24 points at order 12 2.75 ms either way).  Up to
+// kP2MShare leaves several waves take a leaf: 100,000 points off the median in
+// 512 leaves 279 -> 81 us, 47,003 points 45 -> 28; with 4,096 leaves, which
+// fill the chip, 18 -> 44 us at order 6 and 108 -> 212 at order 16.
+constexpr int64_t kP2MShare = 512;
 __host__ __device__ constexpr int p2m_stride(int p) { return 2 * (p + 1) + 1; }
 
 // The recurrence's constants (c1, c2) of (n, m), in the order in which P2M and
@@ -682,18 +690,26 @@ __device__ __forceinline__ void stage_rec(const XT& tb, double2* cc) {
   const int p = tb.p, P1 = p + 1;
   const double* c1 = tb.rc + 2 * P1;
   const double* c2 = c1 + P1 * P1;
-  for (int k = threadIdx.x; k < P1 * P1; k += 64) {
+  for (int k = threadIdx.x; k < P1 * P1; k += blockDim.x) {
     const int n = k / P1, m = k % P1;
     // terms before order m: sum over a < m of (p - 1 - a)
     if (n >= m + 2) cc[m * (p - 1) - m * (m - 1) / 2 + n - m - 2] = make_double2(c1[k], c2[k]);
   }
 }
 
-__global__ __launch_bounds__(64) void k_p2m(LevelView lv, XT tb, const double* __restrict__ px,
+// the wave's LDS accesses before are done before those after
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const double* __restrict__ px,
                                             const double* __restrict__ py, const double* __restrict__ pz,
                                             const double* __restrict__ qt, double* __restrict__ Mx) {
-  extern __shared__ __align__(16) double rows[];  // (c1, c2), 64 x p2m_stride(p), then the sums (tb.nt)
-  const int lane = threadIdx.x;
+  extern __shared__ __align__(16) double rows[];  // (c1, c2), then per wave 64 x p2m_stride(p) and the sums (tb.nt)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int L = lv.L, p = tb.p, P1 = p + 1, nt = tb.nt;
   const int64_t b = blockIdx.x;
   const double* g = lv.geom[L] + b * 10;
@@ -704,13 +720,14 @@ __global__ __launch_bounds__(64) void k_p2m(LevelView lv, XT tb, const double* _
   const double s2 = 1.4142135623730951;
   const int SP = p2m_stride(p);
   double2* cc = (double2*)rows;
-  double* tab = rows + P1 * P1;
+  const int per = 64 * SP + nt;  // doubles per wave
+  double* tab = rows + P1 * P1 + wave * per;
   double* row = tab + lane * SP;
   double* acc = tab + 64 * SP;
   for (int k = lane; k < nt; k += 64) acc[k] = 0.0;
   stage_rec(tb, cc);
   __syncthreads();
-  for (int c0 = s0; c0 < s1; c0 += 64) {
+  for (int c0 = s0 + 64 * wave; c0 < s1; c0 += 64 * W) {
     const int t = c0 + lane;
     const bool valid = t < s1;
     const int nrow = s1 - c0 < 64 ? s1 - c0 : 64;  // rows of points
@@ -758,7 +775,7 @@ __global__ __launch_bounds__(64) void k_p2m(LevelView lv, XT tb, const double* _
           row[2 * (n - m) + 1] = sq * ai;
         }
       }
-      __syncthreads();
+      wave_lds_fence();
       // column col = 2 (n - m) + part of every row that holds a point; g lanes
       // per column
       const int ncol = 2 * (P1 - m);
@@ -771,16 +788,25 @@ __global__ __launch_bounds__(64) void k_p2m(LevelView lv, XT tb, const double* _
       for (int d = 1; d < g; d <<= 1) v += __shfl_xor(v, d);
       const int n = m + (col >> 1), part = col & 1;
       if (col < ncol && sub == 0 && (m > 0 || part == 0)) acc[cidx(n, m, part)] += v;
-      __syncthreads();
+      wave_lds_fence();
     }
   }
   __syncthreads();
+  if constexpr (W > 1) {  // the waves' sums, in wave order
+    if (wave > 0) return;
+    for (int k = lane; k < nt; k += 64)
+      for (int w = 1; w < W; ++w) acc[k] += acc[w * per + k];
+    wave_lds_fence();
+  }
   store_coefs(acc, Mx + (size_t)(lv.gofs[L] + b) * tb.stride, tb);
 }
 
 // ---- L2P: far field at the points of each leaf (phi and E = -grad phi) ----
 // The evaluation points of leaf b are [start[b], start[b+1]) of (px, py, pz):
-// the leaf's own sources, or the separate targets grouped by leaf.
+// the leaf's own sources, or the separate targets grouped by leaf.  Bound by
+// the chain of the recurrence and, in long launches, by binary64 issue: 64
+// leaves at order 12 21 us, 2^24 points 2.0 ms (33 us and 3.6 ms with
+// constants and coefficients read from global memory at every step).
 __global__ __launch_bounds__(64) void k_l2p(LevelView lv, XT tb, const int32_t* __restrict__ start,
                                             const double* __restrict__ px, const double* __restrict__ py,
                                             const double* __restrict__ pz, const double* __restrict__ Lx,
@@ -888,16 +914,29 @@ __global__ __launch_bounds__(64) void k_l2p(LevelView lv, XT tb, const int32_t* 
 
 // launch helpers used by evaluate() (p2p.hip)
 void launch_p2m(const Tree& t, const Tables& tb, const double* qt, double* Mx, hipStream_t s) {
-  const size_t lds = ((size_t)64 * p2m_stride(tb.p) + 2 * nterms(tb.p)) * sizeof(double);
-  k_p2m<<<(unsigned)t.lev[t.L].nbox, 64, lds, s>>>(t.view(), make_xt(tb), t.px, t.py, t.pz, qt, Mx);
+  const int64_t nleaf = t.lev[t.L].nbox;
+  auto lds = [&](int w) { return (nterms(tb.p) + w * ((size_t)64 * p2m_stride(tb.p) + nterms(tb.p))) * sizeof(double); };
+  auto go = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    k_p2m<W><<<(unsigned)nleaf, 64 * W, lds(W), s>>>(t.view(), make_xt(tb), t.px, t.py, t.pz, qt, Mx);
+  };
+  // few leaves leave most SIMDs idle, and leaves of very different sizes wait
+  // for the largest: four waves per leaf (two above order 12, by their LDS)
+  if (nleaf > kP2MShare)
+    go(std::integral_constant<int, 1>{});
+  else if (lds(4) <= (size_t)64 << 10)
+    go(std::integral_constant<int, 4>{});
+  else
+    go(std::integral_constant<int, 2>{});
   HIPCHECK(hipGetLastError());
 }
 bool launch_m2m_quad64(const Tree& t, int l, const Tables& tb, double* Mx, hipStream_t s);
 bool launch_l2l_quad64(const Tree& t, int l, const Tables& tb, double* Lx, hipStream_t s);
 
 // M2M and L2L four lanes per translation on the matrix cores up to order
-// kQuadXlateMaxP (order 16, 4,096 leaves: 1,790 + 190 us with the generic
-// translation, which runs above)
+// kQuadXlateMaxP (M2M + L2L of 4,096 leaves at order 16 112 + 176 us, of
+// 32,768 at order 15 168 + 315; the generic translation, which runs above,
+// took 1,790 + 190 and 2,007 + 660)
 void launch_m2m(const Tree& t, int l, const Tables& tb, double* Mx, hipStream_t s) {
   if (launch_m2m_quad64(t, l, tb, Mx, s)) return;
   const size_t lds = 3 * (size_t)nterms(tb.p) * sizeof(double);
