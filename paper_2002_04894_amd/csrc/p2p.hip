@@ -314,7 +314,8 @@ struct P2POut {
   }
 };
 
-// The targets [t0, t1) of a leaf against the segment; red: 4 T W 64 doubles of
+// The targets [t0, t1) of a leaf against the segment, T TT of them per pass, the
+// passes dealt to the blocks in y (the same sums as in one block); red: 4 T W 64 doubles of
 // LDS for the sums of the waves (W > 1; it may be the waves' buffers).
 template <bool F32, int T, int W, class V>
 __device__ __forceinline__ void p2p_targets(const P2PSeg& sg, int t0, int t1, int TT, int R, V* buf, double* red,
@@ -326,7 +327,7 @@ __device__ __forceinline__ void p2p_targets(const P2PSeg& sg, int t0, int t1, in
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tl = lane % TT, h = lane / TT;
   const bool lane_on = h < R;
-  for (int c0 = t0; c0 < t1; c0 += T * TT) {
+  for (int c0 = t0 + (int)blockIdx.y * T * TT; c0 < t1; c0 += (int)gridDim.y * T * TT) {
     double f[T][4] = {};
     double x[T], y[T], z[T];
 #pragma unroll
@@ -527,6 +528,8 @@ __global__ __launch_bounds__(64 * W) void k_p2p(
   const int64_t e0 = seg_e0[g], e1 = r + 1 < ns ? seg_e0[g + 1] : s_off[b + 1];
   const int t0 = tstart[b], t1 = tstart[b + 1];
   const int nt = t1 - t0;
+  const P2PSplit sp = F32 ? P2PSplit{2, nt <= 16 ? 8 : (nt <= 32 ? 16 : (nt <= 64 ? 32 : 64)), 0} : p2p_split(nt);
+  if (blockIdx.y > 0 && (int64_t)blockIdx.y * sp.T * sp.TT >= nt) return;  // no pass left for this block
   const P2PSeg sg{s_idx + e0, start, (int)(e1 - e0), ebase, ecnt};
   for (int i = threadIdx.x; i < sg.ne && i < kP2PEntries; i += 64 * W) {
     const int j = sg.s_idx[i], u = start[j];
@@ -539,10 +542,8 @@ __global__ __launch_bounds__(64 * W) void k_p2p(
   double* red = (double*)(F32 ? lds + W * kBytes : lds);
   if constexpr (F32) {
     const double ccx = lgeom[b * 10 + 6], ccy = lgeom[b * 10 + 7], ccz = lgeom[b * 10 + 8];
-    const int TT = nt <= 16 ? 8 : (nt <= 32 ? 16 : (nt <= 64 ? 32 : 64));
-    p2p_targets<true, 2, W>(sg, t0, t1, TT, 64 / TT, buf, red, px, py, pz, qt, tx, ty, tz, ccx, ccy, ccz, out);
+    p2p_targets<true, 2, W>(sg, t0, t1, sp.TT, 64 / sp.TT, buf, red, px, py, pz, qt, tx, ty, tz, ccx, ccy, ccz, out);
   } else {
-    const P2PSplit sp = p2p_split(nt);
     auto go = [&](auto t) __attribute__((always_inline)) {
       p2p_targets<false, decltype(t)::value, W>(sg, t0, t1, sp.TT, sp.R, buf, red, px, py, pz, qt, tx, ty, tz, 0.0, 0.0,
                                                 0.0, out);
@@ -724,8 +725,17 @@ void near_field_and_store(const Tree& t, const double* qt, int parts, int prec, 
   if (parts & FMM_PART_NEAR) {
     double4* part = npart > 0 ? (double4*)dalloc(npart * sizeof(double4), s) : nullptr;
     const unsigned grid = (unsigned)(8 * ((t.p2p_nseg + 7) / 8));
+    // A block takes its leaf's targets 64 to 256 at a time; where leaves may
+    // hold more (cells off the median, separate targets, few levels) and the
+    // segments alone leave the chip idle, blocks in y share these passes: the
+    // largest leaf held the launch (30,011 targets, 512 leaves off the median
+    // 1,750 -> 993 us; blocks without a pass end at once).
+    const bool even = start == V.start && t.eta == 1.0;
+    const int64_t most = even ? (t.n + V.nbox - 1) / V.nbox : INT64_MAX;  // targets of a leaf
+    const int64_t cap = t.p2p_nseg <= 2048 ? 16 : t.p2p_nseg <= 16384 ? 4 : 1;
+    const unsigned gy = most <= (prec == FMM_PREC_F32 ? 128 : 256) ? 1 : (unsigned)std::min(cap, (most - 1) / 64 + 1);
     auto go = [&](auto f32, auto w) {
-      k_p2p<decltype(f32)::value, decltype(w)::value><<<grid, 64 * decltype(w)::value, 0, s>>>(
+      k_p2p<decltype(f32)::value, decltype(w)::value><<<dim3(grid, gy), 64 * decltype(w)::value, 0, s>>>(
           t.p2p_nseg, t.p2p_seg_leaf, t.p2p_seg_e0, t.p2p_leaf_seg, leaf_part, V.start, V.s_off, V.s_idx, t.px, t.py,
           t.pz, qt, start, px, py, pz, perm, far[0], far[1], far[2], far[3], part, pot, ex, ey, ez, V.geom);
     };
