@@ -36,9 +36,8 @@ LANE_M2L_MAX_P = 14            # mixed precision: the per-lane M2L kernel up to 
 
 
 def quad_m2l(p: int) -> bool:
-    """binary64 M2L runs four lanes per pair at these orders (16x16 tiles at
-    14 and 15)"""
-    return p <= 13 or 16 <= p <= 20
+    """binary64 M2L runs four lanes per pair at these orders"""
+    return 0 <= p <= 20
 HBM_PEAK_GBS = 8000.0
 
 # HBM traffic of one M2L launch, per kernel and workload: from two rocprofv3
@@ -52,20 +51,20 @@ COPY_WRITE_SCALE = 1.0
 M2L_COUNTERS: dict = {  # (kernel, n, theta) -> {"sources_sha256", "fetch_kib", "write_kib"}
     # profiles/m2l_counters_plummer134m.md (theta 0.6, p 12): mixed precision and binary64
     ("k_m2l_lane<12>", 1 << 27, 0.6): {
-        "sources_sha256": "1e390d48b53daa9cf247241abb1bb3e2ea4ac8e19a66424d12fd0d64fb5aefd5",
-        "fetch_kib": 3976133030.875,
-        "write_kib": 479565723.84375,
+        "sources_sha256": "3cd92d4759a611a1cad4868b2ea6d7fff781341505d3bb86bbb7fd80ac579a2e",
+        "fetch_kib": 1993446604.625,
+        "write_kib": 6232508.90625,
     },
     ("k_m2l_quad<12>", 1 << 27, 0.6): {
-        "sources_sha256": "7506a256e0c87c880341bd40c953d8f76270fd36dfee7dc9c089359c5c6d4cc4",
-        "fetch_kib": 10978627894.625,
-        "write_kib": 20261523.8125,
+        "sources_sha256": "17d14efcd5f20ce184882c2bc953cbb6ed00e3cbf19a2db67c7f874df8514b97",
+        "fetch_kib": 6458831153.5,
+        "write_kib": 4291872.34375,
     },
-    # the binary64 leg's tuned setting (theta 0.55, p 10)
+    # binary64 at theta 0.55, p 10
     ("k_m2l_quad<10>", 1 << 27, 0.55): {
-        "sources_sha256": "7506a256e0c87c880341bd40c953d8f76270fd36dfee7dc9c089359c5c6d4cc4",
-        "fetch_kib": 8859291027.4375,
-        "write_kib": 6013182.5,
+        "sources_sha256": "17d14efcd5f20ce184882c2bc953cbb6ed00e3cbf19a2db67c7f874df8514b97",
+        "fetch_kib": 6909006802.0,
+        "write_kib": 3678283.53125,
     },
 }
 
@@ -73,8 +72,8 @@ M2L_COUNTERS: dict = {  # (kernel, n, theta) -> {"sources_sha256", "fetch_kib", 
 def m2l_sources_sha256(kernel: str) -> str:
     import hashlib
     h = hashlib.sha256()
-    files = {"k_m2l_lane": ("m2l_lane.hip", "lane_ops.h"), "k_m2l_quad": ("m2l_quad.hip", "lane_ops.h")}.get(
-        kernel.split("<")[0], ("m2l_mfma.hip",))
+    files = {"k_m2l_lane": ("m2l_lane.hip", "lane_ops.h", "m2l_queue.h"),
+             "k_m2l_quad": ("m2l_quad.hip", "lane_ops.h", "m2l_queue.h")}.get(kernel.split("<")[0], ("m2l_mfma.hip",))
     for f in files + ("tile_layout.h",):
         with open(os.path.join(ROOT, "paper_2002_04894_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())

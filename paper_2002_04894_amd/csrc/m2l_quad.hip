@@ -18,7 +18,7 @@
 //     so every step's result is the next step's operand in place; the
 //     operator values come from LDS (binary64 instructions take no broadcast
 //     of one block's operand, so every lane reads its value); the parts that
-//     join orders of the wrong parity are zero and left out (368 instead of
+//     join orders of the wrong parity are zero and left out (360 instead of
 //     576 instructions per batch at order 12); J^T has a
 //     table of its own up to order 18 and above reads the table of J with
 //     the two chunk indices swapped and each 4x4 part transposed;
