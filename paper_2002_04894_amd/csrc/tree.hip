@@ -30,6 +30,11 @@ __device__ __forceinline__ uint64_t okey(double c) {
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
+// A coordinate that is not acceptable (the build is refused for it when the
+// host next looks at the flag) is read as zero meanwhile: the rounds enqueued
+// before rely on finite points inside their cells.  A NaN matches no digit of
+// its segment's bounds, and the select of a segment of two such points would
+// not end.
 __global__ void k_canon_copy(const double* __restrict__ x, const double* __restrict__ y,
                              const double* __restrict__ z, double* __restrict__ ox, double* __restrict__ oy,
                              double* __restrict__ oz, int32_t* __restrict__ oid, int64_t n, int* bad) {
@@ -37,10 +42,11 @@ __global__ void k_canon_copy(const double* __restrict__ x, const double* __restr
   if (i >= n) return;
   const double a = x[i] + 0.0, b = y[i] + 0.0, c = z[i] + 0.0;
   const double lim = 1e300;
-  if (!(fabs(a) <= lim && fabs(b) <= lim && fabs(c) <= lim)) atomicOr(bad, 1);
-  ox[i] = a;
-  oy[i] = b;
-  oz[i] = c;
+  const bool ok = fabs(a) <= lim && fabs(b) <= lim && fabs(c) <= lim;
+  if (!ok) atomicOr(bad, 1);
+  ox[i] = ok ? a : 0.0;
+  oy[i] = ok ? b : 0.0;
+  oz[i] = ok ? c : 0.0;
   oid[i] = (int32_t)i;
 }
 
