@@ -16,6 +16,7 @@
 
 #include "fmm_internal.h"
 #include "lane_ops.h"
+#include "launch_rules.h"
 #include "tile_layout.h"
 
 namespace fmm {
@@ -740,17 +741,10 @@ void near_field_and_store(const Tree& t, const double* qt, int parts, int prec, 
           t.pz, qt, start, px, py, pz, perm, far[0], far[1], far[2], far[3], part, pot, ex, ey, ez, V.geom);
     };
     auto go_w = [&](auto f32) {
-      // Waves per segment: about four on every SIMD (1,024 of them).  One wave
-      // takes 150 us over a full segment, so few segments left the launch
-      // waiting for single waves; with many, more waves per segment only add
-      // barriers.  Measured, one wave / here: 20,000 uniform points, 512 leaves
-      // 228 / 88 us (of which the split of the lanes a third), 47,003 points on
-      // a sphere 1,001 / 531, 3,000 points binary32 141 / 35; from 2,048
-      // segments on within 2 % (issue-bound: 1.42e12 interactions/s on 2^22
-      // Plummer points).
-      if (t.p2p_nseg <= 512)
+      const int w = rules::p2p_waves(t.p2p_nseg, V.s_nnz, decltype(f32)::value);
+      if (w == 8)
         go(f32, std::integral_constant<int, 8>{});
-      else if (t.p2p_nseg <= 2048)
+      else if (w == 4)
         go(f32, std::integral_constant<int, 4>{});
       else
         go(f32, std::integral_constant<int, 1>{});
