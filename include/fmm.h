@@ -161,8 +161,8 @@ fmm_status fmm_evaluate_tree_ex(fmm_tree* tree, const double* q, int p, int part
  *   - FMM_EINVAL when the evaluation needs more scratch than the array holds
  *     (the charges, and the larger of the expansions with M2L's copy of them
  *     and the expansions with the far field and the near field's partial
- *     sums; checked before any work is enqueued; about 2e5 points at 4 levels
- *     and p = 12 fit).
+ *     sums, of these what the parts asked for need; checked before any work
+ *     is enqueued; about 2e5 points at 4 levels and p = 12 fit).
  *   - FMM_EUNSUPPORTED when the operator tables of order p are not on the
  *     device yet: one evaluation at order p through an allocating entry point
  *     makes them.

@@ -513,7 +513,8 @@ fmm_status fmm_evaluate_targets(fmm_tree* tree, const double* q, int p, int part
     if (precision != FMM_PREC_F64 && precision != FMM_PREC_MIXED && precision != FMM_PREC_F32)
       fail(FMM_EINVAL, "unknown precision");
     hipStream_t s = (hipStream_t)stream;
-    run_evaluation(t, s, t.m > 0 ? fmm::arena_bytes(t, p, precision) : 0, [&] { fmm::evaluate_targets(t, q, p, parts, precision, pot, ex, ey, ez, s); });
+    run_evaluation(t, s, t.m > 0 ? fmm::arena_bytes(t, p, precision, parts, true) : 0,
+                   [&] { fmm::evaluate_targets(t, q, p, parts, precision, pot, ex, ey, ez, s); });
   });
 }
 
@@ -537,7 +538,8 @@ fmm_status fmm_evaluate_tree_ex(fmm_tree* tree, const double* q, int p, int part
     if (precision != FMM_PREC_F64 && precision != FMM_PREC_MIXED && precision != FMM_PREC_F32)
       fail(FMM_EINVAL, "unknown precision");
     hipStream_t s = (hipStream_t)stream;
-    run_evaluation(t, s, fmm::arena_bytes(t, p, precision), [&] { fmm::evaluate(t, q, p, parts, precision, pot, ex, ey, ez, s); });
+    run_evaluation(t, s, fmm::arena_bytes(t, p, precision, parts, false),
+                   [&] { fmm::evaluate(t, q, p, parts, precision, pot, ex, ey, ez, s); });
   });
 }
 
@@ -575,7 +577,8 @@ fmm_status fmm_evaluate(const double* x, const double* y, const double* z, const
       fmm::Tree& t;
       ~Rel() { fmm::release(t); }
     } rel{h->t};
-    run_evaluation(h->t, s, fmm::arena_bytes(h->t, p, FMM_PREC_F64), [&] { fmm::evaluate(h->t, q, p, FMM_PART_ALL, FMM_PREC_F64, pot, ex, ey, ez, s); });
+    run_evaluation(h->t, s, fmm::arena_bytes(h->t, p, FMM_PREC_F64, FMM_PART_ALL, false),
+                   [&] { fmm::evaluate(h->t, q, p, FMM_PART_ALL, FMM_PREC_F64, pot, ex, ey, ez, s); });
   });
 }
 

@@ -221,8 +221,9 @@ size_t noalloc_scratch_bytes();
 // peak scratch bytes of one evaluation (evaluate, plus evaluate_targets when
 // the tree has targets) at order p and precision prec
 size_t eval_scratch_bytes(const Tree& t, int p, int prec);
-// the same cut out of one block (no buffer is used twice but M2L's copy)
-size_t arena_bytes(const Tree& t, int p, int prec);
+// what the given parts at the sources, or at the separate targets, take cut out
+// of one block (no buffer is used twice but M2L's copy)
+size_t arena_bytes(const Tree& t, int p, int prec, int parts, bool targets);
 // Evaluations of up to this much take one block: enqueueing one takes 54 us at
 // 1,000 points, 193 with an allocation per buffer; beyond, the block would hold
 // memory that separate buffers use twice, and the call takes milliseconds.

@@ -55,7 +55,7 @@ size_t noalloc_scratch_bytes() { return kScratchBytes; }
 // aligned; the limit is checked before anything is enqueued.
 void evaluate_noalloc(const Tree& t, const double* q, int p, int parts, int prec, double* pot, double* ex,
                       double* ey, double* ez, hipStream_t s) {
-  const size_t need = arena_bytes(t, p, prec);
+  const size_t need = arena_bytes(t, p, prec, parts, false);
   if (need > kScratchBytes)
     fail(FMM_EINVAL, "this evaluation needs " + std::to_string(need) + " bytes of scratch; the fixed buffer holds " +
                          std::to_string(kScratchBytes));

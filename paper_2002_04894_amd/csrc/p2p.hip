@@ -791,11 +791,15 @@ void evaluate(const Tree& t, const double* q, int p, int parts, int prec, double
 }
 
 namespace {
-// What evaluate() holds: the charges all along; the expansions with M2L's copy
-// of the multipoles and its queue, then the expansions with the far field, then
-// the far field with the near field's partial sums.  In one block the
-// expansions' place is not used again.
-size_t scratch_bytes(const Tree& t, int p, int prec, bool one_block) {
+// What an evaluation of the given parts at npts points holds: the charges all
+// along; for the far field the expansions with M2L's copy of the multipoles and
+// its queue, then the expansions with the far field, then the far field with
+// the near field's partial sums.  In one block the expansions' place is not
+// used again.
+size_t scratch_bytes(const Tree& t, int p, int prec, int parts, int64_t npts, int64_t npart, bool one_block) {
+  const size_t qt = (size_t)t.n * 8;
+  const size_t part = parts & FMM_PART_NEAR ? (size_t)std::max<int64_t>(0, npart) * 32 : 0;
+  if (!(parts & FMM_PART_FAR) || t.L == 0) return qt + part;
   const size_t stride = p <= tl::kMaxP ? (size_t)tl::stride(p) : (size_t)nterms(p);
   const size_t nbox = (size_t)t.nbox_total;
   // the copy, per box: binary32 dense (per-lane kernel, orders up to 14) or
@@ -804,27 +808,25 @@ size_t scratch_bytes(const Tree& t, int p, int prec, bool one_block) {
   if (prec != FMM_PREC_F64 && p <= 14) copy = (size_t)lops::dense_stride(p) * 4;
   else if (prec != FMM_PREC_F64 && p <= tl::kMaxP) copy = stride * 4;
   else copy = (size_t)lops::nq(p) * 4 * 8;
-  auto one = [&](int64_t npts, int64_t npart) {
-    const size_t part = (size_t)std::max<int64_t>(0, npart) * 32;
-    if (t.L == 0) return (size_t)t.n * 8 + part;
-    const size_t expn = nbox * stride * 8, far = 4 * (size_t)std::max<int64_t>(1, npts) * 8;
-    const size_t m2l = expn + 256 + nbox * copy;
-    return (size_t)t.n * 8 + (one_block ? std::max(m2l, expn + far + part) : std::max({m2l, expn + far, far + part}));
-  };
-  size_t b = one(t.n, t.p2p_npart);
-  if (t.m > 0) b = std::max(b, one(t.m, t.p2p_ntpart));
-  return b;
+  const size_t expn = nbox * stride * 8, far = 4 * (size_t)std::max<int64_t>(1, npts) * 8;
+  const size_t m2l = expn + 256 + nbox * copy;
+  return qt + (one_block ? std::max(m2l, expn + far + part) : std::max({m2l, expn + far, far + part}));
 }
 }  // namespace
 
-size_t arena_bytes(const Tree& t, int p, int prec) {
+size_t arena_bytes(const Tree& t, int p, int prec, int parts, bool targets) {
   // at most 12 buffers; each may lose 255 bytes to alignment
-  return scratch_bytes(t, p, prec, true) + 12 * 256;
+  return scratch_bytes(t, p, prec, parts, targets ? t.m : t.n, targets ? t.p2p_ntpart : t.p2p_npart, true) + 12 * 256;
 }
 
 size_t eval_scratch_bytes(const Tree& t, int p, int prec) {
-  const size_t a = arena_bytes(t, p, prec);
-  return a <= kOneBlock ? a : scratch_bytes(t, p, prec, false);
+  auto one = [&](bool targets) {
+    const size_t a = arena_bytes(t, p, prec, FMM_PART_ALL, targets);
+    return a <= kOneBlock ? a
+                          : scratch_bytes(t, p, prec, FMM_PART_ALL, targets ? t.m : t.n,
+                                          targets ? t.p2p_ntpart : t.p2p_npart, false);
+  };
+  return t.m > 0 ? std::max(one(false), one(true)) : one(false);
 }
 
 // phi and E at the tree's separate targets (outputs in the caller's target
