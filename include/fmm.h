@@ -201,8 +201,9 @@ fmm_status fmm_evaluate_tree_noalloc(fmm_tree* tree, const double* q, int p, int
  * level, the first child (in child order) whose closed cell holds it.
  * Synchronises `stream` as fmm_build does, plus once for the targets; for
  * eta < 1 also once per bisection round, from the second, while every
- * segment of the round before held at least 32768 points and the round has
- * at most 512 segments (the segment sizes choose the round's kernels).
+ * segment of the rounds before held at least 8192 points, the largest at
+ * least 32768, and the round has at most 512 segments (the segment sizes
+ * choose the round's kernels).
  */
 fmm_status fmm_build_ex(const double* x, const double* y, const double* z, int64_t n, const double* tx, const double* ty,
                  const double* tz, int64_t m, int levels, double theta, double eta, void* stream, fmm_tree** out);

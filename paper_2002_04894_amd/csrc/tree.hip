@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "fmm_internal.h"
+#include "launch_rules.h"
 
 namespace fmm {
 namespace {
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(BS) void k_orb_round(
 // ---- the same bisection round for few, large segments: every segment is
 // cut into chunks of kChunk points, one block per chunk, and the select /
 // partition steps go through per-segment state in global memory ----
-constexpr int kChunk = 2048;
+constexpr int kChunk = rules::kChunk;
 constexpr int kChunkBS = 256;
 constexpr int kSelPasses = 8;  // 8-bit digits cover the 64-bit key
 
@@ -847,37 +848,27 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
   int32_t* esegof = blend ? (int32_t*)dalloc(n * sizeof(int32_t), s) : nullptr;
   int64_t* ebelow = blend ? (int64_t*)dalloc((n + 1) * sizeof(int64_t), s) : nullptr;
 
-  // rounds whose segments all hold at least kMultiMin points (and are few)
-  // go through the chunked kernels; the rest run one block per segment
-  // A chunked round is 20 launches, bound by the host that makes them up to
-  // some 10^5 points; one block of 1,024 threads takes a segment in one.  The
-  // build of 20,000 points (3 levels) with chunked rounds from 8,192 points on
-  // and 256 threads below took 477 us, so 270.
-  constexpr int64_t kMultiMin = 16 * kChunk;
-  constexpr int64_t kMultiMaxSeg = 512;
   SegSel* sel = nullptr;
   unsigned* ghist = nullptr;
   int2* ccount = nullptr;
   int2* cbase = nullptr;
   double2* cpart = nullptr;
-  // the chunked rounds' state, allocated under the condition that selects
-  // them below: a round is chunked when it has at most kMultiMaxSeg segments,
-  // every one holds at least kMultiMin points and the chunks fit in nblk_cap
-  // (the first round, a single segment, whenever n >= kMultiMin).  With
-  // eta = 1 the segment sizes follow from n; with eta < 1 children may be
-  // unequal, so each round's sizes are read back until a segment is smaller
-  // than kMultiMin (its children are no larger, so no later round qualifies).
-  const bool any_multi = n >= kMultiMin;
-  const int64_t nblk_cap = 2 * ((n + kChunk - 1) / kChunk + kMultiMaxSeg);
+  // the chunked rounds' state, for the rounds that rules::round_chunked names
+  // and whose chunks fit in nblk_cap.  With eta = 1 the segment sizes follow
+  // from n; with eta < 1 children may be unequal, so each round's sizes are
+  // read back until one is not chunked for them (children are no larger, so no
+  // later round is).
+  const bool any_multi = n >= rules::kChunkedMax;
+  const int64_t nblk_cap = 2 * ((n + kChunk - 1) / kChunk + rules::kChunkedSeg);
   if (any_multi) {
-    sel = (SegSel*)dalloc(kMultiMaxSeg * sizeof(SegSel), s);
-    ghist = (unsigned*)dalloc(kMultiMaxSeg * 256 * sizeof(unsigned), s);
+    sel = (SegSel*)dalloc(rules::kChunkedSeg * sizeof(SegSel), s);
+    ghist = (unsigned*)dalloc(rules::kChunkedSeg * 256 * sizeof(unsigned), s);
     ccount = (int2*)dalloc(nblk_cap * sizeof(int2), s);
     cbase = (int2*)dalloc(nblk_cap * sizeof(int2), s);
     cpart = (double2*)dalloc(nblk_cap * sizeof(double2), s);
   }
   std::vector<int32_t> hseg_n;
-  bool sizes_ok = true;  // eta < 1: no earlier round had a segment below kMultiMin
+  bool sizes_ok = true;  // eta < 1: every earlier round's sizes were those of a chunked one
 
   int cur = 0;
   for (int depth = 0; depth < 3 * L; ++depth) {
@@ -887,17 +878,17 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
     const int o = cur ^ 1;
     bool multi = false;
     int64_t seg_max = maxn;
-    if (any_multi && nsegd <= kMultiMaxSeg) {
+    if (any_multi && nsegd <= rules::kChunkedSeg) {
       if (!blend || depth == 0) {
-        multi = minn >= kMultiMin;
+        multi = rules::round_chunked(nsegd, minn, maxn);
       } else if (sizes_ok) {
         hseg_n.resize((size_t)nsegd);
         HIPCHECK(hipMemcpyAsync(hseg_n.data(), seg_n + (nsegd - 1), nsegd * sizeof(int32_t), hipMemcpyDeviceToHost,
                                 s));
         HIPCHECK(hipStreamSynchronize(s));
         const auto mm = std::minmax_element(hseg_n.begin(), hseg_n.end());
-        sizes_ok = *mm.first >= kMultiMin;
         seg_max = *mm.second;
+        sizes_ok = rules::round_chunked(nsegd, *mm.first, seg_max);
         multi = sizes_ok && nsegd * ((seg_max + kChunk - 1) / kChunk) <= nblk_cap;
       }
     }

@@ -31,3 +31,12 @@ def run(tmp_path, body):
 ])
 def test_near_field_waves(tmp_path, nseg, entries, f32, waves):
     assert run(tmp_path, f'std::printf("%d\\n", p2p_waves({nseg}, {entries}, {f32}));\n') == [str(waves)]
+
+
+@pytest.mark.parametrize("nseg,smallest,largest,chunked", [
+    # the largest segment decides, down to 8,192 points in the smallest
+    (1, 32_768, 32_768, 1), (1, 32_767, 32_767, 0), (2, 20_000, 4_000_000, 1), (4, 8_192, 32_768, 1),
+    (4, 8_191, 4_000_000, 0), (4, 9_000, 32_767, 0), (512, 32_768, 40_000, 1), (1024, 32_768, 40_000, 0),
+])
+def test_chunked_rounds(tmp_path, nseg, smallest, largest, chunked):
+    assert run(tmp_path, f'std::printf("%d\\n", round_chunked({nseg}, {smallest}, {largest}));\n') == [str(chunked)]
