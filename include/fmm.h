@@ -292,7 +292,10 @@ fmm_status fmm_last_timings(double* ms);
  * bytes the handle owns (tree, lists, plans); *eval_bytes (may be NULL) the
  * peak scratch bytes one evaluation at order p and the given precision
  * allocates on top (sources, and the separate targets when the tree has
- * them).  Unlike fmm_bytes_estimate these are exact, for any point cloud. */
+ * them).  Unlike fmm_bytes_estimate these are exact, for any point cloud.
+ * Arrays of up to 2 MiB (all of them up to about 2.6e5 points, but for long
+ * lists) share blocks with what only the build needed, which the handle keeps:
+ * its bytes are then up to about twice those of its arrays. */
 fmm_status fmm_tree_bytes(const fmm_tree* tree, int p, int precision, size_t* tree_bytes, size_t* eval_bytes);
 
 /* Estimate of the device bytes a build + evaluation needs, for admission

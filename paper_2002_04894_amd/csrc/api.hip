@@ -4,12 +4,14 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <memory>
 #include <mutex>
 
 #include "fmm_internal.h"
+#include "launch_rules.h"
 
 struct fmm_tree {
   fmm::Tree t;
@@ -77,22 +79,30 @@ void raw_free(const Allocator& a, void* p, hipStream_t s) {
 
 // The allocations of one entry-point call: a failed call frees those still
 // live; a successful build hands them to its tree.  A build cuts its small
-// buffers (about 45, most of them a few bytes per box) out of shared blocks
-// that double in size: an allocation or a free of the stream-ordered pool
-// costs 4 to 8 us of host time (building, evaluating and freeing 1,000 points
-// 875 us with a block per buffer, of which 320 us to free the tree).  A buffer
-// that is given back is handed out again to a request of at least half its
-// size; larger buffers have blocks of their own.
+// buffers (about 45, most of them a few bytes per box) out of shared blocks: a
+// free of the stream-ordered pool costs 10 to 20 us of host time, an allocation
+// up to 40 (building, evaluating and freeing 1,000 points 875 us with a block
+// per buffer, of which 320 us to free the tree).  A request takes the smallest
+// spare piece that holds it and leaves the rest spare, so that what the tree
+// keeps of the lists takes the place of what the bisection needed; without one,
+// a new block.  The first block is sized for what the build is expected to hold
+// at once.  The tree keeps the blocks: at most about twice its arrays (few boxes
+// for the points, or planes off the median; 226,650 points in 8 leaves 12.8 MB
+// for 6.3, 60,000 in 512 leaves 3.5 for 2.6).  Giving back what only the build
+// needed would cost a pass 6 % at 10^5 points (1.55 -> 1.65 ms).
+struct Piece {
+  char* p;
+  size_t n;
+  size_t block;  // of the shared blocks
+};
 struct Ledger {
-  static constexpr size_t kPiece = (size_t)2 << 20;  // buffers up to this size share
-  static constexpr size_t kFirst = (size_t)128 << 10, kLast = (size_t)8 << 20;  // sizes of the blocks
+  static constexpr size_t kPiece = (size_t)2 << 20;  // larger buffers have blocks of their own
+  static constexpr size_t kFirst = (size_t)64 << 10, kNext = (size_t)256 << 10;  // least sizes of the shared blocks
   Allocator a;
   std::vector<std::pair<void*, size_t>> live;
   bool share = false;
-  char* cur = nullptr;  // the newest shared block
-  size_t left = 0;      // its bytes not handed out
-  size_t next = kFirst;
-  std::vector<std::pair<char*, size_t>> pieces, spare;  // handed out / given back
+  size_t next = kFirst, nblock = 0;
+  std::vector<Piece> pieces, spare;  // handed out / not
 };
 thread_local Ledger* g_ledger = nullptr;
 
@@ -108,6 +118,8 @@ class CallScope {
       for (auto it = led_.live.rbegin(); it != led_.live.rend(); ++it) raw_free(led_.a, it->first, s_);
     g_ledger = prev_;
   }
+  // about the bytes of small buffers that a build will hold at once
+  void expect(size_t bytes) { led_.next = std::max((bytes + 4095) & ~(size_t)4095, Ledger::kFirst); }
   // the live allocations now belong to the caller (a tree)
   std::vector<std::pair<void*, size_t>> keep() {
     kept_ = true;
@@ -222,27 +234,40 @@ void* block_alloc(size_t bytes, hipStream_t s) {
 void* shared_alloc(Ledger& g, size_t bytes, hipStream_t s) {
   bytes = (bytes + 255) & ~(size_t)255;
   g.pieces.reserve(g.pieces.size() + 1);
-  g.spare.reserve(g.pieces.size() + g.spare.size() + 1);  // a free never allocates
-  size_t best = g.spare.size();
-  for (size_t k = 0; k < g.spare.size(); ++k)
-    if (g.spare[k].second >= bytes && g.spare[k].second <= 2 * bytes &&
-        (best == g.spare.size() || g.spare[k].second < g.spare[best].second))
-      best = k;
-  if (best < g.spare.size()) {
-    g.pieces.push_back(g.spare[best]);
-    g.spare.erase(g.spare.begin() + (long)best);
-    return g.pieces.back().first;
-  }
-  if (bytes > g.left) {
+  g.spare.reserve(g.pieces.size() + g.spare.size() + 2);  // a free never allocates
+  auto best = g.spare.end();
+  for (auto it = g.spare.begin(); it != g.spare.end(); ++it)
+    if (it->n >= bytes && (best == g.spare.end() || it->n < best->n)) best = it;
+  if (best == g.spare.end()) {
     const size_t size = std::max(bytes, g.next);
-    g.cur = (char*)block_alloc(size, s);
-    g.left = size;
-    g.next = std::min(2 * size, Ledger::kLast);
+    g.next = Ledger::kNext;
+    best = g.spare.insert(g.spare.end(), Piece{(char*)block_alloc(size, s), size, g.nblock++});
   }
-  g.pieces.emplace_back(g.cur, bytes);
-  g.cur += bytes;
-  g.left -= bytes;
-  return g.pieces.back().first;
+  const Piece t{best->p, bytes, best->block};
+  if (best->n > bytes)
+    *best = Piece{best->p + bytes, best->n - bytes, best->block};
+  else
+    g.spare.erase(best);
+  g.pieces.push_back(t);
+  return t.p;
+}
+
+// a piece given back joins its spare neighbours of the same block
+bool shared_free(Ledger& g, void* p) {
+  for (size_t k = g.pieces.size(); k-- > 0;) {
+    if (g.pieces[k].p != p) continue;
+    Piece t = g.pieces[k];
+    g.pieces.erase(g.pieces.begin() + (long)k);
+    for (size_t i = g.spare.size(); i-- > 0;) {
+      const Piece& o = g.spare[i];
+      if (o.block != t.block || (o.p + o.n != t.p && t.p + t.n != o.p)) continue;
+      t = Piece{std::min(o.p, t.p), o.n + t.n, t.block};
+      g.spare.erase(g.spare.begin() + (long)i);
+    }
+    g.spare.push_back(t);
+    return true;
+  }
+  return false;
 }
 }  // namespace
 
@@ -270,13 +295,7 @@ void dfree(void* p, hipStream_t s) {
   }
   const Allocator a = g_ledger ? g_ledger->a : Allocator{};
   if (g_ledger) {
-    auto& u = g_ledger->pieces;
-    for (size_t k = u.size(); k-- > 0;)
-      if (u[k].first == p) {
-        g_ledger->spare.push_back(u[k]);
-        u.erase(u.begin() + (long)k);
-        return;
-      }
+    if (shared_free(*g_ledger, p)) return;
     auto& v = g_ledger->live;
     for (size_t k = v.size(); k-- > 0;)
       if (v[k].first == p) {
@@ -379,6 +398,34 @@ void ensure_device() {
   }
 }
 
+// About the bytes of buffers up to Ledger::kPiece that a build holds at once:
+// in the bisection both sets of points, afterwards one of them with the boxes,
+// their lists (as at theta 0.5), the masks behind them and the near field's plan.
+size_t build_bytes(const fmm::Tree& t) {
+  auto sh = [](int64_t bytes) {
+    return bytes <= (int64_t)fmm::Ledger::kPiece ? ((size_t)bytes + 255) & ~(size_t)255 : (size_t)0;
+  };
+  const int64_t n = t.n, m = t.m, nleaf = (int64_t)1 << (3 * t.L), nseg = 2 * nleaf - 1;
+  const size_t points = 3 * sh(8 * n) + sh(4 * n), targets = m > 0 ? 3 * sh(8 * m) : 0;
+  size_t first = points + sh(48 * nseg) + 2 * sh(4 * nseg) + sh(6 * 8 * std::min<int64_t>(2048, (n + m) / 256 + 2)) + sh(8);
+  if (n >= fmm::rules::kChunkedMax)
+    first += sh(1056 * std::min(fmm::rules::kChunkedSeg, n / fmm::rules::kChunkedMin)) +
+             sh(64 * (n / fmm::rules::kChunk + fmm::rules::kChunkedSeg + 1));
+  if (t.eta < 1.0) first += 2 * sh(4 * n) + sh(8 * (n + 1)) + sh(4 * nleaf) + sh(2 * nleaf);
+  if (m > 0) first += sh(4 * m);
+  size_t then = 0;
+  int64_t nbox = 0;
+  for (int l = 0; l <= t.L; ++l) {
+    const int64_t nb = (int64_t)1 << (3 * l), entries = std::min<int64_t>(nb * nb, 350 * nb);
+    first += sh(80 * nb) + sh(4 * (nb + 1));
+    then += sh(80 * nb) + sh(4 * (nb + 1)) + 2 * sh(8 * (nb + 1)) + sh(4 * entries);
+    nbox += nb;
+  }
+  then += sh(32 * nbox) + sh(4 * nbox) + sh(100 * nleaf) + 3 * sh(8 * (nleaf + 1)) + 3 * sh(4 * nleaf) + sh(8 * nleaf);
+  if (m > 0) then += targets + 2 * sh(4 * m) + 2 * sh(4 * (nleaf + 1)) + 2 * sh(8 * (nleaf + 1));
+  return points + targets + std::max(first, then);
+}
+
 fmm_tree* build_impl(const double* x, const double* y, const double* z, int64_t n, const double* tx,
                      const double* ty, const double* tz, int64_t m, int levels, double theta, double eta,
                      hipStream_t s) {
@@ -399,6 +446,7 @@ fmm_tree* build_impl(const double* x, const double* y, const double* z, int64_t 
   t.build_stream = s;
   t.alloc = fmm::current_allocator();
   fmm::CallScope scope(t.alloc, s, true);  // frees everything allocated here if the build fails
+  scope.expect(build_bytes(t));
   // kernels of the build write into this thread's pinned words: a build that
   // fails waits for them, so that none writes into a later build's
   struct Drain {

@@ -861,8 +861,9 @@ void tree_build(Tree& t, const double* x, const double* y, const double* z, cons
   const bool any_multi = n >= rules::kChunkedMax;
   const int64_t nblk_cap = 2 * ((n + kChunk - 1) / kChunk + rules::kChunkedSeg);
   if (any_multi) {
-    sel = (SegSel*)dalloc(rules::kChunkedSeg * sizeof(SegSel), s);
-    ghist = (unsigned*)dalloc(rules::kChunkedSeg * 256 * sizeof(unsigned), s);
+    const int64_t nsel = std::min(rules::kChunkedSeg, n / rules::kChunkedMin);  // segments of a chunked round
+    sel = (SegSel*)dalloc(nsel * sizeof(SegSel), s);
+    ghist = (unsigned*)dalloc(nsel * 256 * sizeof(unsigned), s);
     ccount = (int2*)dalloc(nblk_cap * sizeof(int2), s);
     cbase = (int2*)dalloc(nblk_cap * sizeof(int2), s);
     cpart = (double2*)dalloc(nblk_cap * sizeof(double2), s);
