@@ -34,6 +34,7 @@ import math
 import queue
 import threading
 import time
+from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -353,7 +354,9 @@ class Server:
         """Serve `requests` (sorted by arrival).  With `realtime`, a request
         becomes visible at its arrival time; latency is completion - arrival.
         Without, the requests are a backlog: the data of as many as the queue
-        holds are drawn before the first is served."""
+        holds are drawn, by as many threads as there are workers, before the
+        first is served (one thread draws a cloud in more time than a solve
+        takes).  The clock of the latencies starts before the drawing."""
         import torch
         reqs = sorted(requests, key=lambda r: r.arrival)
         ready: queue.Queue = queue.Queue(maxsize=64)
@@ -429,9 +432,11 @@ class Server:
         threads = [threading.Thread(target=producer, daemon=True)]
         threads += [threading.Thread(target=worker, daemon=True) for _ in range(self.workers)]
         try:
-            for r in reqs[:backlog]:
-                ready.put((r, request_points(r)))
             t0[0] = time.perf_counter()
+            if backlog:
+                with ThreadPoolExecutor(self.workers) as pool:
+                    for item in zip(reqs, pool.map(request_points, reqs[:backlog])):
+                        ready.put(item)
             for th in threads:
                 th.start()
             for th in threads:
