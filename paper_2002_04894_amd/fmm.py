@@ -108,15 +108,16 @@ def _stream(stream):
 class Tree:
     """Owning wrapper of an fmm_tree handle (n sources, m separate targets)."""
 
-    def __init__(self, handle: int, n: int, m: int = 0):
+    def __init__(self, handle: int, n: int, m: int = 0, hook=None):
         self.handle = handle
         self.n = n
         self.m = m
+        self._hook = hook  # the tree is freed through the allocator it was built with
 
     def free(self):
         if self.handle:
             _check(lib().fmm_free(self.handle))
-            self.handle = None
+            self.handle = self._hook = None
 
     def __del__(self):
         try:
@@ -134,10 +135,10 @@ def fmm_build(x, y, z, levels: int, theta: float, stream=None) -> Tree:
     _same_length(x, y, z)
     for t, nm in ((x, "x"), (y, "y"), (z, "z")):
         _dev(t, nm)
-    h = C.c_void_p()
+    h, hook = C.c_void_p(), _hook_refs
     _check(lib().fmm_build(_ptr(x), _ptr(y), _ptr(z), x.numel(), int(levels), float(theta), _stream(stream),
                            C.byref(h)))
-    return Tree(h.value, x.numel())
+    return Tree(h.value, x.numel(), hook=hook)
 
 
 def fmm_build_ex(x, y, z, levels: int, theta: float, eta: float = 1.0, targets=None, stream=None) -> Tree:
@@ -154,10 +155,10 @@ def fmm_build_ex(x, y, z, levels: int, theta: float, eta: float = 1.0, targets=N
         if any(t.numel() != m for t in targets):
             raise ValueError("tx, ty, tz must have the same length")
         tp = tuple(_ptr(t) for t in targets)
-    h = C.c_void_p()
+    h, hook = C.c_void_p(), _hook_refs
     _check(lib().fmm_build_ex(_ptr(x), _ptr(y), _ptr(z), x.numel(), *tp, m, int(levels), float(theta), float(eta),
                               _stream(stream), C.byref(h)))
-    return Tree(h.value, x.numel(), m)
+    return Tree(h.value, x.numel(), m, hook)
 
 
 def fmm_evaluate_targets(tree: Tree, q, p: int, pot, ex, ey, ez, stream=None, parts: int = FMM_PART_ALL,
@@ -285,7 +286,8 @@ def fmm_set_allocator(alloc=None, free=None):
     """Routes the library's device allocations through Python callables
     alloc(nbytes, stream) -> int pointer (0 on failure) and free(ptr, stream);
     with no arguments the library's own stream-ordered pool is restored.
-    The callables are kept alive until the next call."""
+    The callables are kept alive until the next call, and as long as a tree
+    built with them."""
     global _hook_refs
     if (alloc is None) != (free is None):
         raise ValueError("alloc and free must both be given or both omitted")
