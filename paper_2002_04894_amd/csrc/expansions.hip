@@ -676,10 +676,12 @@ __global__ __launch_bounds__(64) void k_l2l(LevelView lv, int l, int64_t nbox, X
 // writes and the column reads are free of bank conflicts.
 // Bound by latency: a wave's chain over the orders, 64 points at a time (64
 // leaves at order 12 take 19 us, 27 with the constants in global memory), in
-// long launches by LDS (2^24 points at order 12 2.75 ms either way).  Up to
-// kP2MShare leaves several waves take a leaf: 100,000 points off the median in
-// 512 leaves 279 -> 81 us, 47,003 points 45 -> 28; with 4,096 leaves, which
-// fill the chip, 18 -> 44 us at order 6 and 108 -> 212 at order 16.
+// long launches by LDS, where the constants' place would cost more than the
+// loads (2^24 points, 262,144 leaves, order 12 2.69 ms, staged 2.87; order 16
+// 4.88 and 5.27), so only several waves together stage them.  Up to kP2MShare
+// leaves several waves take a leaf: 100,000 points off the median in 512 leaves
+// 279 -> 81 us, 47,003 points 45 -> 28; with 4,096 leaves, which fill the chip,
+// 18 -> 44 us at order 6 and 108 -> 212 at order 16.
 constexpr int64_t kP2MShare = 512;
 __host__ __device__ constexpr int p2m_stride(int p) { return 2 * (p + 1) + 1; }
 
@@ -708,7 +710,9 @@ template <int W>
 __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const double* __restrict__ px,
                                             const double* __restrict__ py, const double* __restrict__ pz,
                                             const double* __restrict__ qt, double* __restrict__ Mx) {
-  extern __shared__ __align__(16) double rows[];  // (c1, c2), then per wave 64 x p2m_stride(p) and the sums (tb.nt)
+  constexpr bool STAGED = W > 1;
+  // (c1, c2) if staged, then per wave 64 x p2m_stride(p) and the sums (tb.nt)
+  extern __shared__ __align__(16) double rows[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int L = lv.L, p = tb.p, P1 = p + 1, nt = tb.nt;
   const int64_t b = blockIdx.x;
@@ -717,15 +721,17 @@ __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const doubl
   const int s0 = lv.start[L][b], s1 = lv.start[L][b + 1];
   const double* am = tb.rc;
   const double* bm = tb.rc + P1;
+  const double* c1 = tb.rc + 2 * P1;
+  const double* c2 = c1 + P1 * P1;
   const double s2 = 1.4142135623730951;
   const int SP = p2m_stride(p);
   double2* cc = (double2*)rows;
   const int per = 64 * SP + nt;  // doubles per wave
-  double* tab = rows + P1 * P1 + wave * per;
+  double* tab = rows + (STAGED ? P1 * P1 : 0) + wave * per;
   double* row = tab + lane * SP;
   double* acc = tab + 64 * SP;
   for (int k = lane; k < nt; k += 64) acc[k] = 0.0;
-  stage_rec(tb, cc);
+  if constexpr (STAGED) stage_rec(tb, cc);
   __syncthreads();
   for (int c0 = s0 + 64 * wave; c0 < s1; c0 += 64 * W) {
     const int t = c0 + lane;
@@ -739,6 +745,9 @@ __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const doubl
     double mr = 1.0, mi = 0.0;  // G_m^m
     const double2* cm = cc;
     for (int m = 0; m <= p; ++m) {
+      auto rec = [&](int n) __attribute__((always_inline)) {
+        return STAGED ? *cm++ : make_double2(c1[n * P1 + m], c2[n * P1 + m]);
+      };
       if (m > 0) {
         const double nr = am[m] * (x * mr - y * mi);
         const double ni = am[m] * (x * mi + y * mr);
@@ -757,7 +766,7 @@ __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const doubl
         row[3] = sq * bi;
         int n = m + 2;
         for (; n + 1 <= p; n += 2) {
-          const double2 ca = *cm++, cb = *cm++;
+          const double2 ca = rec(n), cb = rec(n + 1);
           ar = ca.x * z * br - ca.y * r2 * ar;
           ai = ca.x * z * bi - ca.y * r2 * ai;
           row[2 * (n - m)] = cq * ar;
@@ -768,7 +777,7 @@ __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const doubl
           row[2 * (n + 1 - m) + 1] = sq * bi;
         }
         if (n <= p) {
-          const double2 ca = *cm++;
+          const double2 ca = rec(n);
           ar = ca.x * z * br - ca.y * r2 * ar;
           ai = ca.x * z * bi - ca.y * r2 * ai;
           row[2 * (n - m)] = cq * ar;
@@ -915,7 +924,9 @@ __global__ __launch_bounds__(64) void k_l2p(LevelView lv, XT tb, const int32_t* 
 // launch helpers used by evaluate() (p2p.hip)
 void launch_p2m(const Tree& t, const Tables& tb, const double* qt, double* Mx, hipStream_t s) {
   const int64_t nleaf = t.lev[t.L].nbox;
-  auto lds = [&](int w) { return (nterms(tb.p) + w * ((size_t)64 * p2m_stride(tb.p) + nterms(tb.p))) * sizeof(double); };
+  auto lds = [&](int w) {
+    return ((w > 1 ? nterms(tb.p) : 0) + w * ((size_t)64 * p2m_stride(tb.p) + nterms(tb.p))) * sizeof(double);
+  };
   auto go = [&](auto w) {
     constexpr int W = decltype(w)::value;
     k_p2m<W><<<(unsigned)nleaf, 64 * W, lds(W), s>>>(t.view(), make_xt(tb), t.px, t.py, t.pz, qt, Mx);
