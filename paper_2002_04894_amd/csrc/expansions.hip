@@ -227,7 +227,8 @@ HostTables make_host_tables(int p) {
     for (int k = 0; k < nt; ++k) h.pos[k] = h.ipos[k] = k;
     return h;
   }
-  h.sdeg.assign(h.stride, -1);
+  const bool tiles = p == kTileM2LP;
+  if (tiles) h.sdeg.assign(h.stride, -1);
   for (int t = 0; t < tl::ntiles(p); ++t)
     for (int sl = 0; sl < 16; ++sl) {
       const tl::Slot d = tl::decode(p, t, sl);
@@ -235,8 +236,9 @@ HostTables make_host_tables(int p) {
       const int k = d.n * d.n + (d.m == 0 ? 0 : 2 * d.m - 1 + d.sine);
       h.pos[k] = tl::spos(t, sl);
       h.ipos[tl::spos(t, sl)] = k;
-      h.sdeg[tl::spos(t, sl)] = (int8_t)d.n;
+      if (tiles) h.sdeg[tl::spos(t, sl)] = (int8_t)d.n;
     }
+  if (!tiles) return h;
   // MFMA tables, stored as operand fragments (entry [step][lane] is what lane
   // `lane` feeds to the k-step `step` of a 16x16x4 chain: row lane % 16,
   // column 4 step + lane / 16):
@@ -425,9 +427,10 @@ const Tables& tables_for(int p, hipStream_t s) {
     t.quad_m2m = upload(quad_tables(h, p, kQuadM2M), s);
     t.quad_l2l = upload(quad_tables(h, p, kQuadL2L), s);
   }
-  if (h.tiled) {
+  if (p == kTileM2LP) {
     t.mtab32 = upload(h.mtab32, s);
     t.sdeg = upload(h.sdeg, s);
+  } else if (h.tiled) {
     t.lane = upload(lane_tables(h, p), s);
   }
   HIPCHECK(hipStreamSynchronize(s));  // also keeps h alive until the copies are done

@@ -17,6 +17,9 @@ constexpr int kMaxOrder = FMM_MAX_ORDER;
 // M2M and L2L run four lanes per translation on the matrix cores up to this
 // order (as far as the table holds J^T), the generic binary64 translation above
 constexpr int kQuadXlateMaxP = 18;
+// binary32 M2L runs one pair per lane below this order, in 16x16 tiles at it,
+// and in binary64 above
+constexpr int kTileM2LP = 15;
 
 // M2L work order (lists.hip, m2l_queue.h): from this many targets on siblings
 // stay together; the waves that run at once, about
@@ -165,13 +168,13 @@ struct Tables {
   int stride = 0;
   int* pos = nullptr;
   int* ipos = nullptr;
-  // 16x16 tile tables (p <= 15), as operand fragments [step][lane] of the
-  // binary32 MFMA: the y-quarter-turn tile matrices [ntiles * 4][64], then the
+  // order kTileM2LP: 16x16 tile tables as operand fragments [step][lane] of the
+  // binary32 MFMA, the y-quarter-turn tile matrices [ntiles * 4][64], then the
   // z-translation matrices per order [sum_m hsteps][64]
   float* mtab32 = nullptr;
   int8_t* sdeg = nullptr;  // degree of each storage position, -1 for a zero slot
-  // J, J^T and the z-translation core as operands of the per-lane M2L
-  // kernel's 4x4x1 matrix instructions (lane_ops.h), binary32
+  // orders below kTileM2LP: J, J^T and the z-translation core as operands of
+  // the per-lane M2L kernel's 4x4x1 matrix instructions (lane_ops.h), binary32
   float* lane = nullptr;
   // J, J^T (where it fits in LDS) and the z-translation core for the
   // binary64 per-quad M2L kernel (lane_ops.h), and the same with the M2M and

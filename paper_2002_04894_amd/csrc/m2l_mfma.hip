@@ -626,14 +626,14 @@ bool launch_m2l_mfma_mixed(const Tree& t, const Tables& tb, const double* Mx, do
   if (!tb.tiled) return false;
   // orders up to 14 one pair per lane (m2l_lane.hip), 15 in 16x16 tiles
   if (launch_m2l_lane32(t, tb, Mx, Lx, s)) return true;
-  if (tb.p != 15) return false;
+  if (tb.p != kTileM2LP) return false;
   float* Mf = (float*)dalloc((size_t)t.nbox_total * tb.stride * sizeof(float), s);
   if (t.nbox_total > 1) {
     k_scale_m32<<<(unsigned)((t.nbox_total - 1 + 3) / 4), 256, 0, s>>>(t.view(), tb.stride, tb.sdeg, Mx, Mf,
                                                                       t.nbox_total);
     HIPCHECK(hipGetLastError());
   }
-  launch_one<15>(t, tb, Mf, Lx, s);
+  launch_one<kTileM2LP>(t, tb, Mf, Lx, s);
   dfree(Mf, s);
   return true;
 }

@@ -284,12 +284,6 @@ __device__ __forceinline__ P2PSplit p2p_split(int nt) {
   return best;
 }
 
-// What the waves of a workgroup share.
-template <bool F32>
-struct P2PShared {
-  typedef typename std::conditional<F32, float4, double4>::type V;
-};
-
 struct P2POut {
   double4* part;  // partial sums by target - t0, or null: then the far field is
                   // added and the results go to the outputs
@@ -514,7 +508,7 @@ __global__ __launch_bounds__(64 * W) void k_p2p(
     const double* __restrict__ f1, const double* __restrict__ f2, const double* __restrict__ f3,
     double4* __restrict__ part, double* __restrict__ pot, double* __restrict__ ex, double* __restrict__ ey,
     double* __restrict__ ez, const double* __restrict__ lgeom) {
-  typedef typename P2PShared<F32>::V V;
+  typedef typename std::conditional<F32, float4, double4>::type V;
   // the waves' chunks (8 KB each, 4 KB in binary32); in binary64 later their
   // sums, at most 4 x 4 x 64 doubles a wave
   constexpr int kBytes = (int)sizeof(V) * kP2PBuf;
