@@ -51,18 +51,18 @@ COPY_WRITE_SCALE = 1.0
 M2L_COUNTERS: dict = {  # (kernel, n, theta) -> {"sources_sha256", "fetch_kib", "write_kib"}
     # profiles/m2l_counters_plummer134m.md (theta 0.6, p 12): mixed precision and binary64
     ("k_m2l_lane<12>", 1 << 27, 0.6): {
-        "sources_sha256": "3cd92d4759a611a1cad4868b2ea6d7fff781341505d3bb86bbb7fd80ac579a2e",
+        "sources_sha256": "4caa7658cfae9b240c1d73ff844864d627bd46e5f9028512ecf3c7ba2b3452f1",
         "fetch_kib": 1993446604.625,
         "write_kib": 6232508.90625,
     },
     ("k_m2l_quad<12>", 1 << 27, 0.6): {
-        "sources_sha256": "17d14efcd5f20ce184882c2bc953cbb6ed00e3cbf19a2db67c7f874df8514b97",
+        "sources_sha256": "34bd04e0177e9c671646c851700a06644f0785525732a18088e5cd3c17e4ad9f",
         "fetch_kib": 6458831153.5,
         "write_kib": 4291872.34375,
     },
     # binary64 at theta 0.55, p 10
     ("k_m2l_quad<10>", 1 << 27, 0.55): {
-        "sources_sha256": "17d14efcd5f20ce184882c2bc953cbb6ed00e3cbf19a2db67c7f874df8514b97",
+        "sources_sha256": "34bd04e0177e9c671646c851700a06644f0785525732a18088e5cd3c17e4ad9f",
         "fetch_kib": 6909006802.0,
         "write_kib": 3678283.53125,
     },

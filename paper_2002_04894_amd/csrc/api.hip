@@ -407,7 +407,7 @@ size_t build_bytes(const fmm::Tree& t) {
   };
   const int64_t n = t.n, m = t.m, nleaf = (int64_t)1 << (3 * t.L), nseg = 2 * nleaf - 1;
   const size_t points = 3 * sh(8 * n) + sh(4 * n), targets = m > 0 ? 3 * sh(8 * m) : 0;
-  size_t first = points + sh(48 * nseg) + 2 * sh(4 * nseg) + sh(6 * 8 * std::min<int64_t>(2048, (n + m) / 256 + 2)) + sh(8);
+  size_t first = points + sh(48 * nseg) + 2 * sh(4 * nseg) + sh(48 * std::min<int64_t>(2048, (n + m) / 256 + 2)) + sh(8);
   if (n >= fmm::rules::kChunkedMax)
     first += sh(1056 * std::min(fmm::rules::kChunkedSeg, n / fmm::rules::kChunkedMin)) +
              sh(64 * (n / fmm::rules::kChunk + fmm::rules::kChunkedSeg + 1));

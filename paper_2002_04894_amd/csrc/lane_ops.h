@@ -76,7 +76,9 @@ __host__ __device__ constexpr int j_rows(int n, int cls, int a) {
 // these classes: 3/4, 1/2, -5/8, 9/16, ...), its product often lies halfway
 // between two binary32 values, and the vanishing entry before it, about 1e-21
 // as tabulated, decides the rounding.  That one instruction is kept, so that
-// every rounding is that of the whole block.
+// every rounding is that of the whole block: 40 of 1,500 instructions per batch at
+// order 12, for results that differ in the tenth digit without.  Which classes
+// have such entries was read off the tables of orders up to 14.
 __host__ __device__ constexpr bool j_lead(int n, int cls) { return ((n + cls) & 1) == 0 || n == 6; }
 // instructions of one J application and of the z translation (per part)
 __host__ __device__ constexpr int n_j(int p) { return j_offset(p + 1, 0); }

@@ -392,7 +392,8 @@ k_m2l_lane(LevelView lv, const float* __restrict__ ltab, const int* __restrict__
   constexpr int GJ = 64 * lops::groups(lops::n_j(P));  // table: J, J^T, z core
   __shared__ float tabs[lops::table_floats(P)];
   // the turn angles' cosines and sines: two angles per lane (12 KB per wave at
-  // order 12; with the tables 66 KB per block, two blocks per CU)
+  // order 12; with the tables and the parked values 80 KB per block, so that two
+  // blocks just fit on a CU)
   constexpr int TW = 64 * Turn<P>::kWords;
   __shared__ float4 turns[P > 0 ? 4 * 2 * TW : 1];
   // values that a lane parks while the translation runs, where they would
@@ -557,8 +558,8 @@ __global__ void k_scale_lane(LevelView lv, int S, const int* __restrict__ pos, c
   }
 }
 
-__global__ void k_start_queue_l(int* queue, const int32_t* first) {
-  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = threadIdx.x == 0 && first ? *first : 0;
+__global__ void k_start_queue_l(int* queue) {
+  if (threadIdx.x < m2lq::kXcds) queue[threadIdx.x] = 0;
 }
 
 template <int P>
@@ -585,7 +586,7 @@ void launch_one_lane(const Tree& t, const Tables& tb, const double* Mx, double* 
   const int64_t need = (ntarget + 3) / 4;
   const unsigned grid = (unsigned)(need < grid_max ? need : grid_max);
   int* queue = (int*)dalloc(m2lq::kXcds * sizeof(int), s);
-  k_start_queue_l<<<1, 64, 0, s>>>(queue, nullptr);
+  k_start_queue_l<<<1, 64, 0, s>>>(queue);
   HIPCHECK(hipGetLastError());
   if (ntarget >= kM2LSiblingsMin)
     k_m2l_lane<P, false, true><<<grid, 256, 0, s>>>(t.view(), tb.lane, tb.pos, Mf, Lx, ntarget, t.m2l_order, queue);

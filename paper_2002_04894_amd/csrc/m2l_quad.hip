@@ -29,8 +29,8 @@
 //     exchanged halves: each lane runs it for its orders on the vector units (binary64 vector and matrix peaks are equal on this part);
 //   - the 16 pair results are summed across the lanes by halving exchanges
 //     through DPP (fixed order: deterministic) and the batches in binary64.
-// What bounds it: binary64 matrix and vector issue, up to order 14 at better
-// than 85 % of the cycles; from order 15 on a few values still spill, and above
+// What bounds it: binary64 matrix and vector issue (order 12, 2^27 points: 34 and
+// 44 % of the cycles); from order 15 on a few values still spill, and above
 // it one wave per SIMD hides no latency.  Measured on 2^22 Plummer points (5
 // levels, theta 0.6, 194 million pairs), M2L in ms: order 8 38, 10 59, 12 87,
 // 13 102, 14 120, 15 154, 16 289, 18 574, 20 833; with whole blocks of J and

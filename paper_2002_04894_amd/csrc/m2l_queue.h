@@ -75,6 +75,9 @@ struct Kept {
 // points on a sphere, 512 leaves 545 / 150; 2^18 Plummer points, 4,096 leaves
 // 4,240 / 6,000; 200,000 points on a sphere, 4,096 leaves 3,730 / 1,960 with the
 // long lists shared; binary32 order 6, 200,000 points, 4,096 leaves 350 / 215.
+// The numbers of targets are 8, 72, 584, 4,680, 37,448, 299,592, ...: the limits
+// mean trees of up to three levels, of up to four and, for kM2LSiblingsMin, of
+// six and more; what was measured are the numbers on their two sides.
 constexpr int64_t kShareQuad = 1024;  // all targets shared up to here,
 constexpr int64_t kShareLane = 8192;  // and up to here (per-lane kernel)
 constexpr int64_t kLongQuad = 8192;   // binary64: the too long ones up to here
