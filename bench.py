@@ -56,13 +56,13 @@ M2L_COUNTERS: dict = {  # (kernel, n, theta) -> {"sources_sha256", "fetch_kib", 
         "write_kib": 6232508.90625,
     },
     ("k_m2l_quad<12>", 1 << 27, 0.6): {
-        "sources_sha256": "34bd04e0177e9c671646c851700a06644f0785525732a18088e5cd3c17e4ad9f",
+        "sources_sha256": "8c3a300fd5eb3de991ab2fc1dbde4745147435dca853db6e58f4639aa1eede27",
         "fetch_kib": 6458831153.5,
         "write_kib": 4291872.34375,
     },
     # binary64 at theta 0.55, p 10
     ("k_m2l_quad<10>", 1 << 27, 0.55): {
-        "sources_sha256": "34bd04e0177e9c671646c851700a06644f0785525732a18088e5cd3c17e4ad9f",
+        "sources_sha256": "8c3a300fd5eb3de991ab2fc1dbde4745147435dca853db6e58f4639aa1eede27",
         "fetch_kib": 6909006802.0,
         "write_kib": 3678283.53125,
     },

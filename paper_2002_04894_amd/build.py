@@ -26,13 +26,26 @@ FLAGS = [
 ]
 
 
+# sources compiled in several parts (-DFMM_PART=0, 1, ...), each a unit of its own
+PARTS = {"m2l_quad.hip": 4}
+
+
 def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+def units():
+    """(source, part or None), those in parts first: they take longest."""
+    out = []
+    for src in sources():
+        out += [(src, k) for k in range(PARTS.get(os.path.basename(src), 0))] or [(src, None)]
+    return sorted(out, key=lambda u: u[1] is None)
+
+
+def _compile(unit) -> str:
+    src, part = unit
+    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ("" if part is None else f".{part}") + ".o")
+    cmd = [HIPCC, *FLAGS, *([] if part is None else [f"-DFMM_PART={part}"]), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     out = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "not a recognized feature" not in l
                     and "packed-fp32-ops" not in l)
@@ -46,9 +59,9 @@ def _compile(src: str) -> str:
 def build(verbose: bool = True) -> str:
     """Compile every HIP source for gfx950 and link libfmm.so (always rebuilds)."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    srcs = sources()
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
+    todo = units()
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(todo))) as ex:
+        objs = list(ex.map(_compile, todo))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

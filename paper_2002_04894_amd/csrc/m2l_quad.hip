@@ -688,64 +688,70 @@ void launch_one_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStre
   HIPCHECK(hipGetLastError());
 }
 
-template <bool L2L>
-bool launch_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStream_t s) {
-  switch (tb.p) {
-    case 0: launch_one_xlate<0, L2L>(t, l, tb, E, s); break;
-    case 1: launch_one_xlate<1, L2L>(t, l, tb, E, s); break;
-    case 2: launch_one_xlate<2, L2L>(t, l, tb, E, s); break;
-    case 3: launch_one_xlate<3, L2L>(t, l, tb, E, s); break;
-    case 4: launch_one_xlate<4, L2L>(t, l, tb, E, s); break;
-    case 5: launch_one_xlate<5, L2L>(t, l, tb, E, s); break;
-    case 6: launch_one_xlate<6, L2L>(t, l, tb, E, s); break;
-    case 7: launch_one_xlate<7, L2L>(t, l, tb, E, s); break;
-    case 8: launch_one_xlate<8, L2L>(t, l, tb, E, s); break;
-    case 9: launch_one_xlate<9, L2L>(t, l, tb, E, s); break;
-    case 10: launch_one_xlate<10, L2L>(t, l, tb, E, s); break;
-    case 11: launch_one_xlate<11, L2L>(t, l, tb, E, s); break;
-    case 12: launch_one_xlate<12, L2L>(t, l, tb, E, s); break;
-    case 13: launch_one_xlate<13, L2L>(t, l, tb, E, s); break;
-    case 14: launch_one_xlate<14, L2L>(t, l, tb, E, s); break;
-    case 15: launch_one_xlate<15, L2L>(t, l, tb, E, s); break;
-    case 16: launch_one_xlate<16, L2L>(t, l, tb, E, s); break;
-    case 17: launch_one_xlate<17, L2L>(t, l, tb, E, s); break;
-    case 18: launch_one_xlate<18, L2L>(t, l, tb, E, s); break;
-    default: return false;
+// The build compiles this file once for each PART of the orders, PART, PART +
+// kQuadParts, ..., as all of them in one unit would take most of its time.
+constexpr int kQuadParts = 4;
+template <int P>
+bool m2l_from(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s) {
+  if constexpr (P > kMaxOrder) {
+    return false;
+  } else {
+    if (tb.p != P) return m2l_from<P + kQuadParts>(t, tb, Mx, Lx, s);
+    launch_one_quad<P>(t, tb, Mx, Lx, s);
+    return true;
   }
-  static_assert(kQuadXlateMaxP == 18, "the cases above cover orders 0 .. kQuadXlateMaxP");
-  return true;
+}
+template <int P, bool L2L>
+bool xlate_from(const Tree& t, int l, const Tables& tb, double* E, hipStream_t s) {
+  if constexpr (P > kQuadXlateMaxP) {
+    return false;
+  } else {
+    if (tb.p != P) return xlate_from<P + kQuadParts, L2L>(t, l, tb, E, s);
+    launch_one_xlate<P, L2L>(t, l, tb, E, s);
+    return true;
+  }
 }
 
 }  // namespace
 
+// the part's kernel of order tb.p; false if it has none
+template <int PART>
+bool quad_m2l(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s) {
+  return m2l_from<PART>(t, tb, Mx, Lx, s);
+}
+template <int PART, bool L2L>
+bool quad_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStream_t s) {
+  return xlate_from<PART, L2L>(t, l, tb, E, s);
+}
+#define FMM_QUAD_PART(EXTERN, PART)                                                                     \
+  EXTERN template bool quad_m2l<PART>(const Tree&, const Tables&, const double*, double*, hipStream_t); \
+  EXTERN template bool quad_xlate<PART, false>(const Tree&, int, const Tables&, double*, hipStream_t);  \
+  EXTERN template bool quad_xlate<PART, true>(const Tree&, int, const Tables&, double*, hipStream_t);
+#ifdef FMM_PART
+FMM_QUAD_PART(, FMM_PART)
+#endif
+
+#if !defined(FMM_PART) || FMM_PART == 0
+static_assert(kQuadParts == 4, "the parts named here");
+#ifdef FMM_PART
+FMM_QUAD_PART(extern, 1)
+FMM_QUAD_PART(extern, 2)
+FMM_QUAD_PART(extern, 3)
+#endif
+
 // binary64 M2L with this kernel, at every order
 bool launch_m2l_quad64(const Tree& t, const Tables& tb, const double* Mx, double* Lx, hipStream_t s) {
-  switch (tb.p) {
-    case 0: launch_one_quad<0>(t, tb, Mx, Lx, s); break;
-    case 1: launch_one_quad<1>(t, tb, Mx, Lx, s); break;
-    case 2: launch_one_quad<2>(t, tb, Mx, Lx, s); break;
-    case 3: launch_one_quad<3>(t, tb, Mx, Lx, s); break;
-    case 4: launch_one_quad<4>(t, tb, Mx, Lx, s); break;
-    case 5: launch_one_quad<5>(t, tb, Mx, Lx, s); break;
-    case 6: launch_one_quad<6>(t, tb, Mx, Lx, s); break;
-    case 7: launch_one_quad<7>(t, tb, Mx, Lx, s); break;
-    case 8: launch_one_quad<8>(t, tb, Mx, Lx, s); break;
-    case 9: launch_one_quad<9>(t, tb, Mx, Lx, s); break;
-    case 10: launch_one_quad<10>(t, tb, Mx, Lx, s); break;
-    case 11: launch_one_quad<11>(t, tb, Mx, Lx, s); break;
-    case 12: launch_one_quad<12>(t, tb, Mx, Lx, s); break;
-    case 13: launch_one_quad<13>(t, tb, Mx, Lx, s); break;
-    case 14: launch_one_quad<14>(t, tb, Mx, Lx, s); break;
-    case 15: launch_one_quad<15>(t, tb, Mx, Lx, s); break;
-    case 16: launch_one_quad<16>(t, tb, Mx, Lx, s); break;
-    case 17: launch_one_quad<17>(t, tb, Mx, Lx, s); break;
-    case 18: launch_one_quad<18>(t, tb, Mx, Lx, s); break;
-    case 19: launch_one_quad<19>(t, tb, Mx, Lx, s); break;
-    case 20: launch_one_quad<20>(t, tb, Mx, Lx, s); break;
-    default: return false;
-  }
-  return true;
+  return quad_m2l<0>(t, tb, Mx, Lx, s) || quad_m2l<1>(t, tb, Mx, Lx, s) || quad_m2l<2>(t, tb, Mx, Lx, s) ||
+         quad_m2l<3>(t, tb, Mx, Lx, s);
 }
+
+namespace {
+template <bool L2L>
+bool launch_xlate(const Tree& t, int l, const Tables& tb, double* E, hipStream_t s) {
+  return quad_xlate<0, L2L>(t, l, tb, E, s) || quad_xlate<1, L2L>(t, l, tb, E, s) ||
+         quad_xlate<2, L2L>(t, l, tb, E, s) || quad_xlate<3, L2L>(t, l, tb, E, s);
+}
+}  // namespace
 
 // M2M from level l into level l - 1, or L2L from level l - 1 into level l,
 // four lanes per translation: orders up to kQuadXlateMaxP with the tables
@@ -756,5 +762,6 @@ bool launch_m2m_quad64(const Tree& t, int l, const Tables& tb, double* Mx, hipSt
 bool launch_l2l_quad64(const Tree& t, int l, const Tables& tb, double* Lx, hipStream_t s) {
   return tb.quad_l2l != nullptr && t.lev[l].nbox % 16 == 0 && launch_xlate<true>(t, l, tb, Lx, s);
 }
+#endif
 
 }  // namespace fmm
