@@ -736,10 +736,11 @@ __global__ __launch_bounds__(64 * W) void k_p2m(LevelView lv, XT tb, const doubl
   for (int k = lane; k < nt; k += 64) acc[k] = 0.0;
   if constexpr (STAGED) stage_rec(tb, cc);
   __syncthreads();
-  for (int c0 = s0 + 64 * wave; c0 < s1; c0 += 64 * W) {
-    const int t = c0 + lane;
-    const bool valid = t < s1;
-    const int nrow = s1 - c0 < 64 ? s1 - c0 : 64;  // rows of points
+  // positions are unsigned: past the last point they may exceed 2^31
+  for (unsigned c0 = (unsigned)s0 + 64 * wave; c0 < (unsigned)s1; c0 += 64 * W) {
+    const unsigned t = c0 + lane;
+    const bool valid = t < (unsigned)s1;
+    const int nrow = s1 - c0 < 64 ? (int)(s1 - c0) : 64;  // rows of points
     const double x = valid ? px[t] - cx : 0.0;
     const double y = valid ? py[t] - cy : 0.0;
     const double z = valid ? pz[t] - cz : 0.0;
@@ -849,9 +850,9 @@ __global__ __launch_bounds__(64) void k_l2p(LevelView lv, XT tb, const int32_t* 
                                                          m == 0 ? 0.0 : Lc[tb.pos[cidx(n, m, 1)]] * s2);
   }
   __syncthreads();
-  for (int c0 = s0; c0 < s1; c0 += 64) {
-    const int t = c0 + lane;
-    if (t >= s1) break;
+  for (unsigned c0 = s0; c0 < (unsigned)s1; c0 += 64) {
+    const unsigned t = c0 + lane;
+    if (t >= (unsigned)s1) break;
     const double x = px[t] - cx, y = py[t] - cy, z = pz[t] - cz;
     const double r2 = x * x + y * y + z * z;
     // G and its gradient (complex): value, d/dx, d/dy, d/dz

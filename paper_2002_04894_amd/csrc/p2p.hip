@@ -322,12 +322,13 @@ __device__ __forceinline__ void p2p_targets(const P2PSeg& sg, int t0, int t1, in
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tl = lane % TT, h = lane / TT;
   const bool lane_on = h < R;
-  for (int c0 = t0 + (int)blockIdx.y * T * TT; c0 < t1; c0 += (int)gridDim.y * T * TT) {
+  // positions are unsigned: past the last target they may exceed 2^31
+  for (unsigned c0 = t0 + blockIdx.y * T * TT; c0 < (unsigned)t1; c0 += gridDim.y * T * TT) {
     double f[T][4] = {};
     double x[T], y[T], z[T];
 #pragma unroll
     for (int i = 0; i < T; ++i) {
-      const int t = c0 + tl + i * TT, u = t < t1 ? t : t0;
+      const unsigned t = c0 + tl + i * TT, u = t < (unsigned)t1 ? t : t0;
       x[i] = tx[u];
       y[i] = ty[u];
       z[i] = tz[u];
@@ -489,8 +490,8 @@ __device__ __forceinline__ void p2p_targets(const P2PSeg& sg, int t0, int t1, in
     if (w == 0 && lane < TT) {
 #pragma unroll
       for (int i = 0; i < T; ++i) {
-        const int t = c0 + tl + i * TT;
-        if (t < t1) out.put(t, t0, f[i][0], f[i][1], f[i][2], f[i][3]);
+        const unsigned t = c0 + tl + i * TT;
+        if (t < (unsigned)t1) out.put((int)t, t0, f[i][0], f[i][1], f[i][2], f[i][3]);
       }
     }
     if constexpr (W > 1) __syncthreads();  // red read before the buffers are filled again
@@ -573,7 +574,7 @@ __global__ __launch_bounds__(256) void k_p2p_final(int64_t nleaf, const int32_t*
   const int64_t ns = NEAR ? leaf_seg[b + 1] - leaf_seg[b] : 0;
   if (NEAR && ns <= 1) return;
   const int t0 = start[b], t1 = start[b + 1], nt = t1 - t0;
-  for (int t = t0 + lane; t < t1; t += 64) {
+  for (unsigned t = (unsigned)t0 + lane; t < (unsigned)t1; t += 64) {
     double f = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
     if (NEAR) {
       const double4* pp = part + leaf_part[b] + (t - t0);

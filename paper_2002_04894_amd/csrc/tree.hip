@@ -217,7 +217,7 @@ __global__ __launch_bounds__(BS) void k_orb_round(
       const int D = min(8, 64 - shift);
       for (int i = tid; i < 256; i += BS) hist[i] = 0u;
       __syncthreads();
-      for (int i = tid; i < n; i += BS) {
+      for (unsigned i = tid; i < (unsigned)n; i += BS) {  // unsigned: past the end it may exceed 2^31
         const uint64_t k = okey(cin[start + i]);
         const bool match = (shift == 0) || ((k >> (64 - shift)) == prefix);
         if (match) atomicAdd(&hist[(unsigned)((k << shift) >> (64 - D))], 1u);
@@ -262,9 +262,9 @@ __global__ __launch_bounds__(BS) void k_orb_round(
     // ---- stable partition: low = key-prefix below, or equal and early ----
     int low_base = 0, eq_base = 0;
     double cmax_low = -INFINITY, cmin_high = INFINITY;
-    for (int c0 = 0; c0 < n; c0 += BS) {
-      const int i = c0 + tid;
-      const bool valid = i < n;
+    for (unsigned c0 = 0; c0 < (unsigned)n; c0 += BS) {
+      const unsigned i = c0 + tid;
+      const bool valid = i < (unsigned)n;
       double cx = 0, cy = 0, cz = 0, cc = 0;
       int id = 0;
       bool less = false, match = false;
@@ -388,14 +388,14 @@ __global__ __launch_bounds__(kChunkBS) void k_mb_hist(const double* __restrict__
   if (st.cnt <= 1 || st.shift >= 64) return;  // selection finished
   const int64_t seg = ((int64_t)1 << depth) - 1 + sg;
   const int start = seg_start[seg], n = seg_n[seg];
-  const int i0 = c * kChunk, i1 = min(n, i0 + kChunk);
+  const int i0 = c * kChunk, i1 = n - i0 < kChunk ? n : i0 + kChunk;
   if (i0 >= i1) return;
   const double* cin = st.axis == 0 ? xin : (st.axis == 1 ? yin : zin);
   const int shift = st.shift;
   const int D = min(8, 64 - shift);
   hist[threadIdx.x] = 0u;
   __syncthreads();
-  for (int i = i0 + threadIdx.x; i < i1; i += kChunkBS) {
+  for (unsigned i = i0 + threadIdx.x; i < (unsigned)i1; i += kChunkBS) {
     const uint64_t k = okey(cin[start + i]);
     const bool match = (shift == 0) || ((k >> (64 - shift)) == st.prefix);
     if (match) atomicAdd(&hist[(unsigned)((k << shift) >> (64 - D))], 1u);
@@ -460,10 +460,10 @@ __global__ __launch_bounds__(kChunkBS) void k_mb_count(const double* __restrict_
   const SegSel st = sel[sg];
   const int64_t seg = ((int64_t)1 << depth) - 1 + sg;
   const int start = seg_start[seg], n = seg_n[seg];
-  const int i0 = c * kChunk, i1 = min(n, i0 + kChunk);
+  const int i0 = c * kChunk, i1 = n - i0 < kChunk ? n : i0 + kChunk;
   const double* cin = st.axis == 0 ? xin : (st.axis == 1 ? yin : zin);
   int nl = 0, ne = 0;
-  for (int i = i0 + threadIdx.x; i < i1; i += kChunkBS) {
+  for (unsigned i = i0 + threadIdx.x; i < (unsigned)i1; i += kChunkBS) {
     bool less, match;
     mb_flags(st, cin[start + i], less, match);
     nl += less;
@@ -533,13 +533,13 @@ __global__ __launch_bounds__(kChunkBS) void k_mb_scatter(
   const int64_t seg = ((int64_t)1 << depth) - 1 + sg;
   const int start = seg_start[seg], n = seg_n[seg];
   const int m = n / 2;
-  const int i0 = c * kChunk, i1 = min(n, i0 + kChunk);
+  const int i0 = c * kChunk, i1 = n - i0 < kChunk ? n : i0 + kChunk;
   const int2 bs = cbase[blockIdx.x];
   int low_base = bs.x, eq_base = bs.y;
   double cmax_low = -INFINITY, cmin_high = INFINITY;
-  for (int c0 = i0; c0 < i1; c0 += kChunkBS) {  // block-uniform trip count
-    const int i = c0 + threadIdx.x;
-    const bool valid = i < i1;
+  for (unsigned c0 = i0; c0 < (unsigned)i1; c0 += kChunkBS) {  // block-uniform trip count
+    const unsigned i = c0 + threadIdx.x;
+    const bool valid = i < (unsigned)i1;
     double cx = 0, cy = 0, cz = 0, cc = 0;
     int id = 0;
     bool less = false, match = false;
